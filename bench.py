@@ -69,7 +69,7 @@ def make_inputs(w):
     return np.stack(srcs), np.stack(p0s), np.stack(p1s)
 
 
-def algorithmic_bytes(w, prec, iters_total, solves, fused=False):
+def algorithmic_bytes(w, prec, iters_total, solves, fused=False, resident=False):
     """Algorithmic HBM bytes of every kernel class over `solves` right-hand-side solves
     that took `iters_total` MINRES iterations in total (summed over right-hand sides).
 
@@ -88,6 +88,9 @@ def algorithmic_bytes(w, prec, iters_total, solves, fused=False):
       form      8 (k+1) N      (read z_1..z_k, write u) once per solve of k <= 12
                                iterations (the convergence check)
       init      24 N           (read f; write v1 = r0, u) per solve
+    `resident` is what the kernels do now: no residual vector (its norm comes from inner
+    products the first pass forms from registers, so there is no update pass) and no
+    inverse transforms in the iteration a solve stops in.
     With `fused` (small 1D plans: one launch per solve, one workgroup per right-hand side
     runs the set-up with its first preconditioner apply and every iteration) all of the
     above is the "iter" class.
@@ -101,6 +104,16 @@ def algorithmic_bytes(w, prec, iters_total, solves, fused=False):
         per_iter = 16 * N + (32 * N + s * NS) + 2 * s * NS + (s * NS + 8 * N) + 24 * N
         setup = 24 * N + (8 * N + s * NS) + 2 * s * NS + (s * NS + 8 * N)
         return {"iter": per_iter * iters_total + 8 * N * (iters_total + solves) + setup * solves}
+    if resident:
+        return {
+            "stencil": 16 * N * iters_total,
+            "dstx_fwd": (32 * N + s * NS) * iters_total + (8 * N + s * NS) * solves,
+            "dsty": 2 * s * NS * (applies + iters_total) if ny else 0,
+            "time": 2 * s * NS * applies,
+            "dstx_inv": (s * NS + 8 * N) * iters_total,
+            "form": 8 * N * (iters_total + solves),
+            "init": 24 * N * solves,
+        }
     return {
         "stencil": 16 * N * iters_total,
         "dstx_fwd": (32 * N + s * NS) * iters_total + (8 * N + s * NS) * solves,
@@ -516,7 +529,7 @@ def main():
                                          args.steps * B)
     else:
         abytes = algorithmic_bytes(w, prec, main_run["prof_iters"], args.steps * B,
-                                   fused=main_run["tiles"].get("small", 0) > 0)
+                                   fused=main_run["tiles"].get("small", 0) > 0, resident=True)
     dom = max((k for k in prof if prof[k]["launches"] > 0 and k in abytes), key=lambda k: prof[k]["ms"])
     launches = prof[dom]["launches"]
     avg_s = prof[dom]["ms"] / 1e3 / launches

@@ -61,7 +61,7 @@ int default_wg(int kind, int L, int prec, int maxlds) {
 struct Layout {
   // vectors: V x3, Z x kZSlots, W x2, R
   static constexpr int kVecs = 3 + kZSlots + 2 + 1;
-  size_t twx, twy, twt, beta, abk, sc, sci, coef, scratch, vec[kVecs], kcoef, gst, gflags, gparts, st, partials,
+  size_t twx, twy, twt, beta, abk, sc, sci, coef, scratch, vec[kVecs], gst, gflags, gparts, st, partials,
       counters, total;
 };
 
@@ -138,7 +138,6 @@ Layout make_layout(const DevPlan& P, int prec) {
   Lo.coef = take(sizeof(double) * ((size_t)P.ny1 * P.Mx + (P.ny ? (size_t)P.My * P.nx : 0)));
   Lo.scratch = take(prec == ABAC_PREC_NONE ? 0 : real * (size_t)P.NS * P.B);
   for (int i = 0; i < Layout::kVecs; ++i) Lo.vec[i] = take(sizeof(double) * (size_t)P.N * P.B);
-  Lo.kcoef = take(sizeof(double) * 3 * kBasis * P.B);
   Lo.gst = take(sizeof(GmresState) * P.B);
   Lo.gflags = take(sizeof(GmresFlags) * P.B);
   Lo.gparts = take(sizeof(double) * (size_t)(kGmresMax + 1) * kVecMaxBlocks * P.B);
@@ -198,34 +197,53 @@ abac_status flush_prof(abac_plan* p) {
     if (s_ != ABAC_OK) return s_;                                 \
   } while (0)
 
-// z = P^{-1} r on the plan stream.  In MINRES mode (init != 0 or iter != 0) the
-// first pass reads V_1 (init) or forms the Lanczos vector (iteration) and the last
-// pass writes Z and finishes the scalar update.
-abac_status enqueue_pinv(abac_plan* p, const double* r, double* z, int minres_mode) {
+// The first half of z = P^{-1} r on the plan stream: the forward space transforms and the
+// time pass (in MINRES mode with the partials of <q, P^{-1} q>).  fwd_mode FWD_LANCZOS
+// forms the Lanczos vector as its input.
+abac_status enqueue_pinv_head(abac_plan* p, const double* r, int fwd_mode, int check) {
   const DevPlan& P = p->P;
-  if (p->prec == ABAC_PREC_NONE) {
-    const int mode = minres_mode == 0 ? INV_PLAIN : (minres_mode == 1 ? INV_GAMMA_INIT : INV_GAMMA_ITER);
-    RUN(ABAC_K_DSTX_INV, launch_identity(P, mode, r, z, p->stream));
-    if (minres_mode) RUN(ABAC_K_FIN, launch_fin(P, minres_mode == 1 ? FIN_GAMMA_INIT : FIN_GAMMA_ITER, 0.0, 0, p->stream));
-    return ABAC_OK;
-  }
-  const int check = minres_mode != 0;
-  const int fwd_mode = minres_mode == 2 ? FWD_LANCZOS : FWD_PLAIN;
-  const double* in = minres_mode == 1 ? P.V[1] : r;
-  // in MINRES mode the time pass forms <q, P^{-1} q> and the last pass writes z only
-  const int inv_mode = minres_mode == 0 ? INV_PLAIN : (minres_mode == 1 ? INV_Z_INIT : INV_Z_ITER);
   if (P.wg_s) {
-    RUN(ABAC_K_DSTX_FWD, launch_dst2_fwd(P, p->prec, fwd_mode, check, in, p->stream));
-    RUN(ABAC_K_TIME, launch_time(P, p->prec, check, p->stream));
+    RUN(ABAC_K_DSTX_FWD, launch_dst2_fwd(P, p->prec, fwd_mode, check, r, p->stream));
+  } else {
+    RUN(ABAC_K_DSTX_FWD, launch_dstx_fwd(P, p->prec, fwd_mode, check, r, p->stream));
+    if (P.ny) RUN(ABAC_K_DSTY, launch_dsty(P, p->prec, check, p->stream));
+  }
+  RUN(ABAC_K_TIME, launch_time(P, p->prec, check, p->stream));
+  return ABAC_OK;
+}
+
+// The second half: the inverse space transforms.
+abac_status enqueue_pinv_tail(abac_plan* p, double* z, int inv_mode, int check) {
+  const DevPlan& P = p->P;
+  if (P.wg_s) {
     RUN(ABAC_K_DSTX_INV, launch_dst2_inv(P, p->prec, inv_mode, z, p->stream));
   } else {
-    RUN(ABAC_K_DSTX_FWD, launch_dstx_fwd(P, p->prec, fwd_mode, check, in, p->stream));
-    if (P.ny) RUN(ABAC_K_DSTY, launch_dsty(P, p->prec, check, p->stream));
-    RUN(ABAC_K_TIME, launch_time(P, p->prec, check, p->stream));
     if (P.ny) RUN(ABAC_K_DSTY, launch_dsty(P, p->prec, check, p->stream));
     RUN(ABAC_K_DSTX_INV, launch_dstx_inv(P, p->prec, inv_mode, z, p->stream));
   }
-  if (minres_mode) RUN(ABAC_K_FIN, launch_fin(P, minres_mode == 1 ? FIN_GAMMA_INIT : FIN_GAMMA_ITER, 0.0, 0, p->stream));
+  return ABAC_OK;
+}
+
+// z = P^{-1} r on the plan stream.
+abac_status enqueue_pinv(abac_plan* p, const double* r, double* z) {
+  if (p->prec == ABAC_PREC_NONE) {
+    RUN(ABAC_K_DSTX_INV, launch_identity(p->P, INV_PLAIN, r, z, p->stream));
+    return ABAC_OK;
+  }
+  abac_status s = enqueue_pinv_head(p, r, FWD_PLAIN, 0);
+  return s != ABAC_OK ? s : enqueue_pinv_tail(p, z, INV_PLAIN, 0);
+}
+
+// The MINRES set-up's z_1 = P^{-1} v_1, gamma_1 and the set-up snapshot.
+abac_status enqueue_pinv_init(abac_plan* p) {
+  if (p->prec == ABAC_PREC_NONE) {
+    RUN(ABAC_K_DSTX_INV, launch_identity(p->P, INV_GAMMA_INIT, nullptr, nullptr, p->stream));
+  } else {
+    abac_status s = enqueue_pinv_head(p, p->P.V[1], FWD_PLAIN, 1);
+    if (s == ABAC_OK) s = enqueue_pinv_tail(p, nullptr, INV_Z_INIT, 1);
+    if (s != ABAC_OK) return s;
+  }
+  RUN(ABAC_K_FIN, launch_fin(p->P, FIN_GAMMA_INIT, 0.0, 0, p->stream));
   return ABAC_OK;
 }
 
@@ -259,14 +277,19 @@ abac_status enqueue_iteration(abac_plan* p) {
   }
   RUN(ABAC_K_STENCIL, launch_stencil(P, STENCIL_MINRES, nullptr, nullptr, nullptr, p->stream));
   RUN(ABAC_K_FIN, launch_fin(P, FIN_DELTA, 0.0, 0, p->stream));
-  abac_status s = enqueue_pinv(p, nullptr, nullptr, 2);
-  if (s != ABAC_OK) return s;
-  RUN(ABAC_K_UPDATE, launch_update(P, p->u, p->stream));
-  RUN(ABAC_K_FIN, launch_fin(P, FIN_RNORM, 0.0, 0, p->stream));
+  if (p->prec == ABAC_PREC_NONE) {
+    RUN(ABAC_K_DSTX_INV, launch_identity(P, INV_GAMMA_ITER, nullptr, nullptr, p->stream));
+  } else {
+    abac_status s = enqueue_pinv_head(p, nullptr, FWD_LANCZOS, 1);
+    if (s != ABAC_OK) return s;
+  }
+  // gamma_{j+1} is known after the time pass, so the stopping test comes before the
+  // inverse transforms of z_{j+1}: a solve that stops here skips them
+  RUN(ABAC_K_FIN, launch_fin(P, FIN_GAMMA_ITER, 0.0, 0, p->stream));
   RUN(ABAC_K_FORM, launch_form(P, p->u, p->stream));
   RUN(ABAC_K_RESIDUAL, launch_stencil(P, STENCIL_RESIDUAL, p->u, nullptr, p->f, p->stream));
   RUN(ABAC_K_FIN, launch_fin(P, FIN_RES, 0.0, 0, p->stream));
-  return ABAC_OK;
+  return p->prec == ABAC_PREC_NONE ? ABAC_OK : enqueue_pinv_tail(p, nullptr, INV_Z_ITER, 1);
 }
 
 // The set-up and every iteration end with a kernel that copies the per-RHS state
@@ -721,12 +744,20 @@ abac_status abac_plan_create(int nx, int ny, int nt, double T, double alpha, int
   for (int i = 0; i < kZSlots; ++i) P.Z[i] = reinterpret_cast<double*>(base + Lo.vec[3 + i]);
   for (int i = 0; i < 2; ++i) P.W[i] = reinterpret_cast<double*>(base + Lo.vec[3 + kZSlots + i]);
   P.R = reinterpret_cast<double*>(base + Lo.vec[3 + kZSlots + 2]);
-  P.kcoef = reinterpret_cast<double*>(base + Lo.kcoef);
   P.gst = reinterpret_cast<GmresState*>(base + Lo.gst);
   P.gflags = reinterpret_cast<GmresFlags*>(base + Lo.gflags);
   P.gparts = reinterpret_cast<double*>(base + Lo.gparts);
   P.st = reinterpret_cast<MinresState*>(base + Lo.st);
   P.partials = reinterpret_cast<double*>(base + Lo.partials);
+  // the third inner product's partials: the GMRES partials' region where a right-hand
+  // side's blocks fit it, else the matvec's, which are summed before that pass starts
+  if ((long long)P.nt * P.ny1 / 2 <= (kGmresMax + 1) * kVecMaxBlocks) {
+    P.dot3 = P.gparts;
+    P.dot3_stride = (long long)(kGmresMax + 1) * kVecMaxBlocks;
+  } else {
+    P.dot3 = P.partials + (size_t)PART_DELTA * P.B * P.maxparts;
+    P.dot3_stride = P.maxparts;
+  }
   P.counters = reinterpret_cast<unsigned*>(base + Lo.counters);
   P.coef_x = nullptr;   // constant coefficient until abac_plan_set_coefficient
   P.coef_y = nullptr;
@@ -898,7 +929,7 @@ abac_status abac_apply_A(abac_plan* p, const double* x, double* y) {
 
 abac_status abac_apply_Pinv(abac_plan* p, const double* r, double* z) {
   if (!p || !r || !z) return fail(ABAC_EINVAL, "NULL argument");
-  return enqueue_pinv(p, r, z, 0);
+  return enqueue_pinv(p, r, z);
 }
 
 abac_status abac_apply_T(abac_plan* p, const double* x, double* y) {
@@ -1002,7 +1033,7 @@ abac_status abac_minres_begin(abac_plan* p, const double* f, double* u, double t
     return record_snapshot_event(p);
   }
   RUN(ABAC_K_INIT, launch_init(p->P, f, u, tol, maxit, p->stream));
-  abac_status s = enqueue_pinv(p, nullptr, nullptr, 1);   // ends with the set-up snapshot
+  abac_status s = enqueue_pinv_init(p);   // ends with the set-up snapshot
   if (s != ABAC_OK) return s;
   return record_snapshot_event(p);
 }

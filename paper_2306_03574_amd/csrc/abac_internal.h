@@ -14,15 +14,17 @@ enum : int { ST_IDLE = 0, ST_RUNNING = 1, ST_DONE = 2 };
 constexpr int kSnapRing = 16;   // host snapshot slots per right-hand side
 constexpr size_t kMaxTransformLds = 152 * 1024;   // dynamic LDS per transform block (gfx950: 160 KB per workgroup, 8 KB kept for static LDS)
 
-// Resident Krylov basis: z_1 .. z_kBasis each keep a slot of their own, and the
-// iterate is formed from them (x_j = sum_l y_l z_l) only when a residual check, a
-// breakdown or the end of the solve needs it, so an iteration updates just the
-// residual vector.  From z_{kBasis+1} on, z alternates between two more slots and
-// w and x follow the classic three-term recurrences (after one flush that forms x,
-// w_kBasis and w_{kBasis-1} from the basis).
+// Resident Krylov basis: the z vectors live in a ring of slots, and the w and x
+// recurrences run on coefficient vectors over the kBasis newest of them (a cycle) and
+// over the two w vectors the cycle started from.  The iterate is formed only when a
+// residual check, a breakdown or the end of the solve needs it, and every kBasis
+// iterations a flush forms x and the two newest w and starts the next cycle; no other
+// step of an iteration touches x or w.  z_{j+1} is written while the cycle of z_j is
+// still needed, so the ring holds more than kBasis slots.
 constexpr int kBasis = 12;
 constexpr int kZSlots = kBasis + 2;
-__host__ __device__ inline int zslot(int j) { return j <= kBasis ? j - 1 : kBasis + (j & 1); }
+constexpr int kCoefs = kBasis + 2;   // basis coefficients of a vector: the cycle's z, then the two carried w
+__host__ __device__ inline int zslot(int j) { return (j - 1) % kZSlots; }
 
 struct MinresState {
   double gamma;     // gamma_j, current Lanczos off-diagonal
@@ -32,10 +34,8 @@ struct MinresState {
   double c1, c2;    // Givens cosines c_{j-1}, c_{j-2}
   double s1, s2;    // Givens sines s_{j-1}, s_{j-2}
   double eta;       // running right-hand side of the rotated least-squares problem
-  double wa, wb, wc;  // w_j = wa * Zslot_j - wb * w_{j-1} - wc * w_{j-2}
-  double xc;        // x_j = x_{j-1} + xc * w_j
   double r1, r2;    // r_j = r1 * r_{j-1} + r2 * Vslot_{j+1}
-  double rnorm2;    // ||r_j||^2 from the recurrence
+  double rnorm2;    // ||r_j||^2 from the recurrence (an estimate unless `track`)
   double bnorm2;    // ||b||^2
   double tol2;      // tol^2
   double res2;      // last explicit ||b - A x||^2
@@ -44,13 +44,41 @@ struct MinresState {
   int state;        // ST_*
   int status;       // abac_status of this right-hand side
   int explicit_mode;
-  int need_check;   // set by the form kernel: confirm convergence explicitly
+  int need_check;   // the recurrence cannot exclude convergence: confirm it explicitly
   int lucky;        // gamma_{j+1} == 0: the Krylov space is invariant
   int snap;         // sequence number of the next host snapshot
-  int nbasis;       // basis slots with coefficients (basis phase)
+  int cbase;        // iterations before the current cycle of the basis
+  int nbasis;       // z vectors of the current cycle with coefficients
+  int u_valid;      // u holds the iterate the coefficients add to (0: they start from x = 0)
   int basis_dirty;  // u does not yet hold the iterate of the basis coefficients
   int form_now;     // this iteration forms u from the basis (flush: also w_j, w_{j-1})
   int flush_now;
+  int track;        // P.R holds the residual vector, updated by the first transform pass
+  int want_r;       // the explicit check also writes the residual vector to P.R
+};
+
+// More per right-hand side state of a MINRES solve, kept in the right-hand side's GMRES
+// state (the two solvers never run on one plan together).
+//
+// The residual vector r_j = r1 r_{j-1} + r2 V_{j+1} is not stored: its norm decides when
+// to stop, and the first transform pass has V_{j+1}, V_j and V_{j-1} in registers, whose
+// pairwise inner products cost no memory traffic.  Unrolled three steps,
+//   r_j = E + ra V_{j-1} + rb V_j + rc V_{j+1},  E = r1_j r1_{j-1} r1_{j-2} r_{j-3},
+// so ||r_j|| lies within ||E|| of the norm of the last three terms, and ||E|| is at
+// most the product of the r1 (squared sines, small where the iteration converges) and
+// the bound on ||r_{j-3}||.  Convergence is only tested explicitly where that interval
+// reaches the tolerance.  Where it is too wide to decide (slow convergence) the explicit
+// test leaves the residual vector in P.R and the first pass updates it from there on,
+// 16 bytes per unknown.  Against a separate update pass of 24 bytes per unknown and
+// iteration, whole solves (with the inverse passes of the last iteration skipped):
+// 511^2 x 512 FP32 transforms 38.5 -> 32.0 ms, 255^2 x 256 FP64 5.56 -> 4.81 ms,
+// 64 x 127^2 x 128 FP64 37.3 -> 32.2 ms, 63^2 x 64 FP32 0.79 -> 0.71 ms.
+struct MinresExt {
+  double kc[3 * kCoefs];    // coefficients of x_j - u, w_j, w_{j-1}
+  double rb, rc;            // r_j's coefficients on V_j and V_{j+1}
+  double n0, n1, d01;       // ||V_j||^2, ||V_{j+1}||^2, <V_j, V_{j+1}> of the last step
+  double hi[3];             // upper bounds on ||r_j||, ||r_{j-1}||, ||r_{j-2}||
+  double r1p[2];            // r1 of the last two steps
 };
 
 // vector kernels: 256 threads, about 16 elements per thread, at most 1024 blocks per
@@ -74,6 +102,7 @@ struct GmresState {
   int iter, k, maxit, restart, state, status, need, explicit_mode, restart_now;
   int reorth;   // the current column needs the second Gram-Schmidt pass
 };
+static_assert(sizeof(MinresExt) <= sizeof(GmresState), "the MINRES state shares the GMRES state's memory");
 // what the host reads after every step
 struct GmresFlags {
   int state, need, k, iter;
@@ -109,11 +138,12 @@ struct DevPlan {
   double* V[3];
   double* Z[kZSlots];  // slot zslot(j) holds the stored z_j
   double* W[2];
-  double* kcoef;       // per right-hand side, 3 x kBasis: coefficients of x_j, w_j, w_{j-1} on the basis
-  GmresState* gst;     // B entries (GMRES solves)
+  GmresState* gst;     // B entries (GMRES solves; MINRES solves keep their MinresExt there)
   GmresFlags* gflags;  // B entries
   double* gparts;      // B x (kGmresMax + 1) x kVecMaxBlocks partial dot products
-  double* R;
+  double* R;           // MINRES: the residual vector while it is tracked; GMRES: the cycle's first iterate
+  double* dot3;        // third inner product of the first transform pass, one partial per block
+  long long dot3_stride;   // doubles per right-hand side
   MinresState* st;     // B entries
   double* partials;    // PART_KINDS * B * maxparts
   unsigned* counters;  // B entries
@@ -140,6 +170,44 @@ enum PartKind : int { PART_DELTA = 0, PART_GAMMA = 1, PART_RNORM = 2, PART_RES =
 
 __device__ __forceinline__ double* part_slot(const DevPlan& P, int kind, int b) {
   return P.partials + ((size_t)kind * P.B + b) * P.maxparts;
+}
+
+__device__ __forceinline__ MinresExt* minres_ext(const DevPlan& P, int b) {
+  return reinterpret_cast<MinresExt*>(P.gst + b);
+}
+
+// The inner products a block of the first transform pass forms for the stopping test
+// (see MinresExt): <q, q>, then <q, V_j> and <q, V_{j-1}>, or with the residual tracked
+// <q, r_{j-1}> and ||r_{j-1}||^2.  One partial each per block.
+struct Dots3 {
+  double a, b, c;
+};
+__device__ __forceinline__ double* dot_slot(const DevPlan& P, int which, int b) {
+  return which == 0 ? part_slot(P, PART_RNORM, b) : which == 1 ? part_slot(P, PART_RES, b) : P.dot3 + b * P.dot3_stride;
+}
+
+// First half of the block sum of three values: every wave leaves its sums in LDS (the
+// caller places the barrier).  Second half, thread 0: the block's partials.
+__device__ __forceinline__ void dots_reduce(Dots3 d, double (*red)[3]) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    d.a += __shfl_down(d.a, off, 64);
+    d.b += __shfl_down(d.b, off, 64);
+    d.c += __shfl_down(d.c, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    double* r = red[threadIdx.x >> 6];
+    r[0] = d.a;
+    r[1] = d.b;
+    r[2] = d.c;
+  }
+}
+__device__ __forceinline__ void dots_store(const DevPlan& P, int b, int blk, const double (*red)[3]) {
+  if (threadIdx.x < 3) {
+    double s = 0.0;
+    for (int w = 0; w < (int)(blockDim.x + 63) >> 6; ++w) s += red[w][threadIdx.x];
+    dot_slot(P, threadIdx.x, b)[blk] = s;
+  }
 }
 
 // Sum of v over the block; the result is valid in thread 0.  Ends with a barrier so
@@ -193,14 +261,15 @@ enum StencilMode : int {
   STENCIL_PLAIN = 0, STENCIL_MINRES = 1, STENCIL_RESIDUAL = 2, STENCIL_REPORT = 3, STENCIL_T = 4, STENCIL_RESVEC = 5
 };
 enum FwdMode : int { FWD_PLAIN = 0, FWD_LANCZOS = 1 };
-// last pass: INV_PLAIN writes out; the MINRES set-up (INIT) and iteration (ITER) modes
-// write z_1 / z_{j+1} into its basis slot, with (GAMMA) or without (Z: the time pass
-// forms <q, P^{-1} q>) the partial sums of <q, p>
+// last pass: INV_PLAIN writes out; the MINRES set-up and iteration modes write z_1 /
+// z_{j+1} into its basis slot.  The identity preconditioner (GAMMA modes) also forms the
+// partial sums of <q, z>; elsewhere the time pass forms <q, P^{-1} q>.
 enum InvMode : int { INV_PLAIN = 0, INV_GAMMA_INIT = 1, INV_GAMMA_ITER = 2, INV_Z_INIT = 3, INV_Z_ITER = 4 };
 enum FinKind : int {
-  FIN_BNORM = 0, FIN_DELTA = 1, FIN_GAMMA_INIT = 2, FIN_GAMMA_ITER = 3, FIN_RES = 4, FIN_REPORT = 5,
-  FIN_RNORM = 6,   // stopping test on the recurrence residual; decides forming u
-  FIN_FINAL = 7    // end of a solve: form u if it is stale
+  FIN_BNORM = 0, FIN_DELTA = 1, FIN_GAMMA_INIT = 2,
+  FIN_GAMMA_ITER = 3,   // Givens step and stopping test of an iteration; decides forming u
+  FIN_RES = 4, FIN_REPORT = 5,
+  FIN_FINAL = 6    // end of a solve: form u if it is stale
 };
 
 // matvec decomposition: a block covers a band of st_rows grid rows times
@@ -225,7 +294,6 @@ hipError_t launch_stencil(const DevPlan& P, int mode, const double* x, double* y
 hipError_t launch_rhs(const DevPlan& P, const double* src, const double* psi0, const double* psi1, double* f,
                       hipStream_t s);
 hipError_t launch_init(const DevPlan& P, const double* f, double* u, double tol, int maxit, hipStream_t s);
-hipError_t launch_update(const DevPlan& P, double* u, hipStream_t s);
 // identity preconditioner: z = r (mode 0), or the MINRES set-up / Lanczos step with
 // z = q and the partials of <q, q> (modes INV_GAMMA_INIT / INV_GAMMA_ITER)
 hipError_t launch_identity(const DevPlan& P, int mode, const double* in, double* out, hipStream_t s);

@@ -1,6 +1,6 @@
 // Solves of different grids advanced together: one launch per step of a MINRES
 // iteration (Section 3's solver: matvec, Lanczos step with the three transform steps of
-// Section 2.3 done twice, Givens QR, residual recurrence, stopping test) covers every
+// Section 2.3 done twice, Givens QR, residual bounds, stopping test) covers every
 // member of a group, whatever its grid, instead of one launch per step per solve.
 //
 // A launch's blocks are the concatenation of the members' blocks of that step: block w
@@ -92,7 +92,14 @@ __device__ __forceinline__ void group_stencil(const GroupTable* __restrict__ G, 
   const size_t off = (size_t)at.b * P.N;
   double acc = 0.0;
   const bool lane = (int)threadIdx.x < P.st_threads;
-  if (MODE == STENCIL_MINRES) {
+  if (MODE == STENCIL_RESIDUAL && st->want_r) {
+    const double* x = M.u + off;
+    double* y = P.R + off;
+    const double* f = M.f + off;
+    if (lane)
+      acc = P.coef_x ? stencil_run<true, OUT_RESREV, false>(P, x, y, f, at.lbk, at.per, threadIdx.x, true)
+                     : stencil_run<false, OUT_RESREV, false>(P, x, y, f, at.lbk, at.per, threadIdx.x, true);
+  } else if (MODE == STENCIL_MINRES) {
     const int j = st->iter + 1;
     const double* x = P.Z[zslot(j)] + off;
     double* y = P.V[(j + 1) % 3] + off;
@@ -145,28 +152,18 @@ __device__ __forceinline__ void group_fin(const GroupTable* __restrict__ G, int 
   if (!fin_begin(P, at.b, kind)) return;
   int nparts;
   switch (kind) {
-    case FIN_BNORM:
-    case FIN_RNORM: nparts = G->off[GS_VEC][at.r + 1] - G->off[GS_VEC][at.r]; nparts /= P.B; break;
     case FIN_DELTA: nparts = stencil_blocks(P); break;
     case FIN_GAMMA_INIT:
     case FIN_GAMMA_ITER: nparts = P.gamma_nparts; break;
     default: nparts = stencil_blocks(P); break;
   }
+  Dots3 dots{0.0, 0.0, 0.0};
+  if (kind == FIN_GAMMA_ITER) dots = sum_dots(P, at.b, (G->off[GS_XFWD][at.r + 1] - G->off[GS_XFWD][at.r]) / P.B);
   const double tot = sum_parts_as(part_slot(P, fin_part_kind(kind), at.b), nparts, kGroupFinThreads);
-  if (threadIdx.x == 0) fin_scalar(P, at.b, kind, tot, 0.0, 0);
+  if (threadIdx.x == 0) fin_scalar(P, at.b, kind, tot, dots, 0.0, 0);
 }
 
-// ---- vector steps: residual recurrence, iterate from the basis ----------------------
-__device__ __forceinline__ void group_update(const GroupTable* __restrict__ G, int w) {
-  const Where at = locate(G, GS_VEC, w);
-  const GroupMember& M = G->m[at.r];
-  const DevPlan& P = M.P;
-  if (P.st[at.b].state != ST_RUNNING) return;
-  const double acc = update_part(P, at.b, M.u, at.lbk, at.per);
-  const double bs = block_sum(acc);
-  if (threadIdx.x == 0) part_slot(P, PART_RNORM, at.b)[at.lbk] = bs;
-}
-
+// ---- vector step: iterate from the basis --------------------------------------------
 __device__ __forceinline__ void group_form(const GroupTable* __restrict__ G, int w) {
   const Where at = locate(G, GS_VEC, w);
   const GroupMember& M = G->m[at.r];
@@ -242,14 +239,14 @@ __device__ __forceinline__ void group_xinv(const GroupTable* __restrict__ G, int
   const int L = 2 * P.Mx;
   if (P.wg_s) {
 #define CASE(LL) \
-    case LL: if constexpr (slab_ok<T, LL, kGroupWG>()) (void)dst2_inv_tile<T, LL, kGroupWG>(P, mode, nullptr, at.b, at.lbk); break;
+    case LL: if constexpr (slab_ok<T, LL, kGroupWG>()) dst2_inv_tile<T, LL, kGroupWG>(P, mode, nullptr, at.b, at.lbk); break;
     switch (L) { ABAC_GROUP_SLAB_LENGTHS(CASE) default: break; }
 #undef CASE
   } else {
 #define CASE(LL)                                                                                                     \
     case LL:                                                                                                         \
       if constexpr (tile_ok<T, LL, kGroupWG, TK_XINV>())                                                             \
-        (void)dstx_inv_tile<T, LL, kGroupWG>(P, mode, nullptr, at.b, at.lbk, reinterpret_cast<const cplx<T>*>(P.twx)); \
+        dstx_inv_tile<T, LL, kGroupWG>(P, mode, nullptr, at.b, at.lbk, reinterpret_cast<const cplx<T>*>(P.twx)); \
       break;
     switch (L) { ABAC_GROUP_X_LENGTHS(CASE) default: break; }
 #undef CASE
@@ -267,9 +264,6 @@ __global__ void __launch_bounds__(kGroupWG) k_group_stencil(const GroupTable* __
 }
 __global__ void __launch_bounds__(kGroupFinThreads) k_group_fin(const GroupTable* __restrict__ G, int kind) {
   group_fin(G, blockIdx.x, kind);
-}
-__global__ void __launch_bounds__(kGroupWG) k_group_update(const GroupTable* __restrict__ G) {
-  group_update(G, blockIdx.x);
 }
 __global__ void __launch_bounds__(kGroupWG) k_group_form(const GroupTable* __restrict__ G) {
   group_form(G, blockIdx.x);
@@ -345,7 +339,6 @@ __device__ __forceinline__ bool grid_barrier(GridSync* gs, unsigned& gen, unsign
 template <int MODE>
 __device__ __noinline__ void ps_stencil(const GroupTable* G, int w) { group_stencil<MODE>(G, w); }
 __device__ __noinline__ void ps_fin(const GroupTable* G, int w, int kind) { group_fin(G, w, kind); }
-__device__ __noinline__ void ps_update(const GroupTable* G, int w) { group_update(G, w); }
 __device__ __noinline__ void ps_form(const GroupTable* G, int w) { group_form(G, w); }
 template <typename T>
 __device__ __noinline__ void ps_xfwd(const GroupTable* G, int w) { group_xfwd<T>(G, w); }
@@ -381,14 +374,12 @@ k_group_persistent(const GroupTable* __restrict__ G, int iterations, GridSync* g
     ABAC_STEP(GS_XFWD, ps_xfwd<T>(G, w))
     ABAC_STEP(GS_Y, ps_y<T>(G, w))
     ABAC_STEP(GS_TIME, ps_time<T>(G, w))
-    ABAC_STEP(GS_Y, ps_y<T>(G, w))
-    ABAC_STEP(GS_XINV, ps_xinv<T>(G, w))
     ABAC_STEP(GS_FIN, ps_fin(G, w, FIN_GAMMA_ITER))
-    ABAC_STEP(GS_VEC, ps_update(G, w))
-    ABAC_STEP(GS_FIN, ps_fin(G, w, FIN_RNORM))
     ABAC_STEP(GS_VEC, ps_form(G, w))
     ABAC_STEP(GS_STENCIL, ps_stencil<STENCIL_RESIDUAL>(G, w))
     ABAC_STEP(GS_FIN, ps_fin(G, w, FIN_RES))
+    ABAC_STEP(GS_Y, ps_y<T>(G, w))
+    ABAC_STEP(GS_XINV, ps_xinv<T>(G, w))
 #undef ABAC_STEP
   }
 }
@@ -487,14 +478,12 @@ abac_status group_iteration(abac_group* g) {
   GRUN(group_launch(g, GS_XFWD, kGroupWG, k_group_xfwd<T>));
   GRUN(group_launch(g, GS_Y, kGroupWG, k_group_y<T>));
   GRUN(group_launch(g, GS_TIME, kGroupWG, k_group_time<T>));
-  GRUN(group_launch(g, GS_Y, kGroupWG, k_group_y<T>));
-  GRUN(group_launch(g, GS_XINV, kGroupWG, k_group_xinv<T>));
   GRUN(group_launch(g, GS_FIN, kGroupFinThreads, k_group_fin, (int)FIN_GAMMA_ITER));
-  GRUN(group_launch(g, GS_VEC, kGroupWG, k_group_update));
-  GRUN(group_launch(g, GS_FIN, kGroupFinThreads, k_group_fin, (int)FIN_RNORM));
   GRUN(group_launch(g, GS_VEC, kGroupWG, k_group_form));
   GRUN(group_launch(g, GS_STENCIL, kGroupWG, k_group_stencil<STENCIL_RESIDUAL>));
   GRUN(group_launch(g, GS_FIN, kGroupFinThreads, k_group_fin, (int)FIN_RES));
+  GRUN(group_launch(g, GS_Y, kGroupWG, k_group_y<T>));
+  GRUN(group_launch(g, GS_XINV, kGroupWG, k_group_xinv<T>));
   return ABAC_OK;
 }
 

@@ -23,21 +23,31 @@ namespace {
 
 constexpr int kSmallWG = 512;
 
-// u = sum_l xm_l z_l over the first nb basis slots (with flush also the two w vectors
-// from their coefficients), the whole right-hand side by one workgroup.
-__device__ void form_small(const DevPlan& P, int b, double* __restrict__ u, int nb, bool flush) {
+// u = [u +] sum_l xm_l z_l over the current cycle of the basis and the carried w vectors
+// (with flush also the two w vectors from their coefficients), the whole right-hand
+// side by one workgroup.
+__device__ void form_small(const DevPlan& P, int b, double* __restrict__ u) {
   const size_t off = (size_t)b * P.N;
-  const double* kc = P.kcoef + (size_t)b * 3 * kBasis;
+  const MinresState* st = P.st + b;
+  const double* kc = minres_ext(P, b)->kc;
+  const int nb = st->nbasis, base = st->cbase;
+  const bool flush = st->flush_now != 0, add = st->u_valid != 0;
   double* X = u + off;
-  double* W1 = P.W[kBasis & 1] + off;
-  double* W2 = P.W[(kBasis + 1) & 1] + off;
+  double* W1 = P.W[0] + off;
+  double* W2 = P.W[1] + off;
   for (int e = threadIdx.x; e < P.N; e += blockDim.x) {
-    double ax = 0.0, a1 = 0.0, a2 = 0.0;
+    double ax = add ? X[e] : 0.0, a1 = 0.0, a2 = 0.0;
+    if (base) {
+      const double p = W1[e], q = W2[e];
+      ax += kc[kBasis] * p + kc[kBasis + 1] * q;
+      a1 = kc[kCoefs + kBasis] * p + kc[kCoefs + kBasis + 1] * q;
+      a2 = kc[2 * kCoefs + kBasis] * p + kc[2 * kCoefs + kBasis + 1] * q;
+    }
     for (int l = 0; l < nb; ++l) {
-      const double z = P.Z[l][off + e];
+      const double z = P.Z[zslot(base + l + 1)][off + e];
       ax += kc[l] * z;
-      a1 += kc[kBasis + l] * z;
-      a2 += kc[2 * kBasis + l] * z;
+      a1 += kc[kCoefs + l] * z;
+      a2 += kc[2 * kCoefs + l] * z;
     }
     X[e] = ax;
     if (flush) {
@@ -105,14 +115,15 @@ __device__ __noinline__ void iter_small(const DevPlan& P, const double* __restri
     const int j = st->iter + 1;
     const double acc = stencil_small<OUT_REV, true>(P, P.Z[zslot(j)] + off, P.V[(j + 1) % 3] + off, nullptr);
     const double tot = block_sum(acc);
-    if (fin_begin(P, b, FIN_DELTA) && tid == 0) fin_scalar(P, b, FIN_DELTA, tot, 0.0, 0);
+    if (fin_begin(P, b, FIN_DELTA) && tid == 0) fin_scalar(P, b, FIN_DELTA, tot, Dots3{}, 0.0, 0);
     __syncthreads();
   }
-  // Lanczos vector and z_{j+1} = P^{-1} q: x-DST (Lanczos fused), time pass with the
-  // partials of <q, P^{-1} q>, inverse x-DST, then gamma_{j+1} and the Givens step
+  // Lanczos vector and the first half of z_{j+1} = P^{-1} q: x-DST (Lanczos fused), time
+  // pass with the partials of <q, P^{-1} q>; then gamma_{j+1}, the Givens step and the
+  // stopping test
+  constexpr int SX = seqs_of<T, L, WG>(), ST = seqs_of<T, NT, WG>();
+  const int xtiles = (P.nt + 2 * SX - 1) / (2 * SX);
   if (st->state == ST_RUNNING) {
-    constexpr int SX = seqs_of<T, L, WG>(), ST = seqs_of<T, NT, WG>();
-    const int xtiles = (P.nt + 2 * SX - 1) / (2 * SX);
     const int ttiles = (P.ms / 2 + ST - 1) / ST;
     for (int t = 0; t < xtiles; ++t) {
       dstx_fwd_tile<T, L, WG>(P, FWD_LANCZOS, nullptr, b, t, twx);
@@ -122,32 +133,31 @@ __device__ __noinline__ void iter_small(const DevPlan& P, const double* __restri
       time_tile<T, NT, WG>(P, 0, b, t, 1);
       __syncthreads();
     }
+    const Dots3 dots = sum_dots(P, b, xtiles);
     const double tot = sum_parts(part_slot(P, PART_GAMMA, b), P.ms / 2);
-    for (int t = 0; t < xtiles; ++t) {
-      dstx_inv_tile<T, L, WG>(P, INV_Z_ITER, nullptr, b, t, twx);
-      __syncthreads();
-    }
-    if (fin_begin(P, b, FIN_GAMMA_ITER) && tid == 0) fin_scalar(P, b, FIN_GAMMA_ITER, tot, 0.0, 0);
-    __syncthreads();
-  }
-  // residual recurrence and the stopping test (a stopped solve marks a stale u)
-  {
-    double tot = 0.0;
-    if (st->state == ST_RUNNING) tot = block_sum(update_part(P, b, u, 0, 1));
-    if (fin_begin(P, b, FIN_RNORM) && tid == 0) fin_scalar(P, b, FIN_RNORM, tot, 0.0, 0);
+    if (fin_begin(P, b, FIN_GAMMA_ITER) && tid == 0) fin_scalar(P, b, FIN_GAMMA_ITER, tot, dots, 0.0, 0);
     __syncthreads();
   }
   // the iterate from the resident basis when a check, a stop or the flush needs it
   if (st->form_now) {
-    form_small(P, b, u, st->nbasis, st->flush_now != 0);
+    form_small(P, b, u);
     __syncthreads();
   }
-  // explicit residual check, end of the iteration (snapshot)
+  // explicit residual check, end of the scalar steps (snapshot)
   {
     double tot = 0.0;
     if (st->state == ST_RUNNING && st->need_check)
-      tot = block_sum(stencil_small<OUT_RESNORM, false>(P, u + off, nullptr, f + off));
-    if (fin_begin(P, b, FIN_RES) && tid == 0) fin_scalar(P, b, FIN_RES, tot, 0.0, 0);
+      tot = block_sum(st->want_r ? stencil_small<OUT_RESREV, false>(P, u + off, P.R + off, f + off)
+                                 : stencil_small<OUT_RESNORM, false>(P, u + off, nullptr, f + off));
+    if (fin_begin(P, b, FIN_RES) && tid == 0) fin_scalar(P, b, FIN_RES, tot, Dots3{}, 0.0, 0);
+    __syncthreads();
+  }
+  // the second half of z_{j+1}: inverse x-DST
+  if (st->state == ST_RUNNING) {
+    for (int t = 0; t < xtiles; ++t) {
+      dstx_inv_tile<T, L, WG>(P, INV_Z_ITER, nullptr, b, t, twx);
+      __syncthreads();
+    }
   }
 }
 
@@ -179,7 +189,7 @@ __device__ __noinline__ void setup_small(const DevPlan& P, const double* __restr
       acc += v * v;
     }
     const double tot = block_sum(acc);
-    if (fin_begin(P, b, FIN_BNORM) && tid == 0) fin_scalar(P, b, FIN_BNORM, tot, tol, maxit);
+    if (fin_begin(P, b, FIN_BNORM) && tid == 0) fin_scalar(P, b, FIN_BNORM, tot, Dots3{}, tol, maxit);
     __syncthreads();
   }
   double tot = 0.0;
@@ -201,7 +211,7 @@ __device__ __noinline__ void setup_small(const DevPlan& P, const double* __restr
       __syncthreads();
     }
   }
-  if (fin_begin(P, b, FIN_GAMMA_INIT) && tid == 0) fin_scalar(P, b, FIN_GAMMA_INIT, tot, 0.0, 0);
+  if (fin_begin(P, b, FIN_GAMMA_INIT) && tid == 0) fin_scalar(P, b, FIN_GAMMA_INIT, tot, Dots3{}, 0.0, 0);
 }
 
 template <typename T, int L, int NT>

@@ -4,8 +4,9 @@
 //     nt-1-k of z without a second read of z;
 //   * the explicit residual ||f - T u|| used to confirm convergence;
 //   * right-hand side assembly of eq. (1.2);
-//   * solve set-up, the MINRES w / x / r update and the scalar steps (Givens QR of the
-//     Lanczos tridiagonal matrix, stopping test) run by one block per right-hand side.
+//   * solve set-up, forming the iterate from the resident basis, and the scalar steps
+//     (Givens QR of the Lanczos tridiagonal matrix, stopping test) run by one block per
+//     right-hand side.
 #include "abac_internal.h"
 #include "minres_device.h"
 #include "stencil_device.h"
@@ -45,7 +46,9 @@ k_stencil(DevPlan P, const double* __restrict__ xin, double* __restrict__ yout, 
     return;
   }
   double acc;
-  if (MODE == STENCIL_MINRES)
+  if (MODE == STENCIL_RESIDUAL && st->want_r)
+    acc = stencil_run<VAR, OUT_RESREV, false>(P, x, P.R + (size_t)b * P.N, f, blockIdx.x, gridDim.x, threadIdx.x, true);
+  else if (MODE == STENCIL_MINRES)
     acc = stencil_run<VAR, OUT_REV, true>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x, true);
   else if (MODE == STENCIL_RESVEC)
     acc = stencil_run<VAR, OUT_RESVEC, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x, true);
@@ -76,9 +79,9 @@ k_rhs(DevPlan P, const double* __restrict__ src, const double* __restrict__ psi0
   }
 }
 
-// Set-up of a solve: b = Y f into V_1, zero u; ||b||^2 partials.  (r_0 = b is read from
-// V_1 by the first residual update, v_0 is never read, and the w vectors are written
-// by the flush of the resident basis before they are first read.)
+// Set-up of a solve: b = Y f into V_1, zero u; ||b||^2 partials.  (v_0 is never read, and
+// the w vectors are written by the flush of the resident basis before they are first
+// read.)
 __global__ void __launch_bounds__(kVecThreads)
 k_init(DevPlan P, const double* __restrict__ f, double* __restrict__ u) {
   const int b = blockIdx.y;
@@ -92,7 +95,7 @@ k_init(DevPlan P, const double* __restrict__ f, double* __restrict__ u) {
     const int k = (int)(e / P.m);
     const size_t i = e - (size_t)k * P.m;
     const double v = f[off + (size_t)(P.nt - 1 - k) * P.m + i];
-    P.V[1][off + e] = v;   // v_1 = r_0 (the first update reads it as r_0)
+    P.V[1][off + e] = v;
     u[off + e] = 0.0;
     acc += v * v;
   }
@@ -100,19 +103,8 @@ k_init(DevPlan P, const double* __restrict__ f, double* __restrict__ u) {
   if (threadIdx.x == 0) part_slot(P, PART_RNORM, b)[blockIdx.x] = bs;
 }
 
-// Residual recurrence r = r1 r + r2 V_{j+1} and ||r||^2 partials; after the resident
-// basis (j > kBasis) also w_j = wa Z_j - wb w_{j-1} - wc w_{j-2} and x += xc w_j.
-__global__ void __launch_bounds__(kVecThreads)
-k_update(DevPlan P, double* __restrict__ u) {
-  const int b = blockIdx.y;
-  if (P.st[b].state != ST_RUNNING) return;
-  const double acc = update_part(P, b, u, blockIdx.x, gridDim.x);
-  const double bs = block_sum(acc);
-  if (threadIdx.x == 0) part_slot(P, PART_RNORM, b)[blockIdx.x] = bs;
-}
-
 // Forms u (and at the flush w_j, w_{j-1}) from the resident basis for the right-hand
-// sides whose scalar step (FIN_RNORM or FIN_FINAL) set form_now; the others return at
+// sides whose scalar step (FIN_GAMMA_ITER or FIN_FINAL) set form_now; the others return at
 // once.  Writes no solve state.
 __global__ void __launch_bounds__(kVecThreads)
 k_form(DevPlan P, double* __restrict__ u) {
@@ -169,11 +161,13 @@ k_identity(DevPlan P, int mode, const double* __restrict__ in, double* __restric
 constexpr int kFinThreads = 1024;
 
 __global__ void __launch_bounds__(kFinThreads)
-k_fin(DevPlan P, int kind, int nparts, double tol, int maxit) {
+k_fin(DevPlan P, int kind, int nparts, int ndots, double tol, int maxit) {
   const int b = blockIdx.x;
   if (!fin_begin(P, b, kind)) return;
+  Dots3 dots{0.0, 0.0, 0.0};
+  if (kind == FIN_GAMMA_ITER) dots = sum_dots(P, b, ndots);
   const double tot = sum_parts(part_slot(P, fin_part_kind(kind), b), nparts);
-  if (threadIdx.x == 0) fin_scalar(P, b, kind, tot, tol, maxit);
+  if (threadIdx.x == 0) fin_scalar(P, b, kind, tot, dots, tol, maxit);
 }
 
 }  // namespace
@@ -230,12 +224,6 @@ hipError_t launch_init(const DevPlan& P, const double* f, double* u, double tol,
   return launch_fin(P, FIN_BNORM, tol, maxit, s);
 }
 
-hipError_t launch_update(const DevPlan& P, double* u, hipStream_t s) {
-  dim3 grid(update_blocks(P), P.B);
-  hipLaunchKernelGGL(k_update, grid, dim3(kVecThreads), 0, s, P, u);
-  return hipGetLastError();
-}
-
 hipError_t launch_form(const DevPlan& P, double* u, hipStream_t s) {
   dim3 grid(update_blocks(P), P.B);
   hipLaunchKernelGGL(k_form, grid, dim3(kVecThreads), 0, s, P, u);
@@ -251,14 +239,15 @@ hipError_t launch_identity(const DevPlan& P, int mode, const double* in, double*
 hipError_t launch_fin(const DevPlan& P, int kind, double tol, int maxit, hipStream_t s) {
   int nparts;
   switch (kind) {
-    case FIN_BNORM:
-    case FIN_RNORM: nparts = update_blocks(P); break;
+    case FIN_BNORM: nparts = update_blocks(P); break;
     case FIN_DELTA: nparts = stencil_grid(P, STENCIL_MINRES); break;
     case FIN_GAMMA_INIT:
     case FIN_GAMMA_ITER: nparts = P.gamma_nparts; break;
     default: nparts = stencil_grid(P, STENCIL_RESIDUAL); break;
   }
-  hipLaunchKernelGGL(k_fin, dim3(P.B), dim3(kFinThreads), 0, s, P, kind, nparts, tol, maxit);
+  // blocks of the first transform pass, which leave the inner products' partials
+  const int ndots = kind != FIN_GAMMA_ITER || P.prec == 2 ? 0 : P.wg_s ? P.nt : dstx_blocks(P, P.wg_x);
+  hipLaunchKernelGGL(k_fin, dim3(P.B), dim3(kFinThreads), 0, s, P, kind, nparts, ndots, tol, maxit);
   return hipGetLastError();
 }
 

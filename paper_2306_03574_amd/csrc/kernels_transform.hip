@@ -57,10 +57,7 @@ __global__ void __launch_bounds__(WG)
 k_dstx_inv(DevPlan P, int mode, double* __restrict__ outp) {
   const int b = blockIdx.y;
   if (mode != INV_PLAIN && P.st[b].state != ST_RUNNING) return;
-  const double acc = dstx_inv_tile<T, L, WG>(P, mode, outp, b, blockIdx.x, reinterpret_cast<const cplx<T>*>(P.twx));
-  if (mode != INV_GAMMA_INIT && mode != INV_GAMMA_ITER) return;
-  const double bs = block_sum(acc);
-  if (threadIdx.x == 0) part_slot(P, PART_GAMMA, b)[blockIdx.x] = bs;
+  dstx_inv_tile<T, L, WG>(P, mode, outp, b, blockIdx.x, reinterpret_cast<const cplx<T>*>(P.twx));
 }
 
 // fused 2D passes (square grids whose level fits in LDS; tile bodies in
@@ -74,18 +71,14 @@ k_dst2_fwd(DevPlan P, int mode, int check, const double* __restrict__ in) {
   dst2_fwd_tile<T, L, WG>(P, mode, in, blockIdx.y, blockIdx.x);
 }
 
-// last pass, fused: DST-I along y and x of one level of the scratch, FP64 rows out,
-// with the block's partial of <q, p> in the GAMMA modes (one partial per level).  Modes
-// as in k_dstx_inv.
+// last pass, fused: DST-I along y and x of one level of the scratch, FP64 rows out.
+// Modes as in k_dstx_inv.
 template <typename T, int L, int WG>
 __global__ void __launch_bounds__(WG)
 k_dst2_inv(DevPlan P, int mode, double* __restrict__ outp) {
   const int b = blockIdx.y;
   if (mode != INV_PLAIN && P.st[b].state != ST_RUNNING) return;
-  const double acc = dst2_inv_tile<T, L, WG>(P, mode, outp, b, blockIdx.x);
-  if (mode != INV_GAMMA_INIT && mode != INV_GAMMA_ITER) return;
-  const double bs = block_sum(acc);
-  if (threadIdx.x == 0) part_slot(P, PART_GAMMA, b)[blockIdx.x] = bs;
+  dst2_inv_tile<T, L, WG>(P, mode, outp, b, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------

@@ -1,7 +1,7 @@
 // Device code of the MINRES steps (Section 3's solver; Paige-Saunders recurrences in
-// the P^{-1} inner product): the residual / w / x update, forming the iterate from the
-// resident Krylov basis, and the per-right-hand-side scalar steps (sums of partials,
-// Givens QR, stopping test, snapshots).  Shared by the separate kernels and the fused
+// the P^{-1} inner product): forming the iterate from the resident Krylov basis, and the
+// per-right-hand-side scalar steps (sums of partials, Givens QR, bounds on the residual
+// norm, stopping test, snapshots).  Shared by the separate kernels and the fused
 // small-problem iteration.
 #pragma once
 #include "abac_internal.h"
@@ -9,65 +9,29 @@
 namespace abac {
 namespace {
 
-// Residual recurrence r = r1 r + r2 V_{j+1} and ||r||^2 partials; after the resident
-// basis (j > kBasis) also w_j = wa Z_j - wb w_{j-1} - wc w_{j-2} and x += xc w_j.
-// Elements [part N/nparts, (part+1) N/nparts) of right-hand side b; returns this
-// thread's part of ||r||^2.  The caller skips stopped right-hand sides.
-__device__ __forceinline__ double update_part(const DevPlan& P, int b, double* __restrict__ u, int part,
-                                              int nparts) {
-  const MinresState* st = P.st + b;
-  const int j = st->iter;
-  const double wa = st->wa, wb = st->wb, wc = st->wc, xc = st->xc, r1 = st->r1, r2 = st->r2;
-  const size_t off = (size_t)b * P.N;
-  const double* __restrict__ Vn = P.V[(j + 1) % 3] + off;
-  double* __restrict__ R = P.R + off;
-  const double* __restrict__ Rin = j == 1 ? P.V[1] + off : R;   // r_0 = v_1
-  const size_t per = ((size_t)P.N + nparts - 1) / nparts;
-  const size_t lo = (size_t)part * per;
-  const size_t hi = lo + per < (size_t)P.N ? lo + per : (size_t)P.N;
-  double acc = 0.0;
-  if (j <= kBasis) {
-    for (size_t e = lo + threadIdx.x; e < hi; e += blockDim.x) {
-      const double r = r1 * Rin[e] + r2 * Vn[e];
-      R[e] = r;
-      acc += r * r;
-    }
-  } else {
-    const double* __restrict__ Zj = P.Z[zslot(j)] + off;
-    const double* __restrict__ Wm1 = P.W[(j - 1) & 1] + off;
-    double* __restrict__ Wm2 = P.W[j & 1] + off;
-    double* __restrict__ X = u + off;
-    for (size_t e = lo + threadIdx.x; e < hi; e += blockDim.x) {
-      const double w = wa * Zj[e] - wb * Wm1[e] - wc * Wm2[e];
-      Wm2[e] = w;
-      X[e] += xc * w;
-      const double r = r1 * R[e] + r2 * Vn[e];
-      R[e] = r;
-      acc += r * r;
-    }
-  }
-  return acc;
-}
-
-// u = sum_l xm_l Z_l over the first NB basis slots; with FLUSH also
-// W[kBasis & 1] = w_kBasis and W[(kBasis+1) & 1] = w_{kBasis-1} from their coefficients.
+// u = [u +] sum_l xm_l z_l over the NB vectors of the current cycle, plus the two carried
+// w vectors of a later cycle; with FLUSH also W[0] = w_j and W[1] = w_{j-1} from their
+// coefficients.  Elements [part N/nparts, (part+1) N/nparts) of right-hand side b.
 template <int NB, bool FLUSH>
 __device__ __forceinline__ void form_from_basis(const DevPlan& P, int b, double* __restrict__ u, int part,
                                                 int nparts) {
   const size_t off = (size_t)b * P.N;
-  const double* kc = P.kcoef + (size_t)b * 3 * kBasis;
+  const MinresState* st = P.st + b;
+  const double* kc = minres_ext(P, b)->kc;
+  const int base = st->cbase;
+  const bool add = st->u_valid != 0, carry = base != 0;
   double cx[NB], c1[NB], c2[NB];
   const double* zs[NB];
 #pragma unroll
   for (int l = 0; l < NB; ++l) {
     cx[l] = kc[l];
-    c1[l] = FLUSH ? kc[kBasis + l] : 0.0;
-    c2[l] = FLUSH ? kc[2 * kBasis + l] : 0.0;
-    zs[l] = P.Z[l] + off;
+    c1[l] = FLUSH ? kc[kCoefs + l] : 0.0;
+    c2[l] = FLUSH ? kc[2 * kCoefs + l] : 0.0;
+    zs[l] = P.Z[zslot(base + l + 1)] + off;
   }
   double* X = u + off;
-  double* W1 = P.W[kBasis & 1] + off;
-  double* W2 = P.W[(kBasis + 1) & 1] + off;
+  double* W1 = P.W[0] + off;
+  double* W2 = P.W[1] + off;
   const size_t per = ((size_t)P.N + nparts - 1) / nparts;
   const size_t lo = (size_t)part * per;
   const size_t hi = lo + per < (size_t)P.N ? lo + per : (size_t)P.N;
@@ -82,6 +46,21 @@ __device__ __forceinline__ void form_from_basis(const DevPlan& P, int b, double*
       z1[l] = zs[l][e1c];
     }
     double ax0 = 0.0, a10 = 0.0, a20 = 0.0, ax1 = 0.0, a11 = 0.0, a21 = 0.0;
+    if (add) {
+      ax0 = X[e0];
+      ax1 = X[e1c];
+    }
+    if (carry) {
+      const double p0 = W1[e0], q0 = W2[e0], p1 = W1[e1c], q1 = W2[e1c];
+      ax0 += kc[kBasis] * p0 + kc[kBasis + 1] * q0;
+      ax1 += kc[kBasis] * p1 + kc[kBasis + 1] * q1;
+      if (FLUSH) {
+        a10 = kc[kCoefs + kBasis] * p0 + kc[kCoefs + kBasis + 1] * q0;
+        a11 = kc[kCoefs + kBasis] * p1 + kc[kCoefs + kBasis + 1] * q1;
+        a20 = kc[2 * kCoefs + kBasis] * p0 + kc[2 * kCoefs + kBasis + 1] * q0;
+        a21 = kc[2 * kCoefs + kBasis] * p1 + kc[2 * kCoefs + kBasis + 1] * q1;
+      }
+    }
 #pragma unroll
     for (int l = 0; l < NB; ++l) {
       ax0 += cx[l] * z0[l];
@@ -110,27 +89,80 @@ __device__ __forceinline__ void form_from_basis(const DevPlan& P, int b, double*
 
 template <bool FLUSH>
 __device__ __forceinline__ void form_dispatch(const DevPlan& P, int b, int nb, double* u, int part, int nparts) {
-  switch (nb) {
+  if constexpr (FLUSH) {
+    form_from_basis<kBasis, true>(P, b, u, part, nparts);   // a flush ends a full cycle
+  } else {
+    switch (nb) {
 #define ABAC_FORM_CASE(K) \
-    case K: form_from_basis<K, FLUSH>(P, b, u, part, nparts); break;
-    ABAC_FORM_CASE(1) ABAC_FORM_CASE(2) ABAC_FORM_CASE(3) ABAC_FORM_CASE(4) ABAC_FORM_CASE(5) ABAC_FORM_CASE(6)
-    ABAC_FORM_CASE(7) ABAC_FORM_CASE(8) ABAC_FORM_CASE(9) ABAC_FORM_CASE(10) ABAC_FORM_CASE(11) ABAC_FORM_CASE(12)
+    case K: form_from_basis<K, false>(P, b, u, part, nparts); break;
+      ABAC_FORM_CASE(1) ABAC_FORM_CASE(2) ABAC_FORM_CASE(3) ABAC_FORM_CASE(4) ABAC_FORM_CASE(5) ABAC_FORM_CASE(6)
+      ABAC_FORM_CASE(7) ABAC_FORM_CASE(8) ABAC_FORM_CASE(9) ABAC_FORM_CASE(10) ABAC_FORM_CASE(11) ABAC_FORM_CASE(12)
 #undef ABAC_FORM_CASE
-    default: break;
+      default: break;
+    }
   }
 }
 static_assert(kBasis == 12, "form_dispatch lists one case per basis size");
 
-// Lanczos coefficient gamma_{j+1} and the Givens QR update of iteration j.  In the
-// basis phase the w and x recurrences run on coefficient vectors over the basis
-// slots (kc: x, w_j, w_{j-1}), the same arithmetic the classic phase does on vectors.
-__device__ void step_gamma_iter(MinresState* st, double* kc, double g2) {
-  if (!(g2 >= 0.0) || !(g2 < 1e300)) {
-    st->state = ST_DONE;
-    st->status = -5;  // ABAC_EBREAKDOWN
-    st->iter += 1;
-    return;
+// The coefficients after a form step wrote the iterate to u: x adds to u from zero again,
+// and after a flush the next cycle's w recurrences start from the two w vectors.
+__device__ __forceinline__ void form_done(MinresState* st, MinresExt* x) {
+  double* xm = x->kc;
+  double* m1 = x->kc + kCoefs;
+  double* m2 = x->kc + 2 * kCoefs;
+  for (int l = 0; l < kCoefs; ++l) xm[l] = 0.0;
+  if (st->flush_now) {
+    for (int l = 0; l < kCoefs; ++l) m1[l] = m2[l] = 0.0;
+    m1[kBasis] = 1.0;
+    m2[kBasis + 1] = 1.0;
+    st->cbase += st->nbasis;
+    st->nbasis = 0;
   }
+  st->u_valid = 1;
+  st->basis_dirty = 0;
+  st->form_now = 0;
+  st->flush_now = 0;
+}
+
+// Bounds on ||r_j|| after the Givens step of iteration j (st->iter), from the inner
+// products of the first transform pass (see MinresExt); returns the estimate of
+// ||r_j||^2.  Sums of squares carry a relative rounding slack of 1e-13 of their terms.
+__device__ __forceinline__ double residual_bounds(MinresState* st, MinresExt* x, const Dots3& d, bool identity,
+                                                  double* lo, double* hi) {
+  const double r1 = st->r1, r2 = st->r2;
+  double est2, tail = 0.0, slack = 0.0;
+  if (identity) {
+    est2 = st->eta * st->eta;   // P = I: ||r_j|| = |eta_j|
+  } else if (st->track) {
+    est2 = r1 * r1 * d.c + 2.0 * r1 * r2 * d.b + r2 * r2 * d.a;
+  } else {
+    const double ra = r1 * x->rb, rb = r1 * x->rc, rc = r2;
+    const double ta = ra * ra * x->n0, tb = rb * rb * x->n1, tc = rc * rc * d.a;
+    est2 = ta + tb + tc + 2.0 * (ra * rb * x->d01 + rb * rc * d.b + ra * rc * d.c);
+    slack = 1e-13 * (ta + tb + tc);
+    if (st->iter >= 3) tail = r1 * x->r1p[0] * x->r1p[1] * x->hi[2];
+    x->rb = rb;
+    x->rc = rc;
+    x->n0 = x->n1;
+    x->n1 = d.a;
+    x->d01 = d.b;
+  }
+  x->r1p[1] = x->r1p[0];
+  x->r1p[0] = r1;
+  *lo = sqrt(fmax(est2 - slack, 0.0)) - tail;
+  *hi = sqrt(fmax(est2 + slack, 0.0)) + tail;
+  if (!(est2 == est2)) *lo = *hi = est2;   // NaN: no bound
+  x->hi[2] = x->hi[1];
+  x->hi[1] = x->hi[0];
+  x->hi[0] = *hi;
+  return est2;
+}
+
+// Lanczos coefficient gamma_{j+1}, the Givens QR update of iteration j, and the stopping
+// test on the bounds of ||r_j||: an explicit check where they do not exclude
+// convergence.  The w and x recurrences run on coefficient vectors over the basis
+// (kc: x, w_j, w_{j-1}).
+__device__ void step_gamma_iter(MinresState* st, MinresExt* x, double g2, const Dots3& dots, bool identity) {
   const double gn = sqrt(g2);
   const double gam = st->gamma, del = st->delta;
   const double eps = st->s2 * gam;
@@ -138,17 +170,17 @@ __device__ void step_gamma_iter(MinresState* st, double* kc, double g2) {
   const double dp = st->c1 * dbar + st->s1 * del;
   const double t2 = -st->s1 * dbar + st->c1 * del;
   const double rho = hypot(t2, gn);
-  if (!(rho > 0.0) || !(rho < 1e300)) {
+  if (!(g2 >= 0.0) || !(g2 < 1e300) || !(rho > 0.0) || !(rho < 1e300)) {
     st->state = ST_DONE;
-    st->status = -5;
+    st->status = -5;  // ABAC_EBREAKDOWN
     st->iter += 1;
+    st->need_check = 0;
+    st->form_now = st->basis_dirty;   // u gets the last iterate
+    st->flush_now = 0;
     return;
   }
   const double c = t2 / rho, s = gn / rho;
-  st->wa = st->sig / rho;
-  st->wb = dp / rho;
-  st->wc = eps / rho;
-  st->xc = c * st->eta;
+  const double wa = st->sig / rho, wb = dp / rho, wc = eps / rho, xc = c * st->eta;
   st->r1 = s * s;
   st->r2 = gn > 0.0 ? -s * c * st->eta / gn : 0.0;
   st->eta = -s * st->eta;
@@ -160,19 +192,29 @@ __device__ void step_gamma_iter(MinresState* st, double* kc, double g2) {
   st->iter += 1;
   if (gn == 0.0) st->lucky = 1;
   const int j = st->iter;
-  if (j <= kBasis) {
-    double* xm = kc;
-    double* m1 = kc + kBasis;
-    double* m2 = kc + 2 * kBasis;
-    for (int l = 0; l < j; ++l) {
-      const double w = (l == j - 1 ? st->wa : 0.0) - st->wb * m1[l] - st->wc * m2[l];
+  {
+    double* xm = x->kc;
+    double* m1 = x->kc + kCoefs;
+    double* m2 = x->kc + 2 * kCoefs;
+    const int nb = st->nbasis;
+    for (int l = 0; l < kCoefs; ++l) {
+      const double w = (l == nb ? wa : 0.0) - wb * m1[l] - wc * m2[l];
       m2[l] = m1[l];
       m1[l] = w;
-      xm[l] += st->xc * w;
+      xm[l] += xc * w;
     }
-    st->nbasis = j;
+    st->nbasis = nb + 1;
     st->basis_dirty = 1;
   }
+  double lo, hi;
+  st->rnorm2 = residual_bounds(st, x, dots, identity, &lo, &hi);
+  const double thr = sqrt(st->tol2 * st->bnorm2);
+  const int need = !(lo > thr) || st->explicit_mode || j >= st->maxit || st->lucky;
+  st->need_check = need;
+  // bounds too wide to decide (slow convergence): keep the residual vector from here on
+  st->want_r = need && !identity && !st->track && !st->explicit_mode && hi > thr && !(hi < 1.25 * lo);
+  st->flush_now = st->nbasis == kBasis;
+  st->form_now = need || st->flush_now;
 }
 
 // Copy the state of right-hand side b into the next slot of the host-mapped ring
@@ -191,14 +233,9 @@ __device__ __forceinline__ void post_snapshot(const DevPlan& P, int b) {
 __device__ __forceinline__ bool fin_begin(const DevPlan& P, int b, int kind) {
   MinresState* st = P.st + b;
   const bool posts = kind == FIN_GAMMA_INIT || kind == FIN_RES;   // end of set-up / of an iteration
-  if ((kind == FIN_RES || kind == FIN_REPORT) && threadIdx.x == 0 && st->form_now) {
-    st->basis_dirty = 0;   // the form step wrote the iterate into u
-    st->form_now = 0;
-    st->flush_now = 0;
-  }
-  if (kind == FIN_FINAL || (kind == FIN_RNORM && st->state != ST_RUNNING)) {
-    // a stopped solve (breakdown in this iteration, or the end of the solve) with a
-    // stale u forms it from the basis
+  if ((kind == FIN_RES || kind == FIN_REPORT) && threadIdx.x == 0 && st->form_now) form_done(st, minres_ext(P, b));
+  if (kind == FIN_FINAL) {
+    // the end of a solve with a stale u forms it from the basis
     if (threadIdx.x == 0) {
       st->form_now = st->basis_dirty;
       st->flush_now = 0;
@@ -219,14 +256,38 @@ __device__ __forceinline__ int fin_part_kind(int kind) {
     case FIN_DELTA: return PART_DELTA;
     case FIN_GAMMA_INIT:
     case FIN_GAMMA_ITER: return PART_GAMMA;
-    case FIN_RNORM: return PART_RNORM;
     default: return PART_RES;
   }
 }
 
-// Second half, thread 0 only: fold the sum `tot` into the state of right-hand side b
-// (Givens QR, stopping test, ...) and post the snapshot at the end of an iteration.
-__device__ void fin_scalar(const DevPlan& P, int b, int kind, double tot, double tol, int maxit) {
+// Sums of the n partials of the first transform pass's inner products; valid in thread 0.
+__device__ __forceinline__ Dots3 sum_dots(const DevPlan& P, int b, int n) {
+  __shared__ double red[16][3];
+  const double *pa = dot_slot(P, 0, b), *pb = dot_slot(P, 1, b), *pc = dot_slot(P, 2, b);
+  Dots3 d{0.0, 0.0, 0.0};
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    d.a += pa[i];
+    d.b += pb[i];
+    d.c += pc[i];
+  }
+  dots_reduce(d, red);
+  __syncthreads();
+  Dots3 t{0.0, 0.0, 0.0};
+  if (threadIdx.x == 0) {
+    for (int w = 0; w < (int)(blockDim.x + 63) >> 6; ++w) {
+      t.a += red[w][0];
+      t.b += red[w][1];
+      t.c += red[w][2];
+    }
+  }
+  __syncthreads();
+  return t;
+}
+
+// Second half, thread 0 only: fold the sum `tot` (and for FIN_GAMMA_ITER the inner
+// products of the first transform pass) into the state of right-hand side b (Givens QR,
+// stopping test, ...) and post the snapshot at the end of an iteration.
+__device__ void fin_scalar(const DevPlan& P, int b, int kind, double tot, const Dots3& dots, double tol, int maxit) {
   MinresState* st = P.st + b;
   const bool posts = kind == FIN_GAMMA_INIT || kind == FIN_RES;
   switch (kind) {
@@ -239,7 +300,11 @@ __device__ void fin_scalar(const DevPlan& P, int b, int kind, double tot, double
       st->need_check = 0;
       st->lucky = 0;
       st->snap = 0;
+      st->cbase = 0;
       st->nbasis = 0;
+      st->u_valid = 0;
+      st->track = 0;
+      st->want_r = 0;
       st->basis_dirty = 0;   // u = 0 = x_0
       st->form_now = 0;
       st->flush_now = 0;
@@ -271,22 +336,21 @@ __device__ void fin_scalar(const DevPlan& P, int b, int kind, double tot, double
       st->c1 = 1.0; st->c2 = 1.0;
       st->s1 = 0.0; st->s2 = 0.0;
       st->iter = 0;
-      for (int l = 0; l < 3 * kBasis; ++l) P.kcoef[(size_t)b * 3 * kBasis + l] = 0.0;
+      {
+        MinresExt* x = minres_ext(P, b);
+        for (int l = 0; l < 3 * kCoefs; ++l) x->kc[l] = 0.0;
+        x->rb = 0.0;   // r_0 = V_1
+        x->rc = 1.0;
+        x->n0 = 0.0;
+        x->n1 = st->bnorm2;
+        x->d01 = 0.0;
+        x->r1p[0] = x->r1p[1] = 0.0;
+        x->hi[0] = x->hi[1] = x->hi[2] = sqrt(st->bnorm2);
+      }
       break;
     case FIN_GAMMA_ITER:
-      step_gamma_iter(st, P.kcoef + (size_t)b * 3 * kBasis, tot);
+      step_gamma_iter(st, minres_ext(P, b), tot, dots, P.prec == 2);
       break;
-    case FIN_RNORM: {
-      // stopping test on the recurrence residual; the explicit residual confirms it
-      const int j = st->iter;
-      const int need = (tot <= st->tol2 * st->bnorm2) || st->explicit_mode || j >= st->maxit || st->lucky ||
-                       !(tot == tot);
-      st->rnorm2 = tot;
-      st->need_check = need;
-      st->form_now = j <= kBasis && (need || j == kBasis);
-      st->flush_now = j == kBasis;
-      break;
-    }
     case FIN_RES:
       st->res2 = tot;
       if (tot <= st->tol2 * st->bnorm2) {
@@ -298,10 +362,19 @@ __device__ void fin_scalar(const DevPlan& P, int b, int kind, double tot, double
       } else if (st->iter >= st->maxit) {
         st->state = ST_DONE;
         st->status = -4;  // ABAC_ENOTCONV
+      } else if (st->want_r) {
+        // undecided and not converged: P.R now holds r_j, so the next first pass must not
+        // add the recurrence's last step again
+        st->track = 1;
+        st->r1 = 1.0;
+        st->r2 = 0.0;
       } else {
-        st->explicit_mode = 1;
+        MinresExt* x = minres_ext(P, b);
+        if (!(x->hi[0] * x->hi[0] > st->tol2 * st->bnorm2)) st->explicit_mode = 1;   // the recurrence was optimistic
+        x->hi[0] = sqrt(tot);
       }
       st->need_check = 0;
+      st->want_r = 0;
       break;
     case FIN_REPORT:
       st->res2 = tot;

@@ -68,8 +68,8 @@ __device__ __forceinline__ double apply_L(const LCoef& q, const double* __restri
 }
 
 // what a matvec block writes: Y T x (time-reversed, the symmetrised operator), T x,
-// the residual vector f - T x, or only the squared residual norm
-enum StencilOut : int { OUT_REV = 0, OUT_NAT = 1, OUT_RESVEC = 2, OUT_RESNORM = 3 };
+// the residual vector f - T x or Y (f - T x), or only the squared residual norm
+enum StencilOut : int { OUT_REV = 0, OUT_NAT = 1, OUT_RESVEC = 2, OUT_RESNORM = 3, OUT_RESREV = 4 };
 
 // One column of a logical block of the matvec, one column per thread (the
 // variable-coefficient tile, and grids one column wide): a band of RB grid rows, forward
@@ -172,13 +172,16 @@ __device__ __forceinline__ double stencil_tile(const DevPlan& P, const double* _
       const double out_b = Lb0[r] + Lb2[r] - 2.0 * zb1[r];    // (T x)_kb, kb = n-1-k
       const int pos = Bd.rowoff[r + 1];
       if (active && iy0 + r < ny1) {
-        if (OUT == OUT_RESNORM || OUT == OUT_RESVEC) {
+        if (OUT == OUT_RESNORM || OUT == OUT_RESVEC || OUT == OUT_RESREV) {
           const double rf = ff[pos] - out_f;
           const double rb = fb[pos] - out_b;
           acc += rf * rf + rb * rb;
           if (OUT == OUT_RESVEC) {
             yf[pos] = rf;
             yb[pos] = rb;
+          } else if (OUT == OUT_RESREV) {
+            yb[pos] = rf;
+            yf[pos] = rb;
           }
         } else if (OUT == OUT_NAT) {
           yf[pos] = out_f;
@@ -325,7 +328,7 @@ __device__ __forceinline__ double stencil_tile2(const DevPlan& P, const double* 
       }
       const int row = rowoff[r + 1];
       if (act0 && iy0 + r < ny1) {
-        if (OUT == OUT_RESNORM || OUT == OUT_RESVEC) {
+        if (OUT == OUT_RESNORM || OUT == OUT_RESVEC || OUT == OUT_RESREV) {
           const dpair pf = *reinterpret_cast<const dpair*>(ff + row + sc);
           const dpair pb = *reinterpret_cast<const dpair*>(fb + row + sc);
           const double rf0 = (h_low ? pf.x : pf.y) - out_f[0];
@@ -334,13 +337,15 @@ __device__ __forceinline__ double stencil_tile2(const DevPlan& P, const double* 
           const double rf1 = pf.y - out_f[1];
           const double rb1 = pb.y - out_b[1];
           if (act1) acc += rf1 * rf1 + rb1 * rb1;
-          if (OUT == OUT_RESVEC) {
+          if (OUT == OUT_RESVEC || OUT == OUT_RESREV) {
+            double* wf = OUT == OUT_RESVEC ? yf : yb;
+            double* wb = OUT == OUT_RESVEC ? yb : yf;
             if (act1) {
-              *reinterpret_cast<dpair*>(yf + row + c) = dpair{rf0, rf1};
-              *reinterpret_cast<dpair*>(yb + row + c) = dpair{rb0, rb1};
+              *reinterpret_cast<dpair*>(wf + row + c) = dpair{rf0, rf1};
+              *reinterpret_cast<dpair*>(wb + row + c) = dpair{rb0, rb1};
             } else {
-              yf[row + c] = rf0;
-              yb[row + c] = rb0;
+              wf[row + c] = rf0;
+              wb[row + c] = rb0;
             }
           }
         } else {

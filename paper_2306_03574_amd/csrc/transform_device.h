@@ -1,7 +1,6 @@
 // Device code of the transform passes of z = P_alpha^{-1} r (Section 2.3): per-tile
 // bodies of the first x-DST pass (with the fused Lanczos step), the y-DST pass, the time
-// pass K Y K Y (or the single K of C_alpha^{-1}) and the last x-DST pass (with the
-// partial sums of <q, p>).  Each body is one workgroup's work on one tile; the kernels
+// pass K Y K Y (or the single K of C_alpha^{-1}) and the last x-DST pass.  Each body is one workgroup's work on one tile; the kernels
 // run one tile per workgroup, the fused small-problem iteration runs every tile of a
 // right-hand side in one workgroup.
 #pragma once
@@ -123,9 +122,73 @@ __device__ __forceinline__ void stage_in(TD* dst, const TS* __restrict__ src, in
   }
 }
 
+// The Lanczos step q = sig_j A Z_j - delta v_j - gamma_j v_{j-1} of right-hand side b, which
+// the first pass forms as it reads its input, with the inner products of q that the
+// stopping test needs (Dots3).  Where the residual vector is kept (st->track) the step
+// also updates it, r_{j-1} = r1 r_{j-2} + r2 V_j.
+struct LanczosStep {
+  const double *az, *vj, *vjm1;
+  double *q, *r;   // r: NULL unless the residual is tracked
+  double cA, cB, cC, r1, r2;
+  __device__ __forceinline__ LanczosStep(const DevPlan& P, int b) {
+    const size_t off = (size_t)b * P.N;
+    const MinresState* st = P.st + b;
+    const int j = st->iter + 1;
+    q = P.V[(j + 1) % 3] + off;
+    az = q;
+    vj = P.V[j % 3] + off;
+    vjm1 = P.V[j == 1 ? j % 3 : (j + 2) % 3] + off;   // v_0 has weight 0 at j = 1
+    r = st->track ? P.R + off : nullptr;
+    cA = st->sig;
+    cB = st->delta * st->sig;
+    cC = st->gamma * st->sig_prev;
+    r1 = st->r1;
+    r2 = st->r2;
+  }
+  // elements e[u] (clamped loads) of a batch; `live` says which are the caller's
+  template <int BATCH>
+  __device__ __forceinline__ void run(const size_t* e, const bool* live, double* out, Dots3& d) const {
+    double a[BATCH], bv[BATCH], cv[BATCH];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      a[u] = az[e[u]];
+      bv[u] = vj[e[u]];
+      cv[u] = vjm1[e[u]];
+    }
+    if (!r) {
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        out[u] = cA * a[u] - cB * bv[u] - cC * cv[u];
+        if (live[u]) {
+          q[e[u]] = out[u];
+          d.a += out[u] * out[u];
+          d.b += out[u] * bv[u];
+          d.c += out[u] * cv[u];
+        }
+      }
+    } else {
+      double rv[BATCH];
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) rv[u] = r[e[u]];
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        out[u] = cA * a[u] - cB * bv[u] - cC * cv[u];
+        const double rn = r1 * rv[u] + r2 * bv[u];
+        if (live[u]) {
+          q[e[u]] = out[u];
+          r[e[u]] = rn;
+          d.a += out[u] * out[u];
+          d.b += out[u] * rn;
+          d.c += rn * rn;
+        }
+      }
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
 // first pass: DST-I along x of every row (FP64 in, transform precision out),
-// optionally fused with the Lanczos step q = sig_j A Z_j - delta v_j - gamma_j v_{j-1}
+// optionally fused with the Lanczos step
 // ---------------------------------------------------------------------------
 // One tile (2 S rows) of right-hand side b; the caller skips stopped right-hand sides.
 // tw: the length-L twiddle table (the plan's, or a copy the caller staged in LDS).
@@ -137,23 +200,7 @@ __device__ __forceinline__ void dstx_fwd_tile(const DevPlan& P, int mode, const 
   extern __shared__ __align__(16) unsigned char smem[];
   C* lds = reinterpret_cast<C*>(smem);
   T* stage = reinterpret_cast<T*>(smem);
-  const size_t off = (size_t)b * P.N;
-  const double* src = in ? in + off : nullptr;
-  double* qout = nullptr;
-  const double* vj = nullptr;
-  const double* vjm1 = nullptr;
-  double cA = 1.0, cB = 0.0, cC = 0.0;
-  if (mode == FWD_LANCZOS) {
-    const MinresState* st = P.st + b;
-    const int j = st->iter + 1;
-    qout = P.V[(j + 1) % 3] + off;
-    src = qout;
-    vj = P.V[j % 3] + off;
-    vjm1 = P.V[j == 1 ? j % 3 : (j + 2) % 3] + off;   // v_0 has weight 0 at j = 1
-    cA = st->sig;
-    cB = st->delta * st->sig;
-    cC = st->gamma * st->sig_prev;
-  }
+  __shared__ double dred[16][3];
   const int nx = P.nx;
   const int rows = P.nt * P.ny1;
   const int row0 = tile * 2 * S;
@@ -164,30 +211,30 @@ __device__ __forceinline__ void dstx_fwd_tile(const DevPlan& P, int mode, const 
   // loads (clamped to the tile, so unconditional) are all issued before they are used
   constexpr int BATCH = 4;
   if (mode == FWD_LANCZOS) {
+    const LanczosStep step(P, b);
+    Dots3 d{0.0, 0.0, 0.0};
 #pragma unroll
     for (int u0 = 0; u0 < R; u0 += BATCH) {
-      double a[BATCH], bv[BATCH], cv[BATCH];
+      size_t e[BATCH];
+      bool live[BATCH];
+      double q[BATCH];
 #pragma unroll
       for (int u = 0; u < BATCH; ++u) {
-        const size_t e = base + min((int)threadIdx.x + (u0 + u) * WG, cnt - 1);
-        a[u] = src[e];
-        bv[u] = vj[e];
-        cv[u] = vjm1[e];
+        const int i = threadIdx.x + (u0 + u) * WG;
+        live[u] = i < cnt;
+        e[u] = base + min(i, cnt - 1);
       }
+      step.run<BATCH>(e, live, q, d);
 #pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        const int e = threadIdx.x + (u0 + u) * WG;
-        if (e < cnt) {
-          const double q = cA * a[u] - cB * bv[u] - cC * cv[u];
-          qout[base + e] = q;
-          stage[e] = (T)q;
-        }
-      }
+      for (int u = 0; u < BATCH; ++u)
+        if (live[u]) stage[threadIdx.x + (u0 + u) * WG] = (T)q[u];
     }
+    dots_reduce(d, dred);
   } else {
-    stage_in<R, WG>(stage, src + base, cnt);
+    stage_in<R, WG>(stage, in + (size_t)b * P.N + base, cnt);
   }
   __syncthreads();
+  if (mode == FWD_LANCZOS) dots_store(P, b, tile, dred);
   const int s = threadIdx.x % S, j = threadIdx.x / S;
   const int ra = 2 * s, rb = 2 * s + 1;
   const bool va = ra < nrows, vb = rb < nrows;
@@ -501,13 +548,12 @@ __device__ __forceinline__ void time_tile(const DevPlan& P, int inv1, int b, int
 }
 
 // ---------------------------------------------------------------------------
-// last pass: inverse DST-I along x (transform precision in, FP64 out), optionally
-// fused with the partial sums of <q, p>.
+// last pass: inverse DST-I along x (transform precision in, FP64 out).
 // ---------------------------------------------------------------------------
-// One tile (2 S rows) of right-hand side b; returns this thread's part of <q, p> (0 in
-// INV_PLAIN).  The caller skips stopped right-hand sides.  tw as for dstx_fwd_tile.
+// One tile (2 S rows) of right-hand side b.  The caller skips stopped right-hand sides.
+// tw as for dstx_fwd_tile.
 template <typename T, int L, int WG>
-__device__ __forceinline__ double dstx_inv_tile(const DevPlan& P, int mode, double* __restrict__ outp, int b,
+__device__ __forceinline__ void dstx_inv_tile(const DevPlan& P, int mode, double* __restrict__ outp, int b,
                                                 int tile, const cplx<T>* __restrict__ tw) {
   using C = cplx<T>;
   constexpr int R = FftShape<T, L>::R, TPS = L / R, S = seqs_of<T, L, WG>(), Mx = L / 2;
@@ -517,17 +563,9 @@ __device__ __forceinline__ double dstx_inv_tile(const DevPlan& P, int mode, doub
   double* ostage = reinterpret_cast<double*>(smem);
   const size_t off = (size_t)b * P.N;
   double* out = outp ? outp + off : nullptr;
-  const double* q = nullptr;
-  const MinresState* st = P.st + b;
   if (mode != INV_PLAIN) {
-    if (mode == INV_GAMMA_INIT || mode == INV_Z_INIT) {
-      out = P.Z[zslot(1)] + off;
-      if (mode == INV_GAMMA_INIT) q = P.V[1] + off;
-    } else {
-      const int jj = st->iter + 1;
-      out = P.Z[zslot(jj + 1)] + off;
-      if (mode == INV_GAMMA_ITER) q = P.V[(jj + 1) % 3] + off;
-    }
+    // z_1, or z_{j+1} after the Givens step of iteration j
+    out = P.Z[zslot(mode == INV_Z_INIT ? 1 : P.st[b].iter + 1)] + off;
   }
   const int nx = P.nx;
   const int rows = P.nt * P.ny1;
@@ -557,8 +595,7 @@ __device__ __forceinline__ double dstx_inv_tile(const DevPlan& P, int mode, doub
   const double scl = 1.0 / sqrt((double)L);
   // stage the FP64 rows packed ([2S][nx]: the block's 2S output rows are one contiguous
   // run of memory, and the odd row length in 8-byte words spreads the sequences of a
-  // wave over the banks) and write them out; with q, accumulate <q, p> in a fixed order
-  // for a fixed tile
+  // wave over the banks) and write them out
   __syncthreads();
   const int ldo = nx;
 #pragma unroll
@@ -572,43 +609,11 @@ __device__ __forceinline__ double dstx_inv_tile(const DevPlan& P, int mode, doub
   __syncthreads();
   double* o = out + (size_t)row0 * nx;
   const int total = nrows * nx;   // < WG * R
-  double acc = 0.0;
-  if (!q) {
-    // one contiguous run: 16-byte moves of pairs, and the odd last value
-    const int npair = total / 2;
-    for (int e = threadIdx.x; e < npair; e += WG)
-      *reinterpret_cast<dpair*>(o + 2 * e) = *reinterpret_cast<const dpair*>(ostage + 2 * e);
-    if ((total & 1) && threadIdx.x == 0) o[total - 1] = ostage[total - 1];
-  } else {
-    const double* qq = q ? q + (size_t)row0 * nx : nullptr;
-    int r = (int)threadIdx.x / nx, c = (int)threadIdx.x - r * nx;
-    const int dr = WG / nx, dc = WG - dr * nx;
-    constexpr int BATCH = 8;
-#pragma unroll
-    for (int u0 = 0; u0 < R; u0 += BATCH) {
-      double qv[BATCH];
-      if (qq) {
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) qv[u] = qq[min((int)threadIdx.x + (u0 + u) * WG, total - 1)];
-      }
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        const int e = threadIdx.x + (u0 + u) * WG;
-        if (e < total) {
-          const double val = ostage[r * ldo + c];
-          o[e] = val;
-          if (qq) acc += val * qv[u];
-        }
-        r += dr;
-        c += dc;
-        if (c >= nx) {
-          c -= nx;
-          ++r;
-        }
-      }
-    }
-  }
-  return acc;
+  // one contiguous run: 16-byte moves of pairs, and the odd last value
+  const int npair = total / 2;
+  for (int e = threadIdx.x; e < npair; e += WG)
+    *reinterpret_cast<dpair*>(o + 2 * e) = *reinterpret_cast<const dpair*>(ostage + 2 * e);
+  if ((total & 1) && threadIdx.x == 0) o[total - 1] = ostage[total - 1];
 }
 
 // ---------------------------------------------------------------------------
@@ -694,54 +699,50 @@ __device__ __forceinline__ void dst2_fwd_tile(const DevPlan& P, int mode, const 
   extern __shared__ __align__(16) unsigned char smem[];
   T* slab = reinterpret_cast<T*>(smem);
   C* exch = reinterpret_cast<C*>(smem + slab_bytes<T, L>());
-  const size_t off = (size_t)b * P.N;
-  const double* src = in ? in + off : nullptr;
-  double* qout = nullptr;
-  const double* vj = nullptr;
-  const double* vjm1 = nullptr;
-  double cA = 1.0, cB = 0.0, cC = 0.0;
-  if (mode == FWD_LANCZOS) {
-    const MinresState* st = P.st + b;
-    const int j = st->iter + 1;
-    qout = P.V[(j + 1) % 3] + off;
-    src = qout;
-    vj = P.V[j % 3] + off;
-    vjm1 = P.V[j == 1 ? j % 3 : (j + 2) % 3] + off;   // v_0 has weight 0 at j = 1
-    cA = st->sig;
-    cB = st->delta * st->sig;
-    cC = st->gamma * st->sig_prev;
-  }
+  __shared__ double dred[16][3];
   const int nx = M - 1, cnt = nx * nx;
   const size_t base = (size_t)lvl * P.m;
   // stage the level; a thread's BATCH loads (clamped, so unconditional) are issued
   // before any is used
   constexpr int BATCH = 8;
-  for (int e0 = 0; e0 < cnt; e0 += BATCH * WG) {
-    double a[BATCH], bv[BATCH], cv[BATCH];
+  auto put = [&](int e, double q) {
+    const int r = e / nx;
+    slab[r * (M + 1) + (e - r * nx)] = (T)q;
+  };
+  if (mode == FWD_LANCZOS) {
+    const LanczosStep step(P, b);
+    Dots3 d{0.0, 0.0, 0.0};
+    for (int e0 = 0; e0 < cnt; e0 += BATCH * WG) {
+      size_t e[BATCH];
+      bool live[BATCH];
+      double q[BATCH];
 #pragma unroll
-    for (int u = 0; u < BATCH; ++u) {
-      const size_t e = base + min(e0 + (int)threadIdx.x + u * WG, cnt - 1);
-      a[u] = src[e];
-      if (mode == FWD_LANCZOS) {
-        bv[u] = vj[e];
-        cv[u] = vjm1[e];
+      for (int u = 0; u < BATCH; ++u) {
+        const int i = e0 + (int)threadIdx.x + u * WG;
+        live[u] = i < cnt;
+        e[u] = base + min(i, cnt - 1);
       }
-    }
+      step.run<BATCH>(e, live, q, d);
 #pragma unroll
-    for (int u = 0; u < BATCH; ++u) {
-      const int e = e0 + (int)threadIdx.x + u * WG;
-      if (e < cnt) {
-        double q = a[u];
-        if (mode == FWD_LANCZOS) {
-          q = cA * a[u] - cB * bv[u] - cC * cv[u];
-          qout[base + e] = q;
-        }
-        const int r = e / nx;
-        slab[r * (M + 1) + (e - r * nx)] = (T)q;
+      for (int u = 0; u < BATCH; ++u)
+        if (live[u]) put(e0 + (int)threadIdx.x + u * WG, q[u]);
+    }
+    dots_reduce(d, dred);
+  } else {
+    const double* src = in + (size_t)b * P.N + base;
+    for (int e0 = 0; e0 < cnt; e0 += BATCH * WG) {
+      double a[BATCH];
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) a[u] = src[min(e0 + (int)threadIdx.x + u * WG, cnt - 1)];
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        const int e = e0 + (int)threadIdx.x + u * WG;
+        if (e < cnt) put(e, a[u]);
       }
     }
   }
   __syncthreads();
+  if (mode == FWD_LANCZOS) dots_store(P, b, lvl, dred);
   slab_dst<T, L, WG, true>(slab, nx, exch, reinterpret_cast<const C*>(P.twx));
   slab_dst<T, L, WG, false>(slab, M, exch, reinterpret_cast<const C*>(P.twy));
   T* out = reinterpret_cast<T*>(P.scratch) + (size_t)b * P.NS + (size_t)lvl * P.ms;
@@ -751,11 +752,10 @@ __device__ __forceinline__ void dst2_fwd_tile(const DevPlan& P, int mode, const 
   }
 }
 
-// Last pass, fused: DST-I along y and x of level lvl of the scratch, FP64 rows out;
-// returns this thread's part of <q, p> in the GAMMA modes (0 otherwise).  The caller
-// skips stopped right-hand sides.
+// Last pass, fused: DST-I along y and x of level lvl of the scratch, FP64 rows out.  The
+// caller skips stopped right-hand sides.
 template <typename T, int L, int WG>
-__device__ __forceinline__ double dst2_inv_tile(const DevPlan& P, int mode, double* __restrict__ outp, int b, int lvl) {
+__device__ __forceinline__ void dst2_inv_tile(const DevPlan& P, int mode, double* __restrict__ outp, int b, int lvl) {
   using C = cplx<T>;
   constexpr int M = L / 2;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -763,17 +763,9 @@ __device__ __forceinline__ double dst2_inv_tile(const DevPlan& P, int mode, doub
   C* exch = reinterpret_cast<C*>(smem + slab_bytes<T, L>());
   const size_t off = (size_t)b * P.N;
   double* out = outp ? outp + off : nullptr;
-  const double* q = nullptr;
-  const MinresState* st = P.st + b;
   if (mode != INV_PLAIN) {
-    if (mode == INV_GAMMA_INIT || mode == INV_Z_INIT) {
-      out = P.Z[zslot(1)] + off;
-      if (mode == INV_GAMMA_INIT) q = P.V[1] + off;
-    } else {
-      const int jj = st->iter + 1;
-      out = P.Z[zslot(jj + 1)] + off;
-      if (mode == INV_GAMMA_ITER) q = P.V[(jj + 1) % 3] + off;
-    }
+    // z_1, or z_{j+1} after the Givens step of iteration j
+    out = P.Z[zslot(mode == INV_Z_INIT ? 1 : P.st[b].iter + 1)] + off;
   }
   const int nx = M - 1, cnt = nx * M;
   const T* scr = reinterpret_cast<const T*>(P.scratch) + (size_t)b * P.NS + (size_t)lvl * P.ms;
@@ -796,29 +788,18 @@ __device__ __forceinline__ double dst2_inv_tile(const DevPlan& P, int mode, doub
   slab_dst<T, L, WG, true>(slab, nx, exch, reinterpret_cast<const C*>(P.twx));
   const size_t base = (size_t)lvl * P.m;
   double* o = out + base;
-  const double* qq = q ? q + base : nullptr;
   const int total = nx * nx;
-  double acc = 0.0;
   for (int e0 = 0; e0 < total; e0 += BATCH * WG) {
-    double qv[BATCH];
-    if (qq) {
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u) qv[u] = qq[min(e0 + (int)threadIdx.x + u * WG, total - 1)];
-    }
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) {
       const int e = e0 + (int)threadIdx.x + u * WG;
       if (e < total) {
         const int r = e / nx;
-        const double val = (double)slab[r * (M + 1) + (e - r * nx)];
-        o[e] = val;
-        if (qq) acc += val * qv[u];
+        o[e] = (double)slab[r * (M + 1) + (e - r * nx)];
       }
     }
   }
-  return acc;
 }
-
 
 }  // namespace
 }  // namespace abac
