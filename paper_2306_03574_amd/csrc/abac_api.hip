@@ -4,10 +4,12 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
+#include <chrono>
 #include <map>
 #include <mutex>
+#include <thread>
 #include <tuple>
-#include <climits>
 #include <cstdlib>
 #include <cmath>
 #include <cstdio>
@@ -197,6 +199,12 @@ abac_status flush_prof(abac_plan* p) {
     if (s_ != ABAC_OK) return s_;                                 \
   } while (0)
 
+FinArgs post_now() {
+  FinArgs a;
+  a.post = 1;
+  return a;
+}
+
 // The first half of z = P^{-1} r on the plan stream: the forward space transforms and the
 // time pass (in MINRES mode with the partials of <q, P^{-1} q>).  fwd_mode FWD_LANCZOS
 // forms the Lanczos vector as its input.
@@ -216,10 +224,10 @@ abac_status enqueue_pinv_head(abac_plan* p, const double* r, int fwd_mode, int c
 abac_status enqueue_pinv_tail(abac_plan* p, double* z, int inv_mode, int check) {
   const DevPlan& P = p->P;
   if (P.wg_s) {
-    RUN(ABAC_K_DSTX_INV, launch_dst2_inv(P, p->prec, inv_mode, z, p->stream));
+    RUN(ABAC_K_DSTX_INV, launch_dst2_inv(P, p->prec, inv_mode, check, z, p->stream));
   } else {
     if (P.ny) RUN(ABAC_K_DSTY, launch_dsty(P, p->prec, check, p->stream));
-    RUN(ABAC_K_DSTX_INV, launch_dstx_inv(P, p->prec, inv_mode, z, p->stream));
+    RUN(ABAC_K_DSTX_INV, launch_dstx_inv(P, p->prec, inv_mode, check, z, p->stream));
   }
   return ABAC_OK;
 }
@@ -239,11 +247,11 @@ abac_status enqueue_pinv_init(abac_plan* p) {
   if (p->prec == ABAC_PREC_NONE) {
     RUN(ABAC_K_DSTX_INV, launch_identity(p->P, INV_GAMMA_INIT, nullptr, nullptr, p->stream));
   } else {
-    abac_status s = enqueue_pinv_head(p, p->P.V[1], FWD_PLAIN, 1);
-    if (s == ABAC_OK) s = enqueue_pinv_tail(p, nullptr, INV_Z_INIT, 1);
+    abac_status s = enqueue_pinv_head(p, p->P.V[1], FWD_PLAIN, CHECK_ACTIVE);
+    if (s == ABAC_OK) s = enqueue_pinv_tail(p, nullptr, INV_Z_INIT, CHECK_ACTIVE);
     if (s != ABAC_OK) return s;
   }
-  RUN(ABAC_K_FIN, launch_fin(p->P, FIN_GAMMA_INIT, 0.0, 0, p->stream));
+  RUN(ABAC_K_FIN, launch_fin(p->P, FIN_GAMMA_INIT, FinArgs{}, p->stream));
   return ABAC_OK;
 }
 
@@ -258,92 +266,99 @@ abac_status enqueue_cinv(abac_plan* p, const double* r, double* z) {
   if (P.wg_s) {
     RUN(ABAC_K_DSTX_FWD, launch_dst2_fwd(P, p->prec, FWD_PLAIN, 0, r, p->stream));
     RUN(ABAC_K_TIME, launch_time(P, p->prec, 0, p->stream, 1));
-    RUN(ABAC_K_DSTX_INV, launch_dst2_inv(P, p->prec, INV_PLAIN, z, p->stream));
+    RUN(ABAC_K_DSTX_INV, launch_dst2_inv(P, p->prec, INV_PLAIN, 0, z, p->stream));
     return ABAC_OK;
   }
   RUN(ABAC_K_DSTX_FWD, launch_dstx_fwd(P, p->prec, FWD_PLAIN, 0, r, p->stream));
   if (P.ny) RUN(ABAC_K_DSTY, launch_dsty(P, p->prec, 0, p->stream));
   RUN(ABAC_K_TIME, launch_time(P, p->prec, 0, p->stream, 1));
   if (P.ny) RUN(ABAC_K_DSTY, launch_dsty(P, p->prec, 0, p->stream));
-  RUN(ABAC_K_DSTX_INV, launch_dstx_inv(P, p->prec, INV_PLAIN, z, p->stream));
+  RUN(ABAC_K_DSTX_INV, launch_dstx_inv(P, p->prec, INV_PLAIN, 0, z, p->stream));
   return ABAC_OK;
 }
 
-abac_status enqueue_iteration(abac_plan* p) {
-  const DevPlan& P = p->P;
-  if (P.small) {
-    RUN(ABAC_K_ITER, launch_iter_small(P, p->prec, p->f, p->u, p->stream));
-    return ABAC_OK;
-  }
-  RUN(ABAC_K_STENCIL, launch_stencil(P, STENCIL_MINRES, nullptr, nullptr, nullptr, p->stream));
-  RUN(ABAC_K_FIN, launch_fin(P, FIN_DELTA, 0.0, 0, p->stream));
-  if (p->prec == ABAC_PREC_NONE) {
-    RUN(ABAC_K_DSTX_INV, launch_identity(P, INV_GAMMA_ITER, nullptr, nullptr, p->stream));
-  } else {
-    abac_status s = enqueue_pinv_head(p, nullptr, FWD_LANCZOS, 1);
-    if (s != ABAC_OK) return s;
-  }
-  // gamma_{j+1} is known after the time pass, so the stopping test comes before the
-  // inverse transforms of z_{j+1}: a solve that stops here skips them
-  RUN(ABAC_K_FIN, launch_fin(P, FIN_GAMMA_ITER, 0.0, 0, p->stream));
-  RUN(ABAC_K_FORM, launch_form(P, p->u, p->stream));
-  RUN(ABAC_K_RESIDUAL, launch_stencil(P, STENCIL_RESIDUAL, p->u, nullptr, p->f, p->stream));
-  RUN(ABAC_K_FIN, launch_fin(P, FIN_RES, 0.0, 0, p->stream));
-  return p->prec == ABAC_PREC_NONE ? ABAC_OK : enqueue_pinv_tail(p, nullptr, INV_Z_ITER, 1);
-}
-
-// The set-up and every iteration end with a kernel that copies the per-RHS state
-// into the host-mapped ring; this event marks when that copy is complete.
-abac_status record_snapshot_event(abac_plan* p) {
-  const int slot = (int)(p->ring_posted % kSnapRing);
-  HIP_TRY(hipEventRecord(p->ring_ev[slot], p->stream));
+// What the stopping test of an iteration asked for: the iterate from the basis, the
+// explicit residual, and the snapshot that reports them.
+abac_status enqueue_check(abac_plan* p) {
+  RUN(ABAC_K_FORM, launch_form(p->P, p->u, p->stream));
+  RUN(ABAC_K_RESIDUAL, launch_stencil(p->P, STENCIL_RESIDUAL, p->u, nullptr, p->f, p->stream));
+  RUN(ABAC_K_FIN, launch_fin(p->P, FIN_RES, FinArgs{}, p->stream));
   p->ring_posted++;
   return ABAC_OK;
 }
 
-abac_status launch_iteration(abac_plan* p) {
-  if (p->prof || !p->use_graph) return enqueue_iteration(p);
-  if (!p->iter_graph || p->graph_f != p->f || p->graph_u != p->u) {
-    if (p->iter_graph) {
-      HIP_TRY(hipGraphExecDestroy(p->iter_graph));
-      p->iter_graph = nullptr;
-    }
-    hipStream_t user = p->stream;
-    p->stream = p->cap_stream;
-    HIP_TRY(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeRelaxed));
-    abac_status s = enqueue_iteration(p);
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(p->cap_stream, &g);
-    p->stream = user;
-    if (s != ABAC_OK) return s;
-    if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
-    e = hipGraphInstantiate(&p->iter_graph, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (e != hipSuccess) return hip_fail(e, "hipGraphInstantiate");
-    p->graph_f = p->f;
-    p->graph_u = p->u;
+// One MINRES iteration on the plan stream; it posts one snapshot.  Ahead of time
+// (host_checks false) it carries the check step, which right-hand sides that need none
+// skip.  A host that reads every snapshot leaves the check step out and enqueues it when
+// a snapshot asks for it (three launches fewer per iteration); the stopping test then
+// posts the snapshot, while the inverse transforms still run.
+abac_status enqueue_iteration(abac_plan* p, bool host_checks) {
+  const DevPlan& P = p->P;
+  if (P.small) {
+    RUN(ABAC_K_ITER, launch_iter_small(P, p->prec, p->f, p->u, p->stream));
+    p->ring_posted++;
+    return ABAC_OK;
   }
-  HIP_TRY(hipGraphLaunch(p->iter_graph, p->stream));
-  return ABAC_OK;
+  RUN(ABAC_K_STENCIL, launch_stencil(P, STENCIL_MINRES, nullptr, nullptr, nullptr, p->stream));
+  RUN(ABAC_K_FIN, launch_fin(P, FIN_DELTA, FinArgs{}, p->stream));
+  if (p->prec == ABAC_PREC_NONE) {
+    RUN(ABAC_K_DSTX_INV, launch_identity(P, INV_GAMMA_ITER, nullptr, nullptr, p->stream));
+  } else {
+    abac_status s = enqueue_pinv_head(p, nullptr, FWD_LANCZOS, CHECK_ACTIVE);
+    if (s != ABAC_OK) return s;
+  }
+  // gamma_{j+1} is known after the time pass, so the stopping test comes before the
+  // inverse transforms of z_{j+1}: a solve that stops here skips them
+  RUN(ABAC_K_FIN, launch_fin(P, FIN_GAMMA_ITER, host_checks ? post_now() : FinArgs{}, p->stream));
+  if (host_checks) {
+    p->ring_posted++;
+  } else {
+    abac_status s = enqueue_check(p);
+    if (s != ABAC_OK) return s;
+  }
+  return p->prec == ABAC_PREC_NONE ? ABAC_OK : enqueue_pinv_tail(p, nullptr, INV_Z_ITER, CHECK_ACTIVE);
 }
 
-bool all_stopped(const MinresState* s, int B) {
-  for (int b = 0; b < B; ++b)
-    if (s[b].state == ST_RUNNING) return false;
+// Snapshot `seq` of the current solve, for every right-hand side.
+bool snapshot_ready(const abac_plan* p, long long seq) {
+  const unsigned long long name = snap_name(snap_word(p->epoch, seq, 0, 0));
+  const Snapshot* s = p->h_ring + (size_t)(seq % kSnapRing) * p->P.B;
+  for (int b = 0; b < p->P.B; ++b)
+    if (snap_name(__atomic_load_n(&s[b].word, __ATOMIC_ACQUIRE)) != name) return false;
   return true;
 }
 
-void fill_results(const MinresState* s, int B, int* iters, double* relres, int* status, abac_status* worst) {
-  *worst = ABAC_OK;
-  for (int b = 0; b < B; ++b) {
-    if (iters) iters[b] = s[b].iter;
-    if (relres) relres[b] = s[b].bnorm2 > 0 ? std::sqrt(s[b].res2 / s[b].bnorm2) : 0.0;
-    int st = s[b].state == ST_DONE ? s[b].status : ABAC_ENOTCONV;
-    if (status) status[b] = st;
-    if (st != ABAC_OK && *worst == ABAC_OK) *worst = (abac_status)st;
+// Wait for snapshot `seq`.  The device writes it to host memory, so the wait is a look at
+// that memory (an event would cost the stream a packet per snapshot and the host a trip
+// through the runtime); every few milliseconds the stream is asked whether it has failed or
+// drained.
+abac_status wait_snapshot(abac_plan* p, long long seq) {
+  using clock = std::chrono::steady_clock;
+  const auto t0 = clock::now();
+  auto asked = t0;
+  for (long long n = 1;; ++n) {
+    if (snapshot_ready(p, seq)) return ABAC_OK;
+    if (n % 64) {
+      std::atomic_signal_fence(std::memory_order_seq_cst);
+      continue;
+    }
+    const auto now = clock::now();
+    if (now - t0 > std::chrono::microseconds(200)) std::this_thread::yield();
+    if (now - asked > std::chrono::milliseconds(5)) {
+      asked = now;
+      const hipError_t e = hipStreamQuery(p->stream);
+      if (e == hipSuccess)
+        return snapshot_ready(p, seq) ? ABAC_OK : fail(ABAC_EDEVICE, "the stream drained without the solve's snapshot");
+      if (e != hipErrorNotReady) return hip_fail(e, "hipStreamQuery");
+    }
   }
 }
 
+bool all_stopped(const Snapshot* s, int B) {
+  for (int b = 0; b < B; ++b)
+    if (snap_state(s[b].word) == ST_RUNNING) return false;
+  return true;
+}
 
 struct TuneKey {
   int prec, nx, ny, nt, batch;
@@ -460,7 +475,7 @@ abac_status autotune(DevPlan& P, int prec, hipStream_t s, int maxlds) {
   // depend on its tile, so it is timed like the others; so is the last pass, which in
   // MINRES mode only writes z
   pick(TK_TIME, P.nt, &P.wg_t, [&] { return launch_time(P, prec, 1, s); });
-  if (!P.wg_s) pick(TK_XINV, 2 * P.Mx, &P.wg_xi, [&] { return launch_dstx_inv(P, prec, INV_Z_ITER, nullptr, s); });
+  if (!P.wg_s) pick(TK_XINV, 2 * P.Mx, &P.wg_xi, [&] { return launch_dstx_inv(P, prec, INV_Z_ITER, 1, nullptr, s); });
   HIP_TRY(hipMemsetAsync(P.st, 0, sizeof(MinresState) * P.B, s));
   HIP_TRY(hipStreamSynchronize(s));
   (void)hipGetLastError();
@@ -474,19 +489,12 @@ abac_status autotune(DevPlan& P, int prec, hipStream_t s, int maxlds) {
 
 namespace abac {
 
-abac_status plan_peek_snapshot(abac_plan* p, long long seq, int* ready, const MinresState** states) {
-  *ready = 0;
-  if (seq < 0 || seq >= p->ring_posted || seq < p->ring_posted - kSnapRing) return ABAC_OK;
-  const int slot = (int)(seq % kSnapRing);
-  hipError_t e = hipEventQuery(p->ring_ev[slot]);
-  if (e == hipErrorNotReady) return ABAC_OK;
-  if (e != hipSuccess) return hip_fail(e, "hipEventQuery");
-  *ready = 1;
-  *states = p->h_ring + (size_t)slot * p->P.B;
-  return ABAC_OK;
+bool plan_peek_snapshot(const abac_plan* p, long long seq, const Snapshot** snaps) {
+  if (seq < 0 || seq >= p->ring_posted || seq < p->ring_posted - kSnapRing) return false;
+  if (!snapshot_ready(p, seq)) return false;
+  *snaps = p->h_ring + (size_t)(seq % kSnapRing) * p->P.B;
+  return true;
 }
-
-long long plan_snapshots_posted(const abac_plan* p) { return p->ring_posted; }
 
 void set_last_error(const std::string& msg) { g_last_error = msg; }
 
@@ -825,27 +833,19 @@ abac_status abac_plan_create(int nx, int ny, int nt, double T, double alpha, int
   p->coef_ws = reinterpret_cast<double*>(base + Lo.coef);
   p->abar = 1.0;
   p->h_ring = nullptr;
-  p->cap_stream = nullptr;
-  p->iter_graph = nullptr;
-  p->graph_f = nullptr;
-  p->graph_u = nullptr;
-  {
-    const char* env = std::getenv("ABAC_GRAPH");
-    p->use_graph = !(env && env[0] == '0');
-  }
-  e = hipHostMalloc(reinterpret_cast<void**>(&p->h_ring), sizeof(MinresState) * (size_t)kSnapRing * batch,
+  e = hipHostMalloc(reinterpret_cast<void**>(&p->h_ring), sizeof(Snapshot) * (size_t)kSnapRing * batch,
                     hipHostMallocMapped);
   if (e == hipSuccess) {
-    std::memset(p->h_ring, 0, sizeof(MinresState) * (size_t)kSnapRing * batch);
+    std::memset(p->h_ring, 0, sizeof(Snapshot) * (size_t)kSnapRing * batch);
     e = hipHostGetDevicePointer(reinterpret_cast<void**>(&p->P.host_ring), p->h_ring, 0);
   }
-  for (int i = 0; e == hipSuccess && i < kSnapRing; ++i) e = hipEventCreateWithFlags(&p->ring_ev[i], hipEventDisableTiming);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking);
   if (e != hipSuccess) {
+    if (p->h_ring) (void)hipHostFree(p->h_ring);
     if (own) (void)hipFree(ws);
     delete p;
     return hip_fail(e, "host ring");
   }
+  p->epoch = 0;
   p->ring_posted = 0;
   p->f = nullptr;
   p->u = nullptr;
@@ -864,9 +864,6 @@ abac_status abac_plan_destroy(abac_plan* p) {
   (void)hipStreamSynchronize(p->stream);
   flush_prof(p);
   for (hipEvent_t e : p->event_pool) (void)hipEventDestroy(e);
-  for (int i = 0; i < kSnapRing; ++i) (void)hipEventDestroy(p->ring_ev[i]);
-  if (p->iter_graph) (void)hipGraphExecDestroy(p->iter_graph);
-  if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
   if (p->h_ring) (void)hipHostFree(p->h_ring);
   if (p->own_ws) (void)hipFree(p->ws);
   delete p;
@@ -906,11 +903,6 @@ abac_status abac_plan_set_coefficient(abac_plan* p, const double* a_xh, const do
   P.coef_x = a_xh ? p->coef_ws : nullptr;
   P.coef_y = a_xh && P.ny ? p->coef_ws + nfx : nullptr;
   p->abar = abar;
-  // kernels take the plan by value: a captured iteration holds the old coefficients
-  if (p->iter_graph) {
-    HIP_TRY(hipGraphExecDestroy(p->iter_graph));
-    p->iter_graph = nullptr;
-  }
   return ABAC_OK;
 }
 
@@ -1020,30 +1012,100 @@ abac_status abac_gmres_solve(abac_plan* p, const double* f, double* u, double to
   return worst;
 }
 
+namespace {
+
+void start_solve(abac_plan* p, const double* f, double* u) {
+  p->f = f;
+  p->u = u;
+  p->active = true;
+  p->epoch = (p->epoch + 1) & 0xffff;
+  p->ring_posted = 0;
+}
+
+FinArgs solve_args(const abac_plan* p, double tol, int maxit) {
+  FinArgs a;
+  a.tol = tol;
+  a.maxit = maxit;
+  a.epoch = p->epoch;
+  return a;
+}
+
+const Snapshot* newest_snapshot(const abac_plan* p) {
+  return p->h_ring + (size_t)((p->ring_posted - 1) % kSnapRing) * p->P.B;
+}
+
+// The results of a solve whose enqueued work has run.
+abac_status finish_solve(abac_plan* p, int* iters, double* relres, int* status) {
+  struct Result {
+    int iter, state, status;
+    double bnorm2, res2, tol2;
+  };
+  const int B = p->P.B;
+  std::vector<Result> h(B);
+  std::vector<MinresState> st;
+  auto read_states = [&]() -> abac_status {
+    st.resize(B);
+    HIP_TRY(hipMemcpyAsync(st.data(), p->P.st, sizeof(MinresState) * B, hipMemcpyDeviceToHost, p->stream));
+    HIP_TRY(hipStreamSynchronize(p->stream));
+    for (int b = 0; b < B; ++b) h[b] = {st[b].iter, st[b].state, st[b].status, st[b].bnorm2, st[b].res2, st[b].tol2};
+    return ABAC_OK;
+  };
+  if (p->ring_posted > 0 && snapshot_ready(p, p->ring_posted - 1)) {
+    const Snapshot* s = newest_snapshot(p);
+    for (int b = 0; b < B; ++b) h[b] = {s[b].iter, snap_state(s[b].word), s[b].status, s[b].bnorm2, s[b].res2, s[b].tol2};
+  } else {
+    abac_status e = read_states();
+    if (e != ABAC_OK) return e;
+  }
+  // The explicit residual of the final iterate is already known for right-hand sides
+  // stopped by the convergence test or maxit; recompute it otherwise.
+  bool report = false;
+  for (int b = 0; b < B; ++b)
+    if (h[b].state != ST_DONE || (h[b].status != ABAC_OK && h[b].status != ABAC_ENOTCONV) ||
+        (h[b].status == ABAC_OK && h[b].iter > 0 && h[b].res2 > h[b].tol2 * h[b].bnorm2))
+      report = true;
+  if (report) {
+    RUN(ABAC_K_FIN, launch_fin(p->P, FIN_FINAL, FinArgs{}, p->stream));
+    RUN(ABAC_K_FORM, launch_form(p->P, p->u, p->stream));
+    RUN(ABAC_K_RESIDUAL, launch_stencil(p->P, STENCIL_REPORT, p->u, nullptr, p->f, p->stream));
+    RUN(ABAC_K_FIN, launch_fin(p->P, FIN_REPORT, FinArgs{}, p->stream));
+    abac_status e = read_states();
+    if (e != ABAC_OK) return e;
+  }
+  p->active = false;
+  abac_status worst = ABAC_OK;
+  for (int b = 0; b < B; ++b) {
+    if (iters) iters[b] = h[b].iter;
+    if (relres) relres[b] = h[b].bnorm2 > 0 ? std::sqrt(h[b].res2 / h[b].bnorm2) : 0.0;
+    const int code = h[b].state == ST_DONE ? h[b].status : ABAC_ENOTCONV;
+    if (status) status[b] = code;
+    if (code != ABAC_OK && worst == ABAC_OK) worst = (abac_status)code;
+  }
+  return worst;
+}
+
+}  // namespace
+
 abac_status abac_minres_begin(abac_plan* p, const double* f, double* u, double tol, int maxit) {
   if (!p || !f || !u) return fail(ABAC_EINVAL, "NULL argument");
   if (!(tol > 0) || maxit < 1) return fail(ABAC_EINVAL, "tol must be > 0 and maxit >= 1");
   if (f == u) return fail(ABAC_EINVAL, "u must not alias f");
-  p->f = f;
-  p->u = u;
-  p->active = true;
-  p->ring_posted = 0;
+  start_solve(p, f, u);
   if (p->P.small) {
-    RUN(ABAC_K_INIT, launch_setup_small(p->P, p->prec, f, u, tol, maxit, p->stream));   // ends with the snapshot
-    return record_snapshot_event(p);
+    RUN(ABAC_K_INIT, launch_setup_small(p->P, p->prec, f, u, solve_args(p, tol, maxit), p->stream));
+  } else {
+    RUN(ABAC_K_INIT, launch_init(p->P, f, u, tol, maxit, p->epoch, p->stream));
+    abac_status s = enqueue_pinv_init(p);
+    if (s != ABAC_OK) return s;
   }
-  RUN(ABAC_K_INIT, launch_init(p->P, f, u, tol, maxit, p->stream));
-  abac_status s = enqueue_pinv_init(p);   // ends with the set-up snapshot
-  if (s != ABAC_OK) return s;
-  return record_snapshot_event(p);
+  p->ring_posted++;   // the set-up ends with its snapshot
+  return ABAC_OK;
 }
 
 abac_status abac_minres_advance(abac_plan* p, int iterations) {
   if (!p || !p->active) return fail(ABAC_EINVAL, "no solve in progress");
   for (int i = 0; i < iterations; ++i) {
-    abac_status s = launch_iteration(p);
-    if (s != ABAC_OK) return s;
-    s = record_snapshot_event(p);
+    abac_status s = enqueue_iteration(p, false);
     if (s != ABAC_OK) return s;
   }
   return ABAC_OK;
@@ -1058,93 +1120,55 @@ abac_status abac_minres_poll(abac_plan* p, int* done) {
   }
   // newest completed snapshot of this solve
   for (long long k = p->ring_posted - 1; k >= 0 && k >= p->ring_posted - kSnapRing; --k) {
-    const int slot = (int)(k % kSnapRing);
-    hipError_t e = hipEventQuery(p->ring_ev[slot]);
-    if (e == hipSuccess) {
-      *done = all_stopped(p->h_ring + (size_t)slot * p->P.B, p->P.B) ? 1 : 0;
+    const Snapshot* s;
+    if (plan_peek_snapshot(p, k, &s)) {
+      *done = all_stopped(s, p->P.B) ? 1 : 0;
       return ABAC_OK;
     }
-    if (e != hipErrorNotReady) return hip_fail(e, "hipEventQuery");
   }
-  return ABAC_OK;
+  const hipError_t e = hipStreamQuery(p->stream);
+  return e == hipSuccess || e == hipErrorNotReady ? ABAC_OK : hip_fail(e, "hipStreamQuery");
 }
 
 abac_status abac_minres_finish(abac_plan* p, int* iters, double* relres, int* status) {
   if (!p || !p->active) return fail(ABAC_EINVAL, "no solve in progress");
-  std::vector<MinresState> h(p->P.B);
-  HIP_TRY(hipMemcpyAsync(h.data(), p->P.st, sizeof(MinresState) * p->P.B, hipMemcpyDeviceToHost, p->stream));
   HIP_TRY(hipStreamSynchronize(p->stream));
-  // The explicit residual of the final iterate is already known for right-hand sides
-  // stopped by the convergence test or maxit; recompute it otherwise.
-  bool report = false;
-  for (int b = 0; b < p->P.B; ++b)
-    if (h[b].state != ST_DONE || (h[b].status != ABAC_OK && h[b].status != ABAC_ENOTCONV) ||
-        (h[b].status == ABAC_OK && h[b].iter > 0 && h[b].res2 > h[b].tol2 * h[b].bnorm2))
-      report = true;
-  if (report) {
-    RUN(ABAC_K_FIN, launch_fin(p->P, FIN_FINAL, 0.0, 0, p->stream));
-    RUN(ABAC_K_FORM, launch_form(p->P, p->u, p->stream));
-    RUN(ABAC_K_RESIDUAL, launch_stencil(p->P, STENCIL_REPORT, p->u, nullptr, p->f, p->stream));
-    RUN(ABAC_K_FIN, launch_fin(p->P, FIN_REPORT, 0.0, 0, p->stream));
-    HIP_TRY(hipMemcpyAsync(h.data(), p->P.st, sizeof(MinresState) * p->P.B, hipMemcpyDeviceToHost, p->stream));
-    HIP_TRY(hipStreamSynchronize(p->stream));
-  }
-  p->active = false;
-  abac_status worst;
-  fill_results(h.data(), p->P.B, iters, relres, status, &worst);
-  return worst;
+  return finish_solve(p, iters, relres, status);
 }
 
 abac_status abac_minres_solve(abac_plan* p, const double* f, double* u, double tol, int maxit, int* iters,
                               double* relres, int* status) {
   if (p && p->P.small && f && u && f != u && tol > 0 && maxit >= 1) {
     // small problems: the set-up and every iteration in one launch
-    p->f = f;
-    p->u = u;
-    p->active = true;
-    p->ring_posted = 0;
-    RUN(ABAC_K_ITER, launch_solve_small(p->P, p->prec, f, u, tol, maxit, p->stream));
+    start_solve(p, f, u);
+    RUN(ABAC_K_ITER, launch_solve_small(p->P, p->prec, f, u, solve_args(p, tol, maxit), p->stream));
+    p->ring_posted++;
     return abac_minres_finish(p, iters, relres, status);
   }
   abac_status s = abac_minres_begin(p, f, u, tol, maxit);
-  if (s != ABAC_OK) return s;
-  // Keep up to kAhead iterations queued beyond the newest observed state while the
-  // observed residual decay predicts that convergence is further away; near the
-  // predicted stop, step one iteration at a time so no idle iterations are queued.
-  const int kAhead = 2;
-  const int B = p->P.B;
-  long long enq = 0, obs = 0;
-  long long est = LLONG_MAX;
-  double rel_last = -1.0;
-  while (true) {
-    if (enq < maxit && enq - obs <= kAhead && enq < est) {
-      s = abac_minres_advance(p, 1);
-      if (s != ABAC_OK) return s;
-      ++enq;
-      continue;
+  // Each iteration is enqueued once the stopping test of the one before has been read:
+  // that test posts its snapshot ahead of the iteration's inverse transforms, which run
+  // while the host enqueues the next iteration, and no iteration is launched in vain.
+  while (s == ABAC_OK) {
+    s = enqueue_iteration(p, true);
+    if (s == ABAC_OK) s = wait_snapshot(p, p->ring_posted - 1);
+    if (s != ABAC_OK) break;
+    const Snapshot* snap = newest_snapshot(p);
+    bool hold = false;
+    for (int b = 0; b < p->P.B; ++b) hold = hold || snap_hold(snap[b].word);
+    if (hold) {
+      s = enqueue_check(p);
+      if (s == ABAC_OK) s = wait_snapshot(p, p->ring_posted - 1);
+      if (s != ABAC_OK) break;
+      snap = newest_snapshot(p);
+      if (!all_stopped(snap, p->P.B) && p->prec != ABAC_PREC_NONE) {
+        s = enqueue_pinv_tail(p, nullptr, INV_Z_ITER, CHECK_RESUME);
+        if (s != ABAC_OK) break;
+      }
     }
-    if (obs >= enq) {
-      if (enq >= maxit) break;
-      est = enq + 1;   // prediction was early: take one more step
-      continue;
-    }
-    const int slot = (int)((obs + 1) % kSnapRing);
-    HIP_TRY(hipEventSynchronize(p->ring_ev[slot]));
-    ++obs;
-    const MinresState* snap = p->h_ring + (size_t)slot * B;
-    if (all_stopped(snap, B)) break;
-    double rel = 0.0;
-    for (int b = 0; b < B; ++b)
-      if (snap[b].state == ST_RUNNING && snap[b].bnorm2 > 0) rel = std::max(rel, std::sqrt(snap[b].rnorm2 / snap[b].bnorm2));
-    if (rel_last > 0.0 && rel > 0.0 && rel < rel_last) {
-      const double rem = std::ceil(std::log(tol / rel) / std::log(rel / rel_last));
-      est = obs + (long long)std::max(1.0, std::min(rem, 1e6));
-    } else {
-      est = LLONG_MAX;
-    }
-    rel_last = rel;
+    if (all_stopped(snap, p->P.B)) return finish_solve(p, iters, relres, status);
   }
-  return abac_minres_finish(p, iters, relres, status);
+  return s;
 }
 
 abac_status abac_profile_enable(abac_plan* p, int on) {
@@ -1197,11 +1221,6 @@ abac_status abac_plan_set_tiles(abac_plan* p, int wg_x, int wg_y, int wg_t, int 
   if (wg_x) P.wg_x = wg_x;
   if (wg_y) P.wg_y = wg_y;
   if (wg_t) P.wg_t = wg_t;
-  // kernels take the plan by value: a captured iteration holds the old tiles
-  if (p->iter_graph) {
-    HIP_TRY(hipGraphExecDestroy(p->iter_graph));
-    p->iter_graph = nullptr;
-  }
   return ABAC_OK;
 }
 
@@ -1274,13 +1293,13 @@ abac_status abac_apply_Pinv_noalloc(int nx, int ny, int nt, double T, double alp
   if (P.wg_s) {
     if ((e = launch_dst2_fwd(P, prec, FWD_PLAIN, 0, r, st)) != hipSuccess) return hip_fail(e, "launch_dst2_fwd");
     if ((e = launch_time(P, prec, 0, st)) != hipSuccess) return hip_fail(e, "launch_time");
-    if ((e = launch_dst2_inv(P, prec, INV_PLAIN, z, st)) != hipSuccess) return hip_fail(e, "launch_dst2_inv");
+    if ((e = launch_dst2_inv(P, prec, INV_PLAIN, 0, z, st)) != hipSuccess) return hip_fail(e, "launch_dst2_inv");
   } else {
     if ((e = launch_dstx_fwd(P, prec, FWD_PLAIN, 0, r, st)) != hipSuccess) return hip_fail(e, "launch_dstx_fwd");
     if (P.ny && (e = launch_dsty(P, prec, 0, st)) != hipSuccess) return hip_fail(e, "launch_dsty");
     if ((e = launch_time(P, prec, 0, st)) != hipSuccess) return hip_fail(e, "launch_time");
     if (P.ny && (e = launch_dsty(P, prec, 0, st)) != hipSuccess) return hip_fail(e, "launch_dsty");
-    if ((e = launch_dstx_inv(P, prec, INV_PLAIN, z, st)) != hipSuccess) return hip_fail(e, "launch_dstx_inv");
+    if ((e = launch_dstx_inv(P, prec, INV_PLAIN, 0, z, st)) != hipSuccess) return hip_fail(e, "launch_dstx_inv");
   }
   return ABAC_OK;
 }

@@ -55,7 +55,37 @@ struct MinresState {
   int flush_now;
   int track;        // P.R holds the residual vector, updated by the first transform pass
   int want_r;       // the explicit check also writes the residual vector to P.R
+  int hold;         // the stopping test asked for a form or check step: nothing else runs before it
+  int tail;         // the inverse transforms of the last iteration were held back
+  int epoch;        // which solve of the plan this is (tags its snapshots)
 };
+// An iteration's kernels skip a right-hand side that stopped or waits for a check.
+__device__ __forceinline__ bool rhs_active(const MinresState* st) { return st->state == ST_RUNNING && !st->hold; }
+// How a transform pass decides that: 0 always run; CHECK_ACTIVE; CHECK_RESUME the inverse
+// passes after a check, only where they were held back.
+enum PassCheck : int { CHECK_NONE = 0, CHECK_ACTIVE = 1, CHECK_RESUME = 2 };
+__device__ __forceinline__ bool pass_runs(const MinresState* st, int check) {
+  return check == CHECK_NONE || (rhs_active(st) && (check == CHECK_ACTIVE || st->tail));
+}
+
+// What the host sees of a right-hand side after the set-up and after the scalar steps of
+// an iteration, in host-mapped memory.  `word` is written last and names the snapshot, so
+// the host needs no event to know that a snapshot is complete: epoch (16 bits), sequence
+// number + 1 (24), hold (bit 2), state (bits 0-1).
+struct Snapshot {
+  unsigned long long word;
+  int status, iter;
+  double rnorm2, bnorm2, res2, tol2;
+  double pad_[2];
+};
+static_assert(sizeof(Snapshot) == 64, "one line of host memory per snapshot");
+__host__ __device__ inline unsigned long long snap_word(int epoch, long long seq, int state, int hold) {
+  return (unsigned long long)(epoch & 0xffff) << 48 | (unsigned long long)((seq + 1) & 0xffffff) << 24 |
+         (unsigned long long)(hold ? 4 : 0) | (unsigned long long)state;
+}
+__host__ __device__ inline unsigned long long snap_name(unsigned long long word) { return word >> 24; }
+__host__ __device__ inline int snap_state(unsigned long long word) { return (int)(word & 3); }
+__host__ __device__ inline bool snap_hold(unsigned long long word) { return (word & 4) != 0; }
 
 // More per right-hand side state of a MINRES solve, kept in the right-hand side's GMRES
 // state (the two solvers never run on one plan together).
@@ -147,7 +177,7 @@ struct DevPlan {
   MinresState* st;     // B entries
   double* partials;    // PART_KINDS * B * maxparts
   unsigned* counters;  // B entries
-  MinresState* host_ring;  // device view of the host-mapped snapshot ring (kSnapRing * B)
+  Snapshot* host_ring;     // device view of the host-mapped snapshot ring (kSnapRing * B)
   int maxparts;
   // workgroup sizes of the transform kernels (chosen by the plan's autotuner)
   int wg_x, wg_xi, wg_y, wg_t;
@@ -293,7 +323,7 @@ int dstx_blocks(const DevPlan& P, int wg);
 hipError_t launch_stencil(const DevPlan& P, int mode, const double* x, double* y, const double* f, hipStream_t s);
 hipError_t launch_rhs(const DevPlan& P, const double* src, const double* psi0, const double* psi1, double* f,
                       hipStream_t s);
-hipError_t launch_init(const DevPlan& P, const double* f, double* u, double tol, int maxit, hipStream_t s);
+hipError_t launch_init(const DevPlan& P, const double* f, double* u, double tol, int maxit, int epoch, hipStream_t s);
 // identity preconditioner: z = r (mode 0), or the MINRES set-up / Lanczos step with
 // z = q and the partials of <q, q> (modes INV_GAMMA_INIT / INV_GAMMA_ITER)
 hipError_t launch_identity(const DevPlan& P, int mode, const double* in, double* out, hipStream_t s);
@@ -314,28 +344,31 @@ static_assert(kGmresMax + 1 <= kZSlots + 2, "the Arnoldi basis must fit the Z an
 hipError_t launch_form(const DevPlan& P, double* u, hipStream_t s);
 // one block per right-hand side: fixed-order sum of the partials of a reduction and
 // the scalar step that consumes it
-hipError_t launch_fin(const DevPlan& P, int kind, double tol, int maxit, hipStream_t s);
+struct FinArgs {
+  double tol = 0.0;            // FIN_BNORM
+  int maxit = 0, epoch = 0;
+  int post = 0;                // FIN_GAMMA_ITER: post a snapshot (the set-up and FIN_RES always do)
+};
+hipError_t launch_fin(const DevPlan& P, int kind, const FinArgs& a, hipStream_t s);
 
-// check != 0: skip right-hand sides whose solve is not running
+// check: which right-hand sides the pass skips (PassCheck)
 hipError_t launch_dstx_fwd(const DevPlan& P, int prec, int mode, int check, const double* in, hipStream_t s);
 hipError_t launch_dsty(const DevPlan& P, int prec, int check, hipStream_t s);
 // inv1 = 1: the single time pass of C_alpha^{-1} (mu^{-1}, no time reversal); with check
 // (and inv1 = 0) the pass also writes the partials of <q, P^{-1} q> (PART_GAMMA, one
 // per mode pair)
 hipError_t launch_time(const DevPlan& P, int prec, int check, hipStream_t s, int inv1 = 0);
-hipError_t launch_dstx_inv(const DevPlan& P, int prec, int mode, double* out, hipStream_t s);
+hipError_t launch_dstx_inv(const DevPlan& P, int prec, int mode, int check, double* out, hipStream_t s);
 // fused 2D first / last pass (square grids whose level fits in LDS; P.wg_s != 0)
 hipError_t launch_dst2_fwd(const DevPlan& P, int prec, int mode, int check, const double* in, hipStream_t s);
-hipError_t launch_dst2_inv(const DevPlan& P, int prec, int mode, double* out, hipStream_t s);
+hipError_t launch_dst2_inv(const DevPlan& P, int prec, int mode, int check, double* out, hipStream_t s);
 int slab_wg(int nx, int ny, int prec, int maxlds, size_t margin);
 // dynamic LDS bytes of the fused 2D passes with workgroup wg (0 if not legal)
 size_t slab_lds_bytes(int L, int wg, int prec);
 // fused small-problem iteration (1D, nt * nx <= 4096; P.small != 0)
 hipError_t launch_iter_small(const DevPlan& P, int prec, const double* f, double* u, hipStream_t s);
-hipError_t launch_setup_small(const DevPlan& P, int prec, const double* f, double* u, double tol, int maxit,
-                              hipStream_t s);
-hipError_t launch_solve_small(const DevPlan& P, int prec, const double* f, double* u, double tol, int maxit,
-                              hipStream_t s);
+hipError_t launch_setup_small(const DevPlan& P, int prec, const double* f, double* u, const FinArgs& a, hipStream_t s);
+hipError_t launch_solve_small(const DevPlan& P, int prec, const double* f, double* u, const FinArgs& a, hipStream_t s);
 bool small_path_valid(int nx, int ny, int nt, int prec);
 // transform kernel kinds (tile validity and LDS size differ per kind)
 enum TransformKind : int { TK_XFWD = 0, TK_XINV = 1, TK_Y = 2, TK_TIME = 3 };

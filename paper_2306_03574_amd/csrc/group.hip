@@ -87,8 +87,7 @@ __device__ __forceinline__ void group_stencil(const GroupTable* __restrict__ G, 
   const GroupMember& M = G->m[at.r];
   const DevPlan& P = M.P;
   const MinresState* st = P.st + at.b;
-  if (st->state != ST_RUNNING) return;
-  if (MODE == STENCIL_RESIDUAL && !st->need_check) return;
+  if (MODE == STENCIL_RESIDUAL ? st->state != ST_RUNNING || !st->need_check : !rhs_active(st)) return;
   const size_t off = (size_t)at.b * P.N;
   double acc = 0.0;
   const bool lane = (int)threadIdx.x < P.st_threads;
@@ -149,7 +148,7 @@ __device__ __forceinline__ double sum_parts_as(const double* __restrict__ part, 
 __device__ __forceinline__ void group_fin(const GroupTable* __restrict__ G, int w, int kind) {
   const Where at = locate(G, GS_FIN, w);
   const DevPlan& P = G->m[at.r].P;
-  if (!fin_begin(P, at.b, kind)) return;
+  if (!fin_begin(P, at.b, kind, FinArgs{})) return;
   int nparts;
   switch (kind) {
     case FIN_DELTA: nparts = stencil_blocks(P); break;
@@ -160,7 +159,7 @@ __device__ __forceinline__ void group_fin(const GroupTable* __restrict__ G, int 
   Dots3 dots{0.0, 0.0, 0.0};
   if (kind == FIN_GAMMA_ITER) dots = sum_dots(P, at.b, (G->off[GS_XFWD][at.r + 1] - G->off[GS_XFWD][at.r]) / P.B);
   const double tot = sum_parts_as(part_slot(P, fin_part_kind(kind), at.b), nparts, kGroupFinThreads);
-  if (threadIdx.x == 0) fin_scalar(P, at.b, kind, tot, dots, 0.0, 0);
+  if (threadIdx.x == 0) fin_scalar(P, at.b, kind, tot, dots, FinArgs{});
 }
 
 // ---- vector step: iterate from the basis --------------------------------------------
@@ -185,7 +184,7 @@ template <typename T>
 __device__ __forceinline__ void group_xfwd(const GroupTable* __restrict__ G, int w) {
   const Where at = locate(G, GS_XFWD, w);
   const DevPlan& P = G->m[at.r].P;
-  if (P.st[at.b].state != ST_RUNNING) return;
+  if (!rhs_active(P.st + at.b)) return;
   constexpr int mode = FWD_LANCZOS;
   const double* in = nullptr;
   const int L = 2 * P.Mx;
@@ -209,7 +208,7 @@ template <typename T>
 __device__ __forceinline__ void group_y(const GroupTable* __restrict__ G, int w) {
   const Where at = locate(G, GS_Y, w);
   const DevPlan& P = G->m[at.r].P;
-  if (P.st[at.b].state != ST_RUNNING) return;
+  if (!rhs_active(P.st + at.b)) return;
   const int lbk = xcd_remap(at.lbk, at.per);
 #define CASE(LL) \
   case LL: if constexpr (tile_ok<T, LL, kGroupWG, TK_Y>()) dsty_tile<T, LL, kGroupWG>(P, at.b, lbk); break;
@@ -221,7 +220,7 @@ template <typename T>
 __device__ __forceinline__ void group_time(const GroupTable* __restrict__ G, int w) {
   const Where at = locate(G, GS_TIME, w);
   const DevPlan& P = G->m[at.r].P;
-  if (P.st[at.b].state != ST_RUNNING) return;
+  if (!rhs_active(P.st + at.b)) return;
   const int lbk = xcd_remap(at.lbk, at.per);
 #define CASE(LL) \
   case LL: if constexpr (tile_ok<T, LL, kGroupWG, TK_TIME>()) time_tile<T, LL, kGroupWG>(P, 0, at.b, lbk, 1); break;
@@ -235,7 +234,7 @@ __device__ __forceinline__ void group_xinv(const GroupTable* __restrict__ G, int
   constexpr int mode = INV_Z_ITER;
   const Where at = locate(G, GS_XINV, w);
   const DevPlan& P = G->m[at.r].P;
-  if (P.st[at.b].state != ST_RUNNING) return;
+  if (!rhs_active(P.st + at.b)) return;
   const int L = 2 * P.Mx;
   if (P.wg_s) {
 #define CASE(LL) \
@@ -487,15 +486,9 @@ abac_status group_iteration(abac_group* g) {
   return ABAC_OK;
 }
 
-// each member's snapshot of every enqueued iteration is complete behind this point
-abac_status post_snapshots(abac_group* g, int iterations) {
-  for (int it = 0; it < iterations; ++it)
-    for (abac_plan* p : g->members) {
-      const int slot = (int)(p->ring_posted % kSnapRing);
-      GHIP(hipEventRecord(p->ring_ev[slot], g->stream));
-      p->ring_posted++;
-    }
-  return ABAC_OK;
+// every enqueued iteration posts one snapshot of each member
+void count_snapshots(abac_group* g, int iterations) {
+  for (abac_plan* p : g->members) p->ring_posted += iterations;
 }
 
 abac_status check_members(abac_group* g, int iterations) {
@@ -635,7 +628,7 @@ abac_status abac_group_advance(abac_group* g, int iterations) {
   GRUN(check_members(g, iterations));
   for (int it = 0; it < iterations && !g->members.empty(); ++it) {
     GRUN(g->prec == ABAC_PREC_FP32 ? group_iteration<float>(g) : group_iteration<double>(g));
-    GRUN(post_snapshots(g, 1));
+    count_snapshots(g, 1);
   }
   return group_release(g);
 }
@@ -689,7 +682,7 @@ abac_status abac_group_run(abac_group* g, int iterations, int blocks, double tim
     hipLaunchKernelGGL((k_group_persistent<double>), dim3(grid), dim3(kGroupWG), lds, g->stream, g->d_table,
                        iterations, g->d_sync, deadline);
   GHIP(hipGetLastError());
-  GRUN(post_snapshots(g, iterations));
+  count_snapshots(g, iterations);
   return group_release(g);
 }
 

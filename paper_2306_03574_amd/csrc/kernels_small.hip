@@ -115,7 +115,7 @@ __device__ __noinline__ void iter_small(const DevPlan& P, const double* __restri
     const int j = st->iter + 1;
     const double acc = stencil_small<OUT_REV, true>(P, P.Z[zslot(j)] + off, P.V[(j + 1) % 3] + off, nullptr);
     const double tot = block_sum(acc);
-    if (fin_begin(P, b, FIN_DELTA) && tid == 0) fin_scalar(P, b, FIN_DELTA, tot, Dots3{}, 0.0, 0);
+    if (fin_begin(P, b, FIN_DELTA, FinArgs{}) && tid == 0) fin_scalar(P, b, FIN_DELTA, tot, Dots3{}, FinArgs{});
     __syncthreads();
   }
   // Lanczos vector and the first half of z_{j+1} = P^{-1} q: x-DST (Lanczos fused), time
@@ -135,7 +135,7 @@ __device__ __noinline__ void iter_small(const DevPlan& P, const double* __restri
     }
     const Dots3 dots = sum_dots(P, b, xtiles);
     const double tot = sum_parts(part_slot(P, PART_GAMMA, b), P.ms / 2);
-    if (fin_begin(P, b, FIN_GAMMA_ITER) && tid == 0) fin_scalar(P, b, FIN_GAMMA_ITER, tot, dots, 0.0, 0);
+    if (fin_begin(P, b, FIN_GAMMA_ITER, FinArgs{}) && tid == 0) fin_scalar(P, b, FIN_GAMMA_ITER, tot, dots, FinArgs{});
     __syncthreads();
   }
   // the iterate from the resident basis when a check, a stop or the flush needs it
@@ -149,7 +149,7 @@ __device__ __noinline__ void iter_small(const DevPlan& P, const double* __restri
     if (st->state == ST_RUNNING && st->need_check)
       tot = block_sum(st->want_r ? stencil_small<OUT_RESREV, false>(P, u + off, P.R + off, f + off)
                                  : stencil_small<OUT_RESNORM, false>(P, u + off, nullptr, f + off));
-    if (fin_begin(P, b, FIN_RES) && tid == 0) fin_scalar(P, b, FIN_RES, tot, Dots3{}, 0.0, 0);
+    if (fin_begin(P, b, FIN_RES, FinArgs{}) && tid == 0) fin_scalar(P, b, FIN_RES, tot, Dots3{}, FinArgs{});
     __syncthreads();
   }
   // the second half of z_{j+1}: inverse x-DST
@@ -173,7 +173,7 @@ k_iter_small(DevPlan P, const double* __restrict__ f, double* __restrict__ u) {
 // first preconditioner apply, in the same order and under the same conditions).
 template <typename T, int L, int NT>
 __device__ __noinline__ void setup_small(const DevPlan& P, const double* __restrict__ f, double* __restrict__ u,
-                                         double tol, int maxit, const cplx<T>* twx) {
+                                         const FinArgs& a, const cplx<T>* twx) {
   constexpr int WG = kSmallWG;
   const int b = blockIdx.x;
   const size_t off = (size_t)b * P.N;
@@ -189,7 +189,7 @@ __device__ __noinline__ void setup_small(const DevPlan& P, const double* __restr
       acc += v * v;
     }
     const double tot = block_sum(acc);
-    if (fin_begin(P, b, FIN_BNORM) && tid == 0) fin_scalar(P, b, FIN_BNORM, tot, Dots3{}, tol, maxit);
+    if (fin_begin(P, b, FIN_BNORM, a) && tid == 0) fin_scalar(P, b, FIN_BNORM, tot, Dots3{}, a);
     __syncthreads();
   }
   double tot = 0.0;
@@ -211,20 +211,20 @@ __device__ __noinline__ void setup_small(const DevPlan& P, const double* __restr
       __syncthreads();
     }
   }
-  if (fin_begin(P, b, FIN_GAMMA_INIT) && tid == 0) fin_scalar(P, b, FIN_GAMMA_INIT, tot, Dots3{}, 0.0, 0);
+  if (fin_begin(P, b, FIN_GAMMA_INIT, a) && tid == 0) fin_scalar(P, b, FIN_GAMMA_INIT, tot, Dots3{}, a);
 }
 
 template <typename T, int L, int NT>
 __global__ void __launch_bounds__(kSmallWG)
-k_setup_small(DevPlan P, const double* __restrict__ f, double* __restrict__ u, double tol, int maxit) {
-  setup_small<T, L, NT>(P, f, u, tol, maxit, stage_twiddles_small<T, L, NT>(P));
+k_setup_small(DevPlan P, const double* __restrict__ f, double* __restrict__ u, FinArgs a) {
+  setup_small<T, L, NT>(P, f, u, a, stage_twiddles_small<T, L, NT>(P));
 }
 
 // A whole solve in one launch: the set-up, then iterations until the right-hand side
 // stops (at most maxit + 1, a safety net: the state machine stops it by maxit).
 template <typename T, int L, int NT>
 __global__ void __launch_bounds__(kSmallWG)
-k_solve_small(DevPlan P, const double* __restrict__ f, double* __restrict__ u, double tol, int maxit) {
+k_solve_small(DevPlan P, const double* __restrict__ f, double* __restrict__ u, FinArgs a) {
   // The right-hand side's scalar state stays in LDS for the whole solve (the scalar steps
   // and every thread's state tests read it many times per iteration) and goes back to
   // memory at the end.  Q addresses it as Q.st + blockIdx.x, like the kernels' state.
@@ -232,30 +232,35 @@ k_solve_small(DevPlan P, const double* __restrict__ f, double* __restrict__ u, d
   const int b = blockIdx.x;
   if (threadIdx.x == 0) st_lds = P.st[b];
   DevPlan Q = P;
+  Q.host_ring = nullptr;   // one snapshot, at the end of the solve
   Q.st = reinterpret_cast<MinresState*>(reinterpret_cast<uintptr_t>(&st_lds) - (uintptr_t)b * sizeof(MinresState));
   const cplx<T>* twx = stage_twiddles_small<T, L, NT>(Q);   // its barrier also publishes st_lds
-  setup_small<T, L, NT>(Q, f, u, tol, maxit, twx);
-  for (int it = 0; it <= maxit; ++it) {
+  setup_small<T, L, NT>(Q, f, u, a, twx);
+  for (int it = 0; it <= a.maxit; ++it) {
     __syncthreads();   // the previous step's state is visible to every thread
     if (st_lds.state != ST_RUNNING) break;
     iter_small<T, L, NT>(Q, f, u, twx);
   }
   __syncthreads();
-  if (threadIdx.x == 0) P.st[b] = st_lds;
+  if (threadIdx.x == 0) {
+    st_lds.snap = 0;
+    P.st[b] = st_lds;
+    post_snapshot(P, b);
+  }
 }
 
 // what: 0 one iteration, 1 the set-up, 2 a whole solve (set-up and iterations)
 template <typename T, int L, int NT>
-hipError_t launch_small_t(const DevPlan& P, const double* f, double* u, hipStream_t s, int what, double tol,
-                          int maxit) {
+hipError_t launch_small_t(const DevPlan& P, const double* f, double* u, hipStream_t s, int what,
+                          const FinArgs& a) {
   if constexpr (!small_ok<T, L, NT>()) {
     return hipErrorInvalidValue;
   } else {
     constexpr size_t lds = small_lds<T, L, NT>();
     if (what == 1)
-      hipLaunchKernelGGL((k_setup_small<T, L, NT>), dim3(P.B), dim3(kSmallWG), lds, s, P, f, u, tol, maxit);
+      hipLaunchKernelGGL((k_setup_small<T, L, NT>), dim3(P.B), dim3(kSmallWG), lds, s, P, f, u, a);
     else if (what == 2)
-      hipLaunchKernelGGL((k_solve_small<T, L, NT>), dim3(P.B), dim3(kSmallWG), lds, s, P, f, u, tol, maxit);
+      hipLaunchKernelGGL((k_solve_small<T, L, NT>), dim3(P.B), dim3(kSmallWG), lds, s, P, f, u, a);
     else
       hipLaunchKernelGGL((k_iter_small<T, L, NT>), dim3(P.B), dim3(kSmallWG), lds, s, P, f, u);
     return hipGetLastError();
@@ -274,9 +279,9 @@ hipError_t launch_small_t(const DevPlan& P, const double* f, double* u, hipStrea
   }
 
 template <typename T>
-hipError_t small_dispatch(const DevPlan& P, const double* f, double* u, hipStream_t s, int what, double tol,
-                          int maxit) {
-#define CALL(LL, NN) launch_small_t<T, LL, NN>(P, f, u, s, what, tol, maxit)
+hipError_t small_dispatch(const DevPlan& P, const double* f, double* u, hipStream_t s, int what,
+                          const FinArgs& a) {
+#define CALL(LL, NN) launch_small_t<T, LL, NN>(P, f, u, s, what, a)
   switch (2 * P.Mx) {
     case 16: ABAC_SMALL_NT(16, CALL)
     case 32: ABAC_SMALL_NT(32, CALL)
@@ -312,17 +317,15 @@ bool small_valid_t(int L, int nt) {
 }  // namespace
 
 hipError_t launch_iter_small(const DevPlan& P, int prec, const double* f, double* u, hipStream_t s) {
-  return prec ? small_dispatch<float>(P, f, u, s, 0, 0.0, 0) : small_dispatch<double>(P, f, u, s, 0, 0.0, 0);
+  return prec ? small_dispatch<float>(P, f, u, s, 0, FinArgs{}) : small_dispatch<double>(P, f, u, s, 0, FinArgs{});
 }
 
-hipError_t launch_setup_small(const DevPlan& P, int prec, const double* f, double* u, double tol, int maxit,
-                              hipStream_t s) {
-  return prec ? small_dispatch<float>(P, f, u, s, 1, tol, maxit) : small_dispatch<double>(P, f, u, s, 1, tol, maxit);
+hipError_t launch_setup_small(const DevPlan& P, int prec, const double* f, double* u, const FinArgs& a, hipStream_t s) {
+  return prec ? small_dispatch<float>(P, f, u, s, 1, a) : small_dispatch<double>(P, f, u, s, 1, a);
 }
 
-hipError_t launch_solve_small(const DevPlan& P, int prec, const double* f, double* u, double tol, int maxit,
-                              hipStream_t s) {
-  return prec ? small_dispatch<float>(P, f, u, s, 2, tol, maxit) : small_dispatch<double>(P, f, u, s, 2, tol, maxit);
+hipError_t launch_solve_small(const DevPlan& P, int prec, const double* f, double* u, const FinArgs& a, hipStream_t s) {
+  return prec ? small_dispatch<float>(P, f, u, s, 2, a) : small_dispatch<double>(P, f, u, s, 2, a);
 }
 
 bool small_path_valid(int nx, int ny, int nt, int prec) {

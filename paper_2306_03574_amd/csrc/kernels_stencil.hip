@@ -26,7 +26,7 @@ k_stencil(DevPlan P, const double* __restrict__ xin, double* __restrict__ yout, 
   const double* x = xin;
   double* y = yout;
   if (MODE == STENCIL_MINRES) {
-    if (st->state != ST_RUNNING) return;
+    if (!rhs_active(st)) return;
     const int j = st->iter + 1;
     x = P.Z[zslot(j)];
     y = P.V[(j + 1) % 3];
@@ -130,7 +130,7 @@ k_identity(DevPlan P, int mode, const double* __restrict__ in, double* __restric
     return;
   }
   const MinresState* st = P.st + b;
-  if (st->state != ST_RUNNING) return;
+  if (!rhs_active(st)) return;
   double acc = 0.0;
   if (mode == INV_GAMMA_INIT) {
     const double* __restrict__ q = P.V[1] + off;
@@ -161,13 +161,13 @@ k_identity(DevPlan P, int mode, const double* __restrict__ in, double* __restric
 constexpr int kFinThreads = 1024;
 
 __global__ void __launch_bounds__(kFinThreads)
-k_fin(DevPlan P, int kind, int nparts, int ndots, double tol, int maxit) {
+k_fin(DevPlan P, int kind, int nparts, int ndots, FinArgs a) {
   const int b = blockIdx.x;
-  if (!fin_begin(P, b, kind)) return;
+  if (!fin_begin(P, b, kind, a)) return;
   Dots3 dots{0.0, 0.0, 0.0};
   if (kind == FIN_GAMMA_ITER) dots = sum_dots(P, b, ndots);
   const double tot = sum_parts(part_slot(P, fin_part_kind(kind), b), nparts);
-  if (threadIdx.x == 0) fin_scalar(P, b, kind, tot, dots, tol, maxit);
+  if (threadIdx.x == 0) fin_scalar(P, b, kind, tot, dots, a);
 }
 
 }  // namespace
@@ -216,12 +216,16 @@ hipError_t launch_rhs(const DevPlan& P, const double* src, const double* psi0, c
   return hipGetLastError();
 }
 
-hipError_t launch_init(const DevPlan& P, const double* f, double* u, double tol, int maxit, hipStream_t s) {
+hipError_t launch_init(const DevPlan& P, const double* f, double* u, double tol, int maxit, int epoch, hipStream_t s) {
   dim3 grid(update_blocks(P), P.B);
   hipLaunchKernelGGL(k_init, grid, dim3(kVecThreads), 0, s, P, f, u);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_fin(P, FIN_BNORM, tol, maxit, s);
+  FinArgs a;
+  a.tol = tol;
+  a.maxit = maxit;
+  a.epoch = epoch;
+  return launch_fin(P, FIN_BNORM, a, s);
 }
 
 hipError_t launch_form(const DevPlan& P, double* u, hipStream_t s) {
@@ -236,7 +240,7 @@ hipError_t launch_identity(const DevPlan& P, int mode, const double* in, double*
   return hipGetLastError();
 }
 
-hipError_t launch_fin(const DevPlan& P, int kind, double tol, int maxit, hipStream_t s) {
+hipError_t launch_fin(const DevPlan& P, int kind, const FinArgs& a, hipStream_t s) {
   int nparts;
   switch (kind) {
     case FIN_BNORM: nparts = update_blocks(P); break;
@@ -247,7 +251,7 @@ hipError_t launch_fin(const DevPlan& P, int kind, double tol, int maxit, hipStre
   }
   // blocks of the first transform pass, which leave the inner products' partials
   const int ndots = kind != FIN_GAMMA_ITER || P.prec == 2 ? 0 : P.wg_s ? P.nt : dstx_blocks(P, P.wg_x);
-  hipLaunchKernelGGL(k_fin, dim3(P.B), dim3(kFinThreads), 0, s, P, kind, nparts, ndots, tol, maxit);
+  hipLaunchKernelGGL(k_fin, dim3(P.B), dim3(kFinThreads), 0, s, P, kind, nparts, ndots, a);
   return hipGetLastError();
 }
 

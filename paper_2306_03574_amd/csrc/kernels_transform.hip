@@ -29,14 +29,14 @@ namespace {
 template <typename T, int L, int WG>
 __global__ void __launch_bounds__(WG)
 k_dstx_fwd(DevPlan P, int mode, int check, const double* __restrict__ in) {
-  if ((check || mode == FWD_LANCZOS) && P.st[blockIdx.y].state != ST_RUNNING) return;
+  if (!pass_runs(P.st + blockIdx.y, check)) return;
   dstx_fwd_tile<T, L, WG>(P, mode, in, blockIdx.y, blockIdx.x, reinterpret_cast<const cplx<T>*>(P.twx));
 }
 
 template <typename T, int L, int WG>
 __global__ void __launch_bounds__(WG)
 k_dsty(DevPlan P, int check) {
-  if (check && P.st[blockIdx.y].state != ST_RUNNING) return;
+  if (!pass_runs(P.st + blockIdx.y, check)) return;
   // XCD-aware order: the blocks one XCD runs together read neighbouring column pairs of
   // a level, so partial cache lines are shared in its L2
   dsty_tile<T, L, WG>(P, blockIdx.y, xcd_remap(blockIdx.x, gridDim.x));
@@ -45,7 +45,7 @@ k_dsty(DevPlan P, int check) {
 template <typename T, int NT, int WG>
 __global__ void __launch_bounds__(WG)
 k_time(DevPlan P, int check, int inv1) {
-  if (check && P.st[blockIdx.y].state != ST_RUNNING) return;
+  if (!pass_runs(P.st + blockIdx.y, check)) return;
   // XCD-aware order: the blocks one XCD runs together read neighbouring column ranges of
   // each time level, so partial cache lines are shared in its L2.  In MINRES mode
   // (check) the pass also forms the partials of <q, P^{-1} q>.
@@ -54,9 +54,9 @@ k_time(DevPlan P, int check, int inv1) {
 
 template <typename T, int L, int WG>
 __global__ void __launch_bounds__(WG)
-k_dstx_inv(DevPlan P, int mode, double* __restrict__ outp) {
+k_dstx_inv(DevPlan P, int mode, int check, double* __restrict__ outp) {
   const int b = blockIdx.y;
-  if (mode != INV_PLAIN && P.st[b].state != ST_RUNNING) return;
+  if (!pass_runs(P.st + b, check)) return;
   dstx_inv_tile<T, L, WG>(P, mode, outp, b, blockIdx.x, reinterpret_cast<const cplx<T>*>(P.twx));
 }
 
@@ -67,7 +67,7 @@ k_dstx_inv(DevPlan P, int mode, double* __restrict__ outp) {
 template <typename T, int L, int WG>
 __global__ void __launch_bounds__(WG)
 k_dst2_fwd(DevPlan P, int mode, int check, const double* __restrict__ in) {
-  if ((check || mode == FWD_LANCZOS) && P.st[blockIdx.y].state != ST_RUNNING) return;
+  if (!pass_runs(P.st + blockIdx.y, check)) return;
   dst2_fwd_tile<T, L, WG>(P, mode, in, blockIdx.y, blockIdx.x);
 }
 
@@ -75,9 +75,9 @@ k_dst2_fwd(DevPlan P, int mode, int check, const double* __restrict__ in) {
 // Modes as in k_dstx_inv.
 template <typename T, int L, int WG>
 __global__ void __launch_bounds__(WG)
-k_dst2_inv(DevPlan P, int mode, double* __restrict__ outp) {
+k_dst2_inv(DevPlan P, int mode, int check, double* __restrict__ outp) {
   const int b = blockIdx.y;
-  if (mode != INV_PLAIN && P.st[b].state != ST_RUNNING) return;
+  if (!pass_runs(P.st + b, check)) return;
   dst2_inv_tile<T, L, WG>(P, mode, outp, b, blockIdx.x);
 }
 
@@ -99,7 +99,7 @@ hipError_t launch_x_fwd_t(const DevPlan& P, int mode, int check, const double* i
 }
 
 template <typename T, int L, int WG>
-hipError_t launch_x_inv_t(const DevPlan& P, int mode, double* out, hipStream_t s) {
+hipError_t launch_x_inv_t(const DevPlan& P, int mode, int check, double* out, hipStream_t s) {
   if constexpr (!tile_ok<T, L, WG, TK_XINV>()) {
     return hipErrorInvalidValue;
   } else {
@@ -107,7 +107,7 @@ hipError_t launch_x_inv_t(const DevPlan& P, int mode, double* out, hipStream_t s
     const int rows = P.nt * P.ny1;
     dim3 grid((rows + 2 * S - 1) / (2 * S), P.B);
     const size_t lds = lds_of<T, L, WG, TK_XINV>();
-    hipLaunchKernelGGL((k_dstx_inv<T, L, WG>), grid, dim3(WG), lds, s, P, mode, out);
+    hipLaunchKernelGGL((k_dstx_inv<T, L, WG>), grid, dim3(WG), lds, s, P, mode, check, out);
     return hipGetLastError();
   }
 }
@@ -152,7 +152,7 @@ hipError_t launch_slab_t(const DevPlan& P, bool fwd, int mode, int check, const 
     if (fwd)
       hipLaunchKernelGGL((k_dst2_fwd<T, L, WG>), grid, dim3(WG), lds, s, P, mode, check, in);
     else
-      hipLaunchKernelGGL((k_dst2_inv<T, L, WG>), grid, dim3(WG), lds, s, P, mode, out);
+      hipLaunchKernelGGL((k_dst2_inv<T, L, WG>), grid, dim3(WG), lds, s, P, mode, check, out);
     return hipGetLastError();
   }
 }
@@ -217,8 +217,8 @@ hipError_t x_fwd_dispatch(const DevPlan& P, int mode, int check, const double* i
 }
 
 template <typename T>
-hipError_t x_inv_dispatch(const DevPlan& P, int mode, double* out, hipStream_t s) {
-#define CALL(LL, WW) launch_x_inv_t<T, LL, WW>(P, mode, out, s)
+hipError_t x_inv_dispatch(const DevPlan& P, int mode, int check, double* out, hipStream_t s) {
+#define CALL(LL, WW) launch_x_inv_t<T, LL, WW>(P, mode, check, out, s)
   ABAC_SWITCH_L(2 * P.Mx, P.wg_xi, CALL)
 #undef CALL
 }
@@ -283,8 +283,8 @@ hipError_t launch_time(const DevPlan& P, int prec, int check, hipStream_t s, int
   return prec ? time_dispatch<float>(P, check, inv1, s) : time_dispatch<double>(P, check, inv1, s);
 }
 
-hipError_t launch_dstx_inv(const DevPlan& P, int prec, int mode, double* out, hipStream_t s) {
-  return prec ? x_inv_dispatch<float>(P, mode, out, s) : x_inv_dispatch<double>(P, mode, out, s);
+hipError_t launch_dstx_inv(const DevPlan& P, int prec, int mode, int check, double* out, hipStream_t s) {
+  return prec ? x_inv_dispatch<float>(P, mode, check, out, s) : x_inv_dispatch<double>(P, mode, check, out, s);
 }
 
 hipError_t launch_dst2_fwd(const DevPlan& P, int prec, int mode, int check, const double* in, hipStream_t s) {
@@ -292,9 +292,9 @@ hipError_t launch_dst2_fwd(const DevPlan& P, int prec, int mode, int check, cons
               : slab_dispatch<double>(P, true, mode, check, in, nullptr, s);
 }
 
-hipError_t launch_dst2_inv(const DevPlan& P, int prec, int mode, double* out, hipStream_t s) {
-  return prec ? slab_dispatch<float>(P, false, mode, 0, nullptr, out, s)
-              : slab_dispatch<double>(P, false, mode, 0, nullptr, out, s);
+hipError_t launch_dst2_inv(const DevPlan& P, int prec, int mode, int check, double* out, hipStream_t s) {
+  return prec ? slab_dispatch<float>(P, false, mode, check, nullptr, out, s)
+              : slab_dispatch<double>(P, false, mode, check, nullptr, out, s);
 }
 
 // Workgroup of the fused 2D passes for this shape, or 0 where they do not apply (1D,

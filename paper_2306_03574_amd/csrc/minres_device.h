@@ -177,6 +177,7 @@ __device__ void step_gamma_iter(MinresState* st, MinresExt* x, double g2, const 
     st->need_check = 0;
     st->form_now = st->basis_dirty;   // u gets the last iterate
     st->flush_now = 0;
+    st->hold = st->form_now;
     return;
   }
   const double c = t2 / rho, s = gn / rho;
@@ -215,25 +216,51 @@ __device__ void step_gamma_iter(MinresState* st, MinresExt* x, double g2, const 
   st->want_r = need && !identity && !st->track && !st->explicit_mode && hi > thr && !(hi < 1.25 * lo);
   st->flush_now = st->nbasis == kBasis;
   st->form_now = need || st->flush_now;
+  st->hold = st->tail = st->form_now;
 }
 
-// Copy the state of right-hand side b into the next slot of the host-mapped ring
-// (zero-copy: the host reads it after an event recorded behind this kernel).
+// Write the next snapshot of right-hand side b to the host-mapped ring (by one thread).
+// Every store goes past the caches (system scope), and the word that names the snapshot
+// is stored once the others have been acknowledged.  A system-scope fence would also
+// write the whole L2 back.
 __device__ __forceinline__ void post_snapshot(const DevPlan& P, int b) {
   MinresState* st = P.st + b;
   const int seq = st->snap;
-  if (P.host_ring) P.host_ring[(size_t)(seq % kSnapRing) * P.B + b] = *st;
   st->snap = seq + 1;
+  if (!P.host_ring) return;
+  Snapshot* s = P.host_ring + (size_t)(seq % kSnapRing) * P.B + b;
+#define ABAC_PUT(field, value) __hip_atomic_store(&s->field, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)
+  ABAC_PUT(status, st->status);
+  ABAC_PUT(iter, st->iter);
+  ABAC_PUT(rnorm2, st->rnorm2);
+  ABAC_PUT(bnorm2, st->bnorm2);
+  ABAC_PUT(res2, st->res2);
+  ABAC_PUT(tol2, st->tol2);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  ABAC_PUT(word, snap_word(st->epoch, seq, st->state, st->hold));
+#undef ABAC_PUT
 }
 
 // First half of a scalar step of right-hand side b: the flag updates of the step kind
 // (by thread 0 of the calling workgroup) and whether the step folds a sum into the
-// state.  A skipped step that ends an iteration still posts the snapshot.  Every
-// thread returns the same answer.
-__device__ __forceinline__ bool fin_begin(const DevPlan& P, int b, int kind) {
+// state.  A skipped step that posts a snapshot still does.  Every thread returns the same
+// answer.
+__device__ __forceinline__ bool fin_posts(int kind, const FinArgs& a) {
+  return kind == FIN_GAMMA_INIT || kind == FIN_RES || (kind == FIN_GAMMA_ITER && a.post);
+}
+
+__device__ __forceinline__ bool fin_begin(const DevPlan& P, int b, int kind, const FinArgs& a) {
   MinresState* st = P.st + b;
-  const bool posts = kind == FIN_GAMMA_INIT || kind == FIN_RES;   // end of set-up / of an iteration
-  if ((kind == FIN_RES || kind == FIN_REPORT) && threadIdx.x == 0 && st->form_now) form_done(st, minres_ext(P, b));
+  const bool posts = fin_posts(kind, a);
+  if (kind == FIN_RES || kind == FIN_REPORT) {
+    if (threadIdx.x == 0) {
+      if (st->form_now) form_done(st, minres_ext(P, b));
+      st->hold = 0;
+    }
+  } else if ((kind == FIN_DELTA || kind == FIN_GAMMA_ITER) && st->hold) {
+    if (posts && threadIdx.x == 0) post_snapshot(P, b);
+    return false;
+  }
   if (kind == FIN_FINAL) {
     // the end of a solve with a stale u forms it from the basis
     if (threadIdx.x == 0) {
@@ -287,14 +314,16 @@ __device__ __forceinline__ Dots3 sum_dots(const DevPlan& P, int b, int n) {
 // Second half, thread 0 only: fold the sum `tot` (and for FIN_GAMMA_ITER the inner
 // products of the first transform pass) into the state of right-hand side b (Givens QR,
 // stopping test, ...) and post the snapshot at the end of an iteration.
-__device__ void fin_scalar(const DevPlan& P, int b, int kind, double tot, const Dots3& dots, double tol, int maxit) {
+__device__ void fin_scalar(const DevPlan& P, int b, int kind, double tot, const Dots3& dots, const FinArgs& a) {
   MinresState* st = P.st + b;
-  const bool posts = kind == FIN_GAMMA_INIT || kind == FIN_RES;
   switch (kind) {
     case FIN_BNORM:
       st->bnorm2 = tot;
-      st->tol2 = tol * tol;
-      st->maxit = maxit;
+      st->tol2 = a.tol * a.tol;
+      st->maxit = a.maxit;
+      st->epoch = a.epoch;
+      st->hold = 0;
+      st->tail = 0;
       st->iter = 0;
       st->explicit_mode = 0;
       st->need_check = 0;
@@ -380,7 +409,7 @@ __device__ void fin_scalar(const DevPlan& P, int b, int kind, double tot, const 
       st->res2 = tot;
       break;
   }
-  if (posts) post_snapshot(P, b);
+  if (fin_posts(kind, a)) post_snapshot(P, b);
 }
 
 }  // namespace

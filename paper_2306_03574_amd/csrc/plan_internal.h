@@ -11,6 +11,7 @@
 
 using abac::DevPlan;
 using abac::MinresState;
+using abac::Snapshot;
 using abac::kSnapRing;
 
 struct ProfPair {
@@ -32,18 +33,12 @@ struct abac_plan {
   double* coef_ws;
   double abar;
   // asynchronous solve bookkeeping
-  MinresState* h_ring;   // host-mapped pinned memory, kSnapRing * B states written by the device
-  hipEvent_t ring_ev[kSnapRing];
+  Snapshot* h_ring;      // host-mapped pinned memory, kSnapRing * B snapshots written by the device
+  int epoch;              // number of the current solve
   long long ring_posted;  // snapshots enqueued in the current solve (= device sequence number)
   const double* f;
   double* u;
   bool active;
-  // one MINRES iteration captured as a graph (launched on the plan stream)
-  bool use_graph;
-  hipStream_t cap_stream;
-  hipGraphExec_t iter_graph;
-  const double* graph_f;
-  double* graph_u;
   // kernel timing
   bool prof;
   std::vector<ProfPair> pending;
@@ -53,11 +48,9 @@ struct abac_plan {
 };
 
 namespace abac {
-// Non-blocking: if snapshot `seq` of the current solve has been written, set *ready
-// and return a pointer to its per-RHS states (host memory); otherwise *ready = 0.
-abac_status plan_peek_snapshot(abac_plan* p, long long seq, int* ready, const MinresState** states);
-// Number of snapshots enqueued in the current solve (the set-up one is number 0).
-long long plan_snapshots_posted(const abac_plan* p);
+// Non-blocking: whether snapshot `seq` of the current solve has been written for every
+// right-hand side; if so *snaps points to them (host memory).
+bool plan_peek_snapshot(const abac_plan* p, long long seq, const Snapshot** snaps);
 hipError_t launch_fill_normal(double* out, unsigned long long n, unsigned long long seed, hipStream_t s);
 hipError_t launch_fill_zero(double* out, unsigned long long n, hipStream_t s);
 // the thread-local message abac_last_error() returns

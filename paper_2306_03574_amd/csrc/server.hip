@@ -279,11 +279,10 @@ bool advance(abac_server* s, Req* r) {
   abac_plan* p = r->slot->plan;
   // observe every snapshot that has completed since the last look
   while (r->obs < r->enq) {
-    int ready = 0;
-    const MinresState* snap = nullptr;
-    if (abac::plan_peek_snapshot(p, r->obs + 1, &ready, &snap) != ABAC_OK || !ready) break;
+    const Snapshot* snap = nullptr;
+    if (!abac::plan_peek_snapshot(p, r->obs + 1, &snap)) break;
     ++r->obs;
-    if (snap[0].state != abac::ST_RUNNING) {
+    if (abac::snap_state(snap[0].word) != abac::ST_RUNNING) {
       int it = 0, stt = 0;
       double rr = 0;
       abac_minres_finish(p, &it, &rr, &stt);
@@ -304,9 +303,8 @@ bool advance(abac_server* s, Req* r) {
   }
   if (r->obs == 0 && r->enq == 0) {
     // the set-up snapshot (number 0) may already report a stopped solve (zero source)
-    int ready = 0;
-    const MinresState* snap = nullptr;
-    if (abac::plan_peek_snapshot(p, 0, &ready, &snap) == ABAC_OK && ready && snap[0].state != abac::ST_RUNNING) {
+    const Snapshot* snap = nullptr;
+    if (abac::plan_peek_snapshot(p, 0, &snap) && abac::snap_state(snap[0].word) != abac::ST_RUNNING) {
       int it = 0, stt = 0;
       double rr = 0;
       abac_minres_finish(p, &it, &rr, &stt);

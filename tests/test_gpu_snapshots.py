@@ -1,0 +1,64 @@
+"""Snapshots of a solve in host-mapped memory: a plan whose earlier solve is abandoned with
+its iterations still queued must not take that solve's snapshots for the new one's, and a
+ring of 16 snapshots must serve solves of any length."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+# separate kernels, fused x-y passes, one workgroup per right-hand side
+GRIDS = [(127, 0, 64), (31, 31, 32), (31, 0, 32)]
+
+
+def _rhs(p, seed):
+    src = np.stack([synth.random_source(p.nx, p.ny, p.nt, seed=seed + b)[0] for b in range(p.batch)])
+    zero = torch.zeros((p.batch,) + p.level_shape, dtype=torch.float64, device=DEV)
+    return p.build_rhs(torch.from_numpy(src).to(DEV), zero, zero)
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+@pytest.mark.parametrize("nx,ny,nt", GRIDS)
+def test_abandoned_solve(nx, ny, nt, batch):
+    from paper_2306_03574_amd import Plan
+    print(f"[case] abandoned solve nx={nx} ny={ny} nt={nt} batch={batch}", flush=True)
+    p = Plan(nx, ny, nt, alpha=1e-2, batch=batch, device=DEV)
+    f1, f2 = _rhs(p, 3), _rhs(p, 40)
+    want, iters, relres, status = p.solve(f2, tol=1e-8, maxit=100)
+    want = want.clone()
+    u1, u2 = p.empty(), p.empty()
+    p.begin(f1, u1, tol=1e-2, maxit=100)   # stops early: its snapshots say "done"
+    p.advance(20)                          # more than the ring holds
+    p.begin(f2, u2, tol=1e-8, maxit=100)   # at once, with those still queued
+    steps = 0
+    while not p.poll():
+        p.advance(1)
+        steps += 1
+        assert steps < 200
+        torch.cuda.synchronize()
+    got = p.finish()
+    assert got == (iters, relres, status)
+    torch.cuda.synchronize()
+    assert torch.equal(u2, want)
+    assert steps <= max(iters) + 1
+
+
+@pytest.mark.parametrize("nx,ny,nt", GRIDS)
+def test_more_iterations_than_the_ring_holds(nx, ny, nt):
+    """40 iterations of an unreachable tolerance, solved at once and enqueued ahead."""
+    from paper_2306_03574_amd import Plan
+    print(f"[case] long solve nx={nx} ny={ny} nt={nt}", flush=True)
+    p = Plan(nx, ny, nt, alpha=1e-2, device=DEV)
+    f = _rhs(p, 5)
+    u1, it1, rr1, st1 = p.solve(f, tol=1e-30, maxit=40)
+    u1 = u1.clone()
+    u2 = p.empty()
+    p.begin(f, u2, tol=1e-30, maxit=40)
+    p.advance(40)
+    it2, rr2, st2 = p.finish()
+    torch.cuda.synchronize()
+    assert it1 == it2 and rr1 == rr2 and st1 == st2
+    assert torch.equal(u1, u2)
