@@ -260,16 +260,29 @@ __device__ __forceinline__ double block_sum(double v) {
 
 // Fixed-order sum of n partials by the whole block (pairs per thread, then the block
 // tree); result valid in thread 0.  `part` is 16-byte aligned.
-__device__ __forceinline__ double sum_parts(const double* __restrict__ part, int n) {
-  double s = 0.0;
+//
+// A thread's share of that sum, for thread t of a block of nt threads.  Its loads go out in
+// batches before any is added: one load at a time costs an L2 trip each (255^2 x 256:
+// 32 k partials over 1024 threads and three sums of 16 k, the Givens step 24 -> 16 us).
+__device__ __forceinline__ double parts_share(const double* __restrict__ part, int n, int t, int nt) {
+  constexpr int BATCH = 8;
   const double2* p2 = reinterpret_cast<const double2*>(part);
   const int n2 = n >> 1;
-  for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-    const double2 v = p2[i];
-    s += v.x + v.y;
+  double s = 0.0;
+  for (int i0 = t; i0 < n2; i0 += BATCH * nt) {
+    double2 v[BATCH];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) v[u] = p2[min(i0 + u * nt, n2 - 1)];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u)
+      if (i0 + u * nt < n2) s += v[u].x + v[u].y;
   }
-  if ((n & 1) && threadIdx.x == 0) s += part[n - 1];
-  return block_sum(s);
+  if ((n & 1) && t == 0) s += part[n - 1];
+  return s;
+}
+
+__device__ __forceinline__ double sum_parts(const double* __restrict__ part, int n) {
+  return block_sum(parts_share(part, n, threadIdx.x, blockDim.x));
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs; remap the hardware block

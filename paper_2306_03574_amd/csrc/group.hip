@@ -124,15 +124,9 @@ __device__ __forceinline__ void group_stencil(const GroupTable* __restrict__ G, 
 // addition and its order are the V-thread block's.  Result valid in thread 0.
 __device__ __forceinline__ double sum_parts_as(const double* __restrict__ part, int n, int V) {
   __shared__ double wsum[16];
-  const double2* p2 = reinterpret_cast<const double2*>(part);
-  const int n2 = n >> 1, lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63;
   for (int vt = threadIdx.x; vt < V; vt += blockDim.x) {
-    double s = 0.0;
-    for (int i = vt; i < n2; i += V) {
-      const double2 v = p2[i];
-      s += v.x + v.y;
-    }
-    if ((n & 1) && vt == 0) s += part[n - 1];
+    double s = parts_share(part, n, vt, V);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
     if (lane == 0) wsum[vt >> 6] = s;
@@ -148,7 +142,6 @@ __device__ __forceinline__ double sum_parts_as(const double* __restrict__ part, 
 __device__ __forceinline__ void group_fin(const GroupTable* __restrict__ G, int w, int kind) {
   const Where at = locate(G, GS_FIN, w);
   const DevPlan& P = G->m[at.r].P;
-  if (!fin_begin(P, at.b, kind, FinArgs{})) return;
   int nparts;
   switch (kind) {
     case FIN_DELTA: nparts = stencil_blocks(P); break;
@@ -156,10 +149,10 @@ __device__ __forceinline__ void group_fin(const GroupTable* __restrict__ G, int 
     case FIN_GAMMA_ITER: nparts = P.gamma_nparts; break;
     default: nparts = stencil_blocks(P); break;
   }
-  Dots3 dots{0.0, 0.0, 0.0};
-  if (kind == FIN_GAMMA_ITER) dots = sum_dots(P, at.b, (G->off[GS_XFWD][at.r + 1] - G->off[GS_XFWD][at.r]) / P.B);
-  const double tot = sum_parts_as(part_slot(P, fin_part_kind(kind), at.b), nparts, kGroupFinThreads);
-  if (threadIdx.x == 0) fin_scalar(P, at.b, kind, tot, dots, FinArgs{});
+  fin_step(P, at.b, kind, FinArgs{}, [&](Dots3* dots) {
+    if (kind == FIN_GAMMA_ITER) *dots = sum_dots(P, at.b, (G->off[GS_XFWD][at.r + 1] - G->off[GS_XFWD][at.r]) / P.B);
+    return sum_parts_as(part_slot(P, fin_part_kind(kind), at.b), nparts, kGroupFinThreads);
+  });
 }
 
 // ---- vector step: iterate from the basis --------------------------------------------

@@ -115,7 +115,7 @@ __device__ __noinline__ void iter_small(const DevPlan& P, const double* __restri
     const int j = st->iter + 1;
     const double acc = stencil_small<OUT_REV, true>(P, P.Z[zslot(j)] + off, P.V[(j + 1) % 3] + off, nullptr);
     const double tot = block_sum(acc);
-    if (fin_begin(P, b, FIN_DELTA, FinArgs{}) && tid == 0) fin_scalar(P, b, FIN_DELTA, tot, Dots3{}, FinArgs{});
+    if (fin_begin(P, b, st, minres_ext(P, b), FIN_DELTA, FinArgs{}) && tid == 0) fin_scalar(P, b, st, minres_ext(P, b), FIN_DELTA, tot, Dots3{}, FinArgs{});
     __syncthreads();
   }
   // Lanczos vector and the first half of z_{j+1} = P^{-1} q: x-DST (Lanczos fused), time
@@ -135,7 +135,7 @@ __device__ __noinline__ void iter_small(const DevPlan& P, const double* __restri
     }
     const Dots3 dots = sum_dots(P, b, xtiles);
     const double tot = sum_parts(part_slot(P, PART_GAMMA, b), P.ms / 2);
-    if (fin_begin(P, b, FIN_GAMMA_ITER, FinArgs{}) && tid == 0) fin_scalar(P, b, FIN_GAMMA_ITER, tot, dots, FinArgs{});
+    if (fin_begin(P, b, st, minres_ext(P, b), FIN_GAMMA_ITER, FinArgs{}) && tid == 0) fin_scalar(P, b, st, minres_ext(P, b), FIN_GAMMA_ITER, tot, dots, FinArgs{});
     __syncthreads();
   }
   // the iterate from the resident basis when a check, a stop or the flush needs it
@@ -149,7 +149,7 @@ __device__ __noinline__ void iter_small(const DevPlan& P, const double* __restri
     if (st->state == ST_RUNNING && st->need_check)
       tot = block_sum(st->want_r ? stencil_small<OUT_RESREV, false>(P, u + off, P.R + off, f + off)
                                  : stencil_small<OUT_RESNORM, false>(P, u + off, nullptr, f + off));
-    if (fin_begin(P, b, FIN_RES, FinArgs{}) && tid == 0) fin_scalar(P, b, FIN_RES, tot, Dots3{}, FinArgs{});
+    if (fin_begin(P, b, st, minres_ext(P, b), FIN_RES, FinArgs{}) && tid == 0) fin_scalar(P, b, st, minres_ext(P, b), FIN_RES, tot, Dots3{}, FinArgs{});
     __syncthreads();
   }
   // the second half of z_{j+1}: inverse x-DST
@@ -189,7 +189,7 @@ __device__ __noinline__ void setup_small(const DevPlan& P, const double* __restr
       acc += v * v;
     }
     const double tot = block_sum(acc);
-    if (fin_begin(P, b, FIN_BNORM, a) && tid == 0) fin_scalar(P, b, FIN_BNORM, tot, Dots3{}, a);
+    if (fin_begin(P, b, st, minres_ext(P, b), FIN_BNORM, a) && tid == 0) fin_scalar(P, b, st, minres_ext(P, b), FIN_BNORM, tot, Dots3{}, a);
     __syncthreads();
   }
   double tot = 0.0;
@@ -211,7 +211,7 @@ __device__ __noinline__ void setup_small(const DevPlan& P, const double* __restr
       __syncthreads();
     }
   }
-  if (fin_begin(P, b, FIN_GAMMA_INIT, a) && tid == 0) fin_scalar(P, b, FIN_GAMMA_INIT, tot, Dots3{}, a);
+  if (fin_begin(P, b, st, minres_ext(P, b), FIN_GAMMA_INIT, a) && tid == 0) fin_scalar(P, b, st, minres_ext(P, b), FIN_GAMMA_INIT, tot, Dots3{}, a);
 }
 
 template <typename T, int L, int NT>
@@ -245,7 +245,7 @@ k_solve_small(DevPlan P, const double* __restrict__ f, double* __restrict__ u, F
   if (threadIdx.x == 0) {
     st_lds.snap = 0;
     P.st[b] = st_lds;
-    post_snapshot(P, b);
+    post_snapshot(P, b, &st_lds);
   }
 }
 

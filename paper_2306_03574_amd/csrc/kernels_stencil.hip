@@ -163,11 +163,10 @@ constexpr int kFinThreads = 1024;
 __global__ void __launch_bounds__(kFinThreads)
 k_fin(DevPlan P, int kind, int nparts, int ndots, FinArgs a) {
   const int b = blockIdx.x;
-  if (!fin_begin(P, b, kind, a)) return;
-  Dots3 dots{0.0, 0.0, 0.0};
-  if (kind == FIN_GAMMA_ITER) dots = sum_dots(P, b, ndots);
-  const double tot = sum_parts(part_slot(P, fin_part_kind(kind), b), nparts);
-  if (threadIdx.x == 0) fin_scalar(P, b, kind, tot, dots, a);
+  fin_step(P, b, kind, a, [&](Dots3* dots) {
+    if (kind == FIN_GAMMA_ITER) *dots = sum_dots(P, b, ndots);
+    return sum_parts(part_slot(P, fin_part_kind(kind), b), nparts);
+  });
 }
 
 }  // namespace
