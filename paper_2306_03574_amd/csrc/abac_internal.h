@@ -109,6 +109,8 @@ struct MinresExt {
   double n0, n1, d01;       // ||V_j||^2, ||V_{j+1}||^2, <V_j, V_{j+1}> of the last step
   double hi[3];             // upper bounds on ||r_j||, ||r_{j-1}||, ||r_{j-2}||
   double r1p[2];            // r1 of the last two steps
+  double wa, wb, wc, xc;    // w_j = wa z_j - wb w_{j-1} - wc w_{j-2}; x_j = x_{j-1} + xc w_j
+  double step;              // 1: the coefficients kc wait for that step
 };
 
 // vector kernels: 256 threads, about 16 elements per thread, at most 1024 blocks per
@@ -360,7 +362,7 @@ hipError_t launch_form(const DevPlan& P, double* u, hipStream_t s);
 struct FinArgs {
   double tol = 0.0;            // FIN_BNORM
   int maxit = 0, epoch = 0;
-  int post = 0;                // FIN_GAMMA_ITER: post a snapshot (the set-up and FIN_RES always do)
+  int post = 0;                // 1: FIN_GAMMA_ITER posts a snapshot, as the set-up and FIN_RES do; -1: none does
 };
 hipError_t launch_fin(const DevPlan& P, int kind, const FinArgs& a, hipStream_t s);
 

@@ -11,6 +11,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace abac {
 
 template <typename T> struct cplx_of;
@@ -184,77 +186,70 @@ __device__ __forceinline__ int stockham_dst(int b, int Ns, int i) {
 // between its last LDS reads and this call); on return other threads may still be
 // reading it, so the caller must barrier before writing it again.  With FROM_LDS the
 // input is read from lds[e*S] in natural order instead (the caller barriers after
-// writing it).
+// writing it).  Threads that hold no sequence pass act = false: they only take the
+// barriers.
 template <typename T, int L, bool INV, bool FROM_LDS = false>
-__device__ __forceinline__ void fft_seq(cplx<T>* v, int j, cplx<T>* lds, int S, const cplx<T>* __restrict__ tw) {
+__device__ __forceinline__ void fft_seq(cplx<T>* v, int j, cplx<T>* lds, int S, const cplx<T>* __restrict__ tw,
+                                        bool act = true) {
   using C = cplx<T>;
   using Sh = FftShape<T, L>;
   constexpr int R = Sh::R;
   constexpr int TPS = L / R;
   if constexpr (FROM_LDS) {
     // input in natural order in LDS (written and fenced by the caller)
+    if (act) {
 #pragma unroll
-    for (int i = 0; i < R; ++i) v[i] = lds[(j + i * TPS) * S];
+      for (int i = 0; i < R; ++i) v[i] = lds[(j + i * TPS) * S];
+    }
     __syncthreads();
   }
   // pass 0: radix R, Ns = 1
-  dftR<R, INV>(v);
+  if (act) dftR<R, INV>(v);
   if constexpr (Sh::passes == 1) {
     return;
   } else {
     int Ns = 1;
+    if (act) {
 #pragma unroll
-    for (int i = 0; i < R; ++i) lds[stockham_dst<C, L, R>(j, Ns, i) * S] = v[i];
+      for (int i = 0; i < R; ++i) lds[stockham_dst<C, L, R>(j, Ns, i) * S] = v[i];
+    }
     Ns *= R;
     __syncthreads();
     // middle passes
-    if constexpr (Sh::m1 != 0) {
-      constexpr int r = Sh::m1;
+    auto middle = [&](auto radix) {
+      constexpr int r = decltype(radix)::value;
       constexpr int NB = R / r;   // butterflies per thread
+      if (act) {
 #pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int b = u * TPS + j;
+        for (int u = 0; u < NB; ++u) {
+          const int b = u * TPS + j;
 #pragma unroll
-        for (int i = 0; i < r; ++i) v[u * r + i] = lds[(b + i * (L / r)) * S];
+          for (int i = 0; i < r; ++i) v[u * r + i] = lds[(b + i * (L / r)) * S];
+        }
       }
       __syncthreads();
+      if (act) {
 #pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int b = u * TPS + j;
-        stockham_twiddle<C, L, r, INV>(v + u * r, b, Ns, tw);
-        dftR<r, INV>(v + u * r);
+        for (int u = 0; u < NB; ++u) {
+          const int b = u * TPS + j;
+          stockham_twiddle<C, L, r, INV>(v + u * r, b, Ns, tw);
+          dftR<r, INV>(v + u * r);
 #pragma unroll
-        for (int i = 0; i < r; ++i) lds[stockham_dst<C, L, r>(b, Ns, i) * S] = v[u * r + i];
-      }
-      Ns *= r;
-      __syncthreads();
-    }
-    if constexpr (Sh::m2 != 0) {
-      constexpr int r = Sh::m2;
-      constexpr int NB = R / r;
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int b = u * TPS + j;
-#pragma unroll
-        for (int i = 0; i < r; ++i) v[u * r + i] = lds[(b + i * (L / r)) * S];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int b = u * TPS + j;
-        stockham_twiddle<C, L, r, INV>(v + u * r, b, Ns, tw);
-        dftR<r, INV>(v + u * r);
-#pragma unroll
-        for (int i = 0; i < r; ++i) lds[stockham_dst<C, L, r>(b, Ns, i) * S] = v[u * r + i];
+          for (int i = 0; i < r; ++i) lds[stockham_dst<C, L, r>(b, Ns, i) * S] = v[u * r + i];
+        }
       }
       Ns *= r;
       __syncthreads();
-    }
+    };
+    if constexpr (Sh::m1 != 0) middle(std::integral_constant<int, Sh::m1>{});
+    if constexpr (Sh::m2 != 0) middle(std::integral_constant<int, Sh::m2>{});
     // last pass: radix R, butterfly b = j, output lands at j + i*Ns with Ns = TPS
+    if (act) {
 #pragma unroll
-    for (int i = 0; i < R; ++i) v[i] = lds[(j + i * TPS) * S];
-    stockham_twiddle<C, L, R, INV>(v, j, Ns, tw);
-    dftR<R, INV>(v);
+      for (int i = 0; i < R; ++i) v[i] = lds[(j + i * TPS) * S];
+      stockham_twiddle<C, L, R, INV>(v, j, Ns, tw);
+      dftR<R, INV>(v);
+    }
   }
 }
 

@@ -160,8 +160,7 @@ __device__ __forceinline__ double residual_bounds(MinresState* st, MinresExt* x,
 
 // Lanczos coefficient gamma_{j+1}, the Givens QR update of iteration j, and the stopping
 // test on the bounds of ||r_j||: an explicit check where they do not exclude
-// convergence.  The w and x recurrences run on coefficient vectors over the basis
-// (kc: x, w_j, w_{j-1}).
+// convergence.  The step of the w and x recurrences is left to step_coefs.
 __device__ void step_gamma_iter(MinresState* st, MinresExt* x, double g2, const Dots3& dots, bool identity) {
   const double gn = sqrt(g2);
   const double gam = st->gamma, del = st->delta;
@@ -178,10 +177,15 @@ __device__ void step_gamma_iter(MinresState* st, MinresExt* x, double g2, const 
     st->form_now = st->basis_dirty;   // u gets the last iterate
     st->flush_now = 0;
     st->hold = st->form_now;
+    x->step = 0.0;
     return;
   }
   const double c = t2 / rho, s = gn / rho;
-  const double wa = st->sig / rho, wb = dp / rho, wc = eps / rho, xc = c * st->eta;
+  x->wa = st->sig / rho;
+  x->wb = dp / rho;
+  x->wc = eps / rho;
+  x->xc = c * st->eta;
+  x->step = 1.0;
   st->r1 = s * s;
   st->r2 = gn > 0.0 ? -s * c * st->eta / gn : 0.0;
   st->eta = -s * st->eta;
@@ -193,21 +197,8 @@ __device__ void step_gamma_iter(MinresState* st, MinresExt* x, double g2, const 
   st->iter += 1;
   if (gn == 0.0) st->lucky = 1;
   const int j = st->iter;
-  {
-    double* xm = x->kc;
-    double* m1 = x->kc + kCoefs;
-    double* m2 = x->kc + 2 * kCoefs;
-    const int nb = st->nbasis;
-#pragma unroll
-    for (int l = 0; l < kCoefs; ++l) {
-      const double w = (l == nb ? wa : 0.0) - wb * m1[l] - wc * m2[l];
-      m2[l] = m1[l];
-      m1[l] = w;
-      xm[l] += xc * w;
-    }
-    st->nbasis = nb + 1;
-    st->basis_dirty = 1;
-  }
+  st->nbasis += 1;
+  st->basis_dirty = 1;
   double lo, hi;
   st->rnorm2 = residual_bounds(st, x, dots, identity, &lo, &hi);
   const double thr = sqrt(st->tol2 * st->bnorm2);
@@ -218,6 +209,20 @@ __device__ void step_gamma_iter(MinresState* st, MinresExt* x, double g2, const 
   st->flush_now = st->nbasis == kBasis;
   st->form_now = need || st->flush_now;
   st->hold = st->tail = st->form_now;
+}
+
+// The w and x recurrences of the last Givens step on the coefficient vectors over the basis
+// (kc: x, w_j, w_{j-1}), a coefficient per thread (behind a barrier).
+__device__ __forceinline__ void step_coefs(const MinresState* st, MinresExt* x) {
+  const int l = threadIdx.x;
+  if (l >= kCoefs || x->step == 0.0) return;
+  double* xm = x->kc + l;
+  double* m1 = xm + kCoefs;
+  double* m2 = m1 + kCoefs;
+  const double w = (l == st->nbasis - 1 ? x->wa : 0.0) - x->wb * *m1 - x->wc * *m2;
+  *m2 = *m1;
+  *m1 = w;
+  *xm += x->xc * w;
 }
 
 // Write the next snapshot of right-hand side b to the host-mapped ring (by one thread).
@@ -247,7 +252,7 @@ __device__ __forceinline__ void post_snapshot(const DevPlan& P, int b, MinresSta
 // state.  A skipped step that posts a snapshot still does.  Every thread returns the same
 // answer.
 __device__ __forceinline__ bool fin_posts(int kind, const FinArgs& a) {
-  return kind == FIN_GAMMA_INIT || kind == FIN_RES || (kind == FIN_GAMMA_ITER && a.post);
+  return a.post >= 0 && (kind == FIN_GAMMA_INIT || kind == FIN_RES || (kind == FIN_GAMMA_ITER && a.post));
 }
 
 __device__ __forceinline__ bool fin_begin(const DevPlan& P, int b, MinresState* st, MinresExt* x, int kind,
@@ -440,6 +445,10 @@ __device__ __forceinline__ void fin_step(const DevPlan& P, int b, int kind, cons
     if (threadIdx.x == 0) fin_scalar(P, b, &s.st, &s.x, kind, tot, dots, a);
   }
   __syncthreads();
+  if (go && kind == FIN_GAMMA_ITER) {
+    step_coefs(&s.st, &s.x);
+    __syncthreads();
+  }
   move_state<false>(P, b, s);
 }
 

@@ -390,18 +390,18 @@ __device__ __forceinline__ C cmul_add_conj(C a, C b, C c, C d) {
 // the mirrored slots R-1-u of thread TPS-j, which travel through LDS at their natural
 // positions (published, updated by the owner, read back); thread 0 pairs its own
 // slots u and R-u.  The LDS region lds[e S] must be free on entry; on return other
-// threads may still be reading it.
+// threads may still be reading it.  act as for fft_seq.
 template <typename T, int NT>
 __device__ __forceinline__ void spectral_apply(cplx<T>* v, int j, cplx<T>* my, int S,
-                                               const SpectralWeights<T, NT>& W) {
+                                               const SpectralWeights<T, NT>& W, bool act = true) {
   using C = cplx<T>;
   constexpr int R = FftShape<T, NT>::R, TPS = NT / R, H = R / 2;
-  if (j != 0) {
+  if (act && j != 0) {
 #pragma unroll
     for (int i = H; i < R; ++i) my[(j + i * TPS) * S] = v[i];
   }
   __syncthreads();
-  if (j != 0) {
+  if (act && j != 0) {
 #pragma unroll
     for (int u = 0; u < H; ++u) {
       const int kp = NT - (j + u * TPS);
@@ -410,7 +410,7 @@ __device__ __forceinline__ void spectral_apply(cplx<T>* v, int j, cplx<T>* my, i
       v[u] = cmul_add_conj(sp, zk, sm, zp);
       my[kp * S] = cmul_add_conj(cconj(sp), zp, cconj(sm), zk);
     }
-  } else {
+  } else if (act) {
 #pragma unroll
     for (int u = 0; u <= H; ++u) {
       const int up = (R - u) & (R - 1);
@@ -422,10 +422,71 @@ __device__ __forceinline__ void spectral_apply(cplx<T>* v, int j, cplx<T>* my, i
     }
   }
   __syncthreads();
-  if (j != 0) {
+  if (act && j != 0) {
 #pragma unroll
     for (int i = H; i < R; ++i) v[i] = my[(j + i * TPS) * S];
   }
+}
+
+// K Y K Y of one mode pair held in registers (v: the pair's D-scaled input, as fft_seq lays
+// it out; on return w with out_t = a^{-t} w_{t+1}), or with inv1 the single K (out_t =
+// a^{-t} w_t).  tw, sc, sci: the tables in LDS.  gamma: also the pair's ||K Y g||^2, valid
+// in thread j = 0; red and red2 (one double per thread and per group of G threads of a
+// sequence) must be free after the first FFT's first barrier.
+template <typename T, int NT>
+__device__ __forceinline__ double time_core(cplx<T>* v, int j, int s, cplx<T>* my, int S, const cplx<T>* tw,
+                                            const T* sc, const T* sci, const SpectralWeights<T, NT>& W, int inv1,
+                                            int gamma, double* red, double* red2, bool act = true) {
+  constexpr int R = FftShape<T, NT>::R, TPS = NT / R, G = TPS >= 8 ? 8 : TPS;
+  // first (or only) factor: FFT, weights, inverse FFT
+  fft_seq<T, NT, false>(v, j, my, S, tw, act);
+  __syncthreads();
+  spectral_apply<T, NT>(v, j, my, S, W, act);
+  __syncthreads();
+  fft_seq<T, NT, true>(v, j, my, S, tw, act);
+  double gsum = 0.0;
+  if (gamma && act) {
+    // this thread's part (K's output is a^{-t} v_t), published for the group sums below
+    double a = 0.0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const double sv = (double)sci[j + i * TPS];
+      a += sv * sv * ((double)v[i].x * v[i].x + (double)v[i].y * v[i].y);
+    }
+    red[j * S + s] = a;
+  }
+  if (!inv1) {
+    // D^{-1}, Y, D between the factors, y_t = a^{2t-nt+1} c_{nt-1-t}, without moving data:
+    // with g_s = y_{nt-1-s} (an elementwise scaling of c), the DFT of y at frequency k is
+    // e^{2 pi i k/nt} G_k, G the inverse-direction DFT of g.  The weights act on G as on
+    // the DFT of y (the phase at -k is the conjugate of the one at k), and the phase left
+    // on the spectrum shifts the inverse DFT by one level: out_t = w_{t+1}.
+    if (act) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const int t = j + i * TPS;
+        v[i] = cscale(v[i], sc[NT - 1 - t] * sci[t]);
+      }
+    }
+    __syncthreads();
+    if (gamma && act && j < TPS / G) {
+      // groups of G consecutive threads of a sequence (red is visible after the barrier
+      // above; red2 after the barriers inside the FFT below)
+      double a = 0.0;
+#pragma unroll
+      for (int q = 0; q < G; ++q) a += red[(j * G + q) * S + s];
+      red2[j * S + s] = a;
+    }
+    fft_seq<T, NT, true>(v, j, my, S, tw, act);
+    __syncthreads();
+    if (gamma && act && j == 0) {
+      for (int q = 0; q < TPS / G; ++q) gsum += red2[q * S + s];
+    }
+    spectral_apply<T, NT>(v, j, my, S, W, act);
+    __syncthreads();
+    fft_seq<T, NT, true>(v, j, my, S, tw, act);
+  }
+  return gsum;
 }
 
 // inv1 = 0: out = K Y K Y g with mu^{-1/2} (the ABAC P^{-1}); inv1 = 1: out = K g with
@@ -485,57 +546,11 @@ __device__ __forceinline__ void time_tile(const DevPlan& P, int inv1, int b, int
   stage_table(sc, reinterpret_cast<const T*>(P.sc), NT);
   stage_table(sci, reinterpret_cast<const T*>(P.sci), NT);
   __syncthreads();
-  const C* tw = tws;
 #pragma unroll
   for (int i = 0; i < R; ++i) v[i] = cscale(v[i], sc[j + i * TPS]);
   SpectralWeights<T, NT> W;
   spectral_weights<T, NT>(W, j, abk, ba, bb, (T)(0.5 / NT), inv1);
-  // first (or only) factor: FFT, weights, inverse FFT
-  fft_seq<T, NT, false>(v, j, my, S, tw);
-  __syncthreads();
-  spectral_apply<T, NT>(v, j, my, S, W);
-  __syncthreads();
-  fft_seq<T, NT, true>(v, j, my, S, tw);
-  double gsum = 0.0;   // with gamma: the pair's ||K Y g||^2, valid in thread j = 0
-  if (gamma) {
-    // this thread's part (K's output is a^{-t} v_t), published for the group sums below
-    double a = 0.0;
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const double sv = (double)sci[j + i * TPS];
-      a += sv * sv * ((double)v[i].x * v[i].x + (double)v[i].y * v[i].y);
-    }
-    red[j * S + s] = a;
-  }
-  if (!inv1) {
-    // D^{-1}, Y, D between the factors, y_t = a^{2t-nt+1} c_{nt-1-t}, without moving data:
-    // with g_s = y_{nt-1-s} (an elementwise scaling of c), the DFT of y at frequency k is
-    // e^{2 pi i k/nt} G_k, G the inverse-direction DFT of g.  The weights act on G as on
-    // the DFT of y (the phase at -k is the conjugate of the one at k), and the phase left
-    // on the spectrum shifts the inverse DFT by one level: out_t = w_{t+1}.
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int t = j + i * TPS;
-      v[i] = cscale(v[i], sc[NT - 1 - t] * sci[t]);
-    }
-    __syncthreads();
-    if (gamma && j < TPS / G) {
-      // groups of G consecutive threads of a sequence (red is visible after the barrier
-      // above; red2 after the barriers inside the FFT below)
-      double a = 0.0;
-#pragma unroll
-      for (int q = 0; q < G; ++q) a += red[(j * G + q) * S + s];
-      red2[j * S + s] = a;
-    }
-    fft_seq<T, NT, true>(v, j, my, S, tw);
-    __syncthreads();
-    if (gamma && j == 0) {
-      for (int q = 0; q < TPS / G; ++q) gsum += red2[q * S + s];
-    }
-    spectral_apply<T, NT>(v, j, my, S, W);
-    __syncthreads();
-    fft_seq<T, NT, true>(v, j, my, S, tw);
-  }
+  const double gsum = time_core<T, NT>(v, j, s, my, S, tws, sc, sci, W, inv1, gamma, red, red2);
   const int shift = inv1 ? 0 : 1;
   if (valid) {
 #pragma unroll
