@@ -172,79 +172,109 @@ __device__ __forceinline__ void group_form(const GroupTable* __restrict__ G, int
 #define ABAC_GROUP_SLAB_LENGTHS(CASE) CASE(16) CASE(32) CASE(64) CASE(128) CASE(256)
 #define ABAC_GROUP_T_LENGTHS(CASE) CASE(8) CASE(16) CASE(32) CASE(64) CASE(128) CASE(256) CASE(512) CASE(1024)
 
+// One tile of a transform pass of one length.  FAR: out of line, for the persistent kernel,
+// so that each tile gets the registers of its own.  One function per length, not one
+// for a pass with all its lengths: past 128 KB of code the compiler reaches a function's end
+// by a long branch through s[30:31], which hold the return address of a function that calls
+// nothing, and the function then never returns.
+template <typename T, int LL>
+__device__ __forceinline__ void tile_slab_fwd(const DevPlan& P, int b, int lbk) {
+  if constexpr (slab_ok<T, LL, kGroupWG>()) dst2_fwd_tile<T, LL, kGroupWG>(P, FWD_LANCZOS, nullptr, b, lbk);
+}
+template <typename T, int LL>
+__device__ __forceinline__ void tile_xfwd(const DevPlan& P, int b, int lbk) {
+  if constexpr (tile_ok<T, LL, kGroupWG, TK_XFWD>())
+    dstx_fwd_tile<T, LL, kGroupWG>(P, FWD_LANCZOS, nullptr, b, lbk, reinterpret_cast<const cplx<T>*>(P.twx));
+}
+template <typename T, int LL>
+__device__ __forceinline__ void tile_y(const DevPlan& P, int b, int lbk) {
+  if constexpr (tile_ok<T, LL, kGroupWG, TK_Y>()) dsty_tile<T, LL, kGroupWG>(P, b, lbk);
+}
+template <typename T, int LL>
+__device__ __forceinline__ void tile_time(const DevPlan& P, int b, int lbk) {
+  if constexpr (tile_ok<T, LL, kGroupWG, TK_TIME>()) time_tile<T, LL, kGroupWG>(P, 0, b, lbk, 1);
+}
+template <typename T, int LL>
+__device__ __forceinline__ void tile_slab_inv(const DevPlan& P, int b, int lbk) {
+  if constexpr (slab_ok<T, LL, kGroupWG>()) dst2_inv_tile<T, LL, kGroupWG>(P, INV_Z_ITER, nullptr, b, lbk);
+}
+template <typename T, int LL>
+__device__ __forceinline__ void tile_xinv(const DevPlan& P, int b, int lbk) {
+  if constexpr (tile_ok<T, LL, kGroupWG, TK_XINV>())
+    dstx_inv_tile<T, LL, kGroupWG>(P, INV_Z_ITER, nullptr, b, lbk, reinterpret_cast<const cplx<T>*>(P.twx));
+}
+#define ABAC_FAR(NAME)                                                              \
+  template <typename T, int LL>                                                     \
+  __device__ __noinline__ void far_##NAME(const DevPlan& P, int b, int lbk) {       \
+    tile_##NAME<T, LL>(P, b, lbk);                                                  \
+  }
+ABAC_FAR(slab_fwd) ABAC_FAR(xfwd) ABAC_FAR(y) ABAC_FAR(time) ABAC_FAR(slab_inv) ABAC_FAR(xinv)
+#undef ABAC_FAR
+#define ABAC_TILE(NAME, LL)                                   \
+  case LL:                                                    \
+    if constexpr (FAR) far_##NAME<T, LL>(P, at.b, lbk);       \
+    else tile_##NAME<T, LL>(P, at.b, lbk);                    \
+    break;
+
 // first pass: the Lanczos step and the x-DST, or the fused x-y pass
-template <typename T>
+template <typename T, bool FAR>
 __device__ __forceinline__ void group_xfwd(const GroupTable* __restrict__ G, int w) {
   const Where at = locate(G, GS_XFWD, w);
   const DevPlan& P = G->m[at.r].P;
   if (!rhs_active(P.st + at.b)) return;
-  constexpr int mode = FWD_LANCZOS;
-  const double* in = nullptr;
-  const int L = 2 * P.Mx;
+  const int lbk = at.lbk;
   if (P.wg_s) {
-#define CASE(LL) \
-    case LL: if constexpr (slab_ok<T, LL, kGroupWG>()) dst2_fwd_tile<T, LL, kGroupWG>(P, mode, in, at.b, at.lbk); break;
-    switch (L) { ABAC_GROUP_SLAB_LENGTHS(CASE) default: break; }
+#define CASE(LL) ABAC_TILE(slab_fwd, LL)
+    switch (2 * P.Mx) { ABAC_GROUP_SLAB_LENGTHS(CASE) default: break; }
 #undef CASE
   } else {
-#define CASE(LL)                                                                                            \
-    case LL:                                                                                                \
-      if constexpr (tile_ok<T, LL, kGroupWG, TK_XFWD>())                                                    \
-        dstx_fwd_tile<T, LL, kGroupWG>(P, mode, in, at.b, at.lbk, reinterpret_cast<const cplx<T>*>(P.twx)); \
-      break;
-    switch (L) { ABAC_GROUP_X_LENGTHS(CASE) default: break; }
+#define CASE(LL) ABAC_TILE(xfwd, LL)
+    switch (2 * P.Mx) { ABAC_GROUP_X_LENGTHS(CASE) default: break; }
 #undef CASE
   }
 }
 
-template <typename T>
+template <typename T, bool FAR>
 __device__ __forceinline__ void group_y(const GroupTable* __restrict__ G, int w) {
   const Where at = locate(G, GS_Y, w);
   const DevPlan& P = G->m[at.r].P;
   if (!rhs_active(P.st + at.b)) return;
   const int lbk = xcd_remap(at.lbk, at.per);
-#define CASE(LL) \
-  case LL: if constexpr (tile_ok<T, LL, kGroupWG, TK_Y>()) dsty_tile<T, LL, kGroupWG>(P, at.b, lbk); break;
+#define CASE(LL) ABAC_TILE(y, LL)
   switch (2 * P.My) { ABAC_GROUP_X_LENGTHS(CASE) default: break; }
 #undef CASE
 }
 
-template <typename T>
+template <typename T, bool FAR>
 __device__ __forceinline__ void group_time(const GroupTable* __restrict__ G, int w) {
   const Where at = locate(G, GS_TIME, w);
   const DevPlan& P = G->m[at.r].P;
   if (!rhs_active(P.st + at.b)) return;
   const int lbk = xcd_remap(at.lbk, at.per);
-#define CASE(LL) \
-  case LL: if constexpr (tile_ok<T, LL, kGroupWG, TK_TIME>()) time_tile<T, LL, kGroupWG>(P, 0, at.b, lbk, 1); break;
+#define CASE(LL) ABAC_TILE(time, LL)
   switch (P.nt) { ABAC_GROUP_T_LENGTHS(CASE) default: break; }
 #undef CASE
 }
 
 // last pass: writes z_{j+1}; <q, P^{-1} q> came from the time pass
-template <typename T>
+template <typename T, bool FAR>
 __device__ __forceinline__ void group_xinv(const GroupTable* __restrict__ G, int w) {
-  constexpr int mode = INV_Z_ITER;
   const Where at = locate(G, GS_XINV, w);
   const DevPlan& P = G->m[at.r].P;
   if (!rhs_active(P.st + at.b)) return;
-  const int L = 2 * P.Mx;
+  const int lbk = at.lbk;
   if (P.wg_s) {
-#define CASE(LL) \
-    case LL: if constexpr (slab_ok<T, LL, kGroupWG>()) dst2_inv_tile<T, LL, kGroupWG>(P, mode, nullptr, at.b, at.lbk); break;
-    switch (L) { ABAC_GROUP_SLAB_LENGTHS(CASE) default: break; }
+#define CASE(LL) ABAC_TILE(slab_inv, LL)
+    switch (2 * P.Mx) { ABAC_GROUP_SLAB_LENGTHS(CASE) default: break; }
 #undef CASE
   } else {
-#define CASE(LL)                                                                                                     \
-    case LL:                                                                                                         \
-      if constexpr (tile_ok<T, LL, kGroupWG, TK_XINV>())                                                             \
-        dstx_inv_tile<T, LL, kGroupWG>(P, mode, nullptr, at.b, at.lbk, reinterpret_cast<const cplx<T>*>(P.twx)); \
-      break;
-    switch (L) { ABAC_GROUP_X_LENGTHS(CASE) default: break; }
+#define CASE(LL) ABAC_TILE(xinv, LL)
+    switch (2 * P.Mx) { ABAC_GROUP_X_LENGTHS(CASE) default: break; }
 #undef CASE
   }
 }
 
+#undef ABAC_TILE
 #undef ABAC_GROUP_X_LENGTHS
 #undef ABAC_GROUP_SLAB_LENGTHS
 #undef ABAC_GROUP_T_LENGTHS
@@ -262,19 +292,19 @@ __global__ void __launch_bounds__(kGroupWG) k_group_form(const GroupTable* __res
 }
 template <typename T>
 __global__ void __launch_bounds__(kGroupWG) k_group_xfwd(const GroupTable* __restrict__ G) {
-  group_xfwd<T>(G, blockIdx.x);
+  group_xfwd<T, false>(G, blockIdx.x);
 }
 template <typename T>
 __global__ void __launch_bounds__(kGroupWG) k_group_y(const GroupTable* __restrict__ G) {
-  group_y<T>(G, blockIdx.x);
+  group_y<T, false>(G, blockIdx.x);
 }
 template <typename T>
 __global__ void __launch_bounds__(kGroupWG) k_group_time(const GroupTable* __restrict__ G) {
-  group_time<T>(G, blockIdx.x);
+  group_time<T, false>(G, blockIdx.x);
 }
 template <typename T>
 __global__ void __launch_bounds__(kGroupWG) k_group_xinv(const GroupTable* __restrict__ G) {
-  group_xinv<T>(G, blockIdx.x);
+  group_xinv<T, false>(G, blockIdx.x);
 }
 
 // ---- persistent kernel: every step of `iterations` iterations in one launch ---------
@@ -326,20 +356,12 @@ __device__ __forceinline__ bool grid_barrier(GridSync* gs, unsigned& gen, unsign
   return pass;
 }
 
-// The step bodies, out of line so that each gets the registers of its own tile (inlined
-// into one loop they would all share the largest tile's and spill).
+// The other step bodies, out of line as well so that each gets its own registers (inlined
+// into one loop they would all share the largest body's and spill).
 template <int MODE>
 __device__ __noinline__ void ps_stencil(const GroupTable* G, int w) { group_stencil<MODE>(G, w); }
 __device__ __noinline__ void ps_fin(const GroupTable* G, int w, int kind) { group_fin(G, w, kind); }
 __device__ __noinline__ void ps_form(const GroupTable* G, int w) { group_form(G, w); }
-template <typename T>
-__device__ __noinline__ void ps_xfwd(const GroupTable* G, int w) { group_xfwd<T>(G, w); }
-template <typename T>
-__device__ __noinline__ void ps_y(const GroupTable* G, int w) { group_y<T>(G, w); }
-template <typename T>
-__device__ __noinline__ void ps_time(const GroupTable* G, int w) { group_time<T>(G, w); }
-template <typename T>
-__device__ __noinline__ void ps_xinv(const GroupTable* G, int w) { group_xinv<T>(G, w); }
 
 // The grid is at most what the device holds at once; block k
 // takes logical blocks k, k + gridDim.x, ... of each step, then the grid meets at a
@@ -363,15 +385,15 @@ k_group_persistent(const GroupTable* __restrict__ G, int iterations, GridSync* g
     }
     ABAC_STEP(GS_STENCIL, ps_stencil<STENCIL_MINRES>(G, w))
     ABAC_STEP(GS_FIN, ps_fin(G, w, FIN_DELTA))
-    ABAC_STEP(GS_XFWD, ps_xfwd<T>(G, w))
-    ABAC_STEP(GS_Y, ps_y<T>(G, w))
-    ABAC_STEP(GS_TIME, ps_time<T>(G, w))
+    ABAC_STEP(GS_XFWD, (group_xfwd<T, true>(G, w)))
+    ABAC_STEP(GS_Y, (group_y<T, true>(G, w)))
+    ABAC_STEP(GS_TIME, (group_time<T, true>(G, w)))
     ABAC_STEP(GS_FIN, ps_fin(G, w, FIN_GAMMA_ITER))
     ABAC_STEP(GS_VEC, ps_form(G, w))
     ABAC_STEP(GS_STENCIL, ps_stencil<STENCIL_RESIDUAL>(G, w))
     ABAC_STEP(GS_FIN, ps_fin(G, w, FIN_RES))
-    ABAC_STEP(GS_Y, ps_y<T>(G, w))
-    ABAC_STEP(GS_XINV, ps_xinv<T>(G, w))
+    ABAC_STEP(GS_Y, (group_y<T, true>(G, w)))
+    ABAC_STEP(GS_XINV, (group_xinv<T, true>(G, w)))
 #undef ABAC_STEP
   }
 }
