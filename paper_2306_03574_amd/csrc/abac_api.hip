@@ -121,6 +121,11 @@ abac_status describe(int nx, int ny, int nt, double T, double alpha, int prec, i
   P.maxparts = std::max(std::max(stencil_blocks(P), update_blocks(P)), std::max((P.nt * P.ny1 + 1) / 2, P.ms / 2));
   P.maxparts = (P.maxparts + 63) & ~63;
   P.prec = prec;
+  // 64 MB: twice the L2s together.  Below it the next pass finds a stored vector in L2
+  // (63 x 64 with 256 right-hand sides, 8 MB: 416 us per solve with plain accesses, 449
+  // marked); above it the mark leaves the cache to the scratch (255^2 x 256, 133 MB: see
+  // stream_load).
+  P.stream = (long long)P.N * P.B * 8 >= (64ll << 20);
   return ABAC_OK;
 }
 

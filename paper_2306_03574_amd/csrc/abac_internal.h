@@ -147,7 +147,7 @@ struct DevPlan {
   int Mx, My;          // nx+1, ny+1 (My = 1 in 1D)
   int m;               // nx * ny1: unknowns per level
   int ms;              // Mx * ny1: scratch modes per level (one zero pad column)
-  int pad_;
+  int stream;          // vectors too large for the caches: see stream_store
   long long N;         // nt * m: unknowns per right-hand side
   long long NS;        // nt * ms: scratch values per right-hand side
   double c0, cx, cy;   // (L s)_i = c0 s_i - cx (s_{i-1} + s_{i+1}) - cy (s_{i-nx} + s_{i+nx})
@@ -285,6 +285,37 @@ __device__ __forceinline__ double parts_share(const double* __restrict__ part, i
 
 __device__ __forceinline__ double sum_parts(const double* __restrict__ part, int n) {
   return block_sum(parts_share(part, n, threadIdx.x, blockDim.x));
+}
+
+// Accesses of vectors that no kernel reads again before as much other data has passed (the
+// Lanczos vectors, the basis, an apply's input and output): marked non-temporal they leave
+// the caches to what the next pass reads, the transform scratch and the matvec's output.
+// Three read streams and one written one of 133 MB: 5.6 TB/s plain, 6.8 with such loads;
+// of 1 GiB 5.7 and 6.3.  Loads of the scratch itself (y and time passes) are faster plain:
+// 255^2 x 256 FP64 4.04 ms per solve against 4.12 to 4.17 with them marked.
+//
+// They are marked only where the plan's vectors exceed the L2s (P.stream): the next pass
+// finds a smaller vector there.  stream_branch makes the choice outside a sweep's loops; its
+// marked branch holds an empty asm statement, since the compiler merges two branches that
+// differ in the marks alone into one of plain accesses.
+template <bool STREAM, typename V>
+__device__ __forceinline__ V stream_load(const V* p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool STREAM, typename V>
+__device__ __forceinline__ void stream_store(V* p, V v) {
+  if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+template <typename F>
+__device__ __forceinline__ void stream_branch(int stream, F&& sweep) {
+  if (stream) {
+    asm volatile("");
+    sweep(std::true_type{});
+  } else {
+    sweep(std::false_type{});
+  }
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs; remap the hardware block

@@ -35,54 +35,42 @@ __device__ __forceinline__ void form_from_basis(const DevPlan& P, int b, double*
   const size_t per = ((size_t)P.N + nparts - 1) / nparts;
   const size_t lo = (size_t)part * per;
   const size_t hi = lo + per < (size_t)P.N ? lo + per : (size_t)P.N;
-  // two elements per trip (the second clamped into range), so 2 NB loads are in flight
-  for (size_t e0 = lo + threadIdx.x; e0 < hi; e0 += 2 * (size_t)blockDim.x) {
-    const size_t e1 = e0 + blockDim.x;
-    const size_t e1c = e1 < hi ? e1 : e0;
-    double z0[NB], z1[NB];
+  // a pair of elements per trip: NB 16-byte loads in flight, past the caches (each z is read
+  // once)
+  const auto pair = [](const double* p) { return stream_load<true>(reinterpret_cast<const dpair*>(p)); };
+  const auto store = [](double* p, dpair v, bool two) {
+    if (two) *reinterpret_cast<dpair*>(p) = v;
+    else *p = v.y;
+  };
+  for (size_t e0 = lo + 2 * threadIdx.x; e0 < hi; e0 += 2 * (size_t)blockDim.x) {
+    // the odd last element of a range is the second of a pair that starts before it
+    const bool two = e0 + 1 < hi;
+    const size_t e = two ? e0 : e0 - 1;
+    dpair z[NB];
 #pragma unroll
-    for (int l = 0; l < NB; ++l) {
-      z0[l] = zs[l][e0];
-      z1[l] = zs[l][e1c];
-    }
-    double ax0 = 0.0, a10 = 0.0, a20 = 0.0, ax1 = 0.0, a11 = 0.0, a21 = 0.0;
-    if (add) {
-      ax0 = X[e0];
-      ax1 = X[e1c];
-    }
+    for (int l = 0; l < NB; ++l) z[l] = pair(zs[l] + e);
+    dpair ax{0.0, 0.0}, a1{0.0, 0.0}, a2{0.0, 0.0};
+    if (add) ax = *reinterpret_cast<const dpair*>(X + e);
     if (carry) {
-      const double p0 = W1[e0], q0 = W2[e0], p1 = W1[e1c], q1 = W2[e1c];
-      ax0 += kc[kBasis] * p0 + kc[kBasis + 1] * q0;
-      ax1 += kc[kBasis] * p1 + kc[kBasis + 1] * q1;
+      const dpair p = *reinterpret_cast<const dpair*>(W1 + e), q = *reinterpret_cast<const dpair*>(W2 + e);
+      ax += kc[kBasis] * p + kc[kBasis + 1] * q;
       if (FLUSH) {
-        a10 = kc[kCoefs + kBasis] * p0 + kc[kCoefs + kBasis + 1] * q0;
-        a11 = kc[kCoefs + kBasis] * p1 + kc[kCoefs + kBasis + 1] * q1;
-        a20 = kc[2 * kCoefs + kBasis] * p0 + kc[2 * kCoefs + kBasis + 1] * q0;
-        a21 = kc[2 * kCoefs + kBasis] * p1 + kc[2 * kCoefs + kBasis + 1] * q1;
+        a1 = kc[kCoefs + kBasis] * p + kc[kCoefs + kBasis + 1] * q;
+        a2 = kc[2 * kCoefs + kBasis] * p + kc[2 * kCoefs + kBasis + 1] * q;
       }
     }
 #pragma unroll
     for (int l = 0; l < NB; ++l) {
-      ax0 += cx[l] * z0[l];
-      ax1 += cx[l] * z1[l];
+      ax += cx[l] * z[l];
       if (FLUSH) {
-        a10 += c1[l] * z0[l];
-        a20 += c2[l] * z0[l];
-        a11 += c1[l] * z1[l];
-        a21 += c2[l] * z1[l];
+        a1 += c1[l] * z[l];
+        a2 += c2[l] * z[l];
       }
     }
-    X[e0] = ax0;
+    store(X + e0, ax, two);
     if (FLUSH) {
-      W1[e0] = a10;
-      W2[e0] = a20;
-    }
-    if (e1 < hi) {
-      X[e1] = ax1;
-      if (FLUSH) {
-        W1[e1] = a11;
-        W2[e1] = a21;
-      }
+      store(W1 + e0, a1, two);
+      store(W2 + e0, a2, two);
     }
   }
 }

@@ -109,12 +109,16 @@ __device__ __forceinline__ void tile_out(TD* __restrict__ dst, const TS* src, in
 }
 
 // Copy cnt <= PER * WG contiguous values of src into LDS (converted to TD): every
-// load of a thread is issued (from a clamped, in-bounds index) before any is used.
+// load of a thread is issued (from a clamped, in-bounds index) before any is used.  What it
+// copies (an apply's input, the scratch in the last pass) is not read again.
 template <int PER, int WG, typename TS, typename TD>
-__device__ __forceinline__ void stage_in(TD* dst, const TS* __restrict__ src, int cnt) {
+__device__ __forceinline__ void stage_in(TD* dst, const TS* __restrict__ src, int cnt, int stream) {
   TS v[PER];
+  stream_branch(stream, [&](auto marked) {
 #pragma unroll
-  for (int u = 0; u < PER; ++u) v[u] = src[min((int)threadIdx.x + u * WG, cnt - 1)];
+    for (int u = 0; u < PER; ++u)
+      v[u] = stream_load<decltype(marked)::value>(src + min((int)threadIdx.x + u * WG, cnt - 1));
+  });
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
     const int e = threadIdx.x + u * WG;
@@ -145,44 +149,65 @@ struct LanczosStep {
     r1 = st->r1;
     r2 = st->r2;
   }
-  // elements e[u] (clamped loads) of a batch; `live` says which are the caller's
-  template <int BATCH>
-  __device__ __forceinline__ void run(const size_t* e, const bool* live, double* out, Dots3& d) const {
-    double a[BATCH], bv[BATCH], cv[BATCH];
+  // One batch of pairs: elements e[u], e[u] + 1 (clamped loads); `live` says which pairs are
+  // the caller's.
+  template <int BATCH, bool STREAM>
+  __device__ __forceinline__ void run(const size_t* e, const bool* live, dpair* out, Dots3& d) const {
+    dpair a[BATCH], bv[BATCH], cv[BATCH];
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) {
-      a[u] = az[e[u]];
-      bv[u] = vj[e[u]];
-      cv[u] = vjm1[e[u]];
+      a[u] = stream_load<STREAM>(reinterpret_cast<const dpair*>(az + e[u]));
+      bv[u] = stream_load<STREAM>(reinterpret_cast<const dpair*>(vj + e[u]));
+      cv[u] = stream_load<STREAM>(reinterpret_cast<const dpair*>(vjm1 + e[u]));
     }
     if (!r) {
 #pragma unroll
       for (int u = 0; u < BATCH; ++u) {
-        out[u] = cA * a[u] - cB * bv[u] - cC * cv[u];
+        out[u] = form(a[u], bv[u], cv[u]);
         if (live[u]) {
-          q[e[u]] = out[u];
-          d.a += out[u] * out[u];
-          d.b += out[u] * bv[u];
-          d.c += out[u] * cv[u];
+          stream_store<STREAM>(reinterpret_cast<dpair*>(q + e[u]), out[u]);
+          d.a += out[u].x * out[u].x + out[u].y * out[u].y;
+          d.b += out[u].x * bv[u].x + out[u].y * bv[u].y;
+          d.c += out[u].x * cv[u].x + out[u].y * cv[u].y;
         }
       }
     } else {
-      double rv[BATCH];
+      dpair rv[BATCH];
 #pragma unroll
-      for (int u = 0; u < BATCH; ++u) rv[u] = r[e[u]];
+      for (int u = 0; u < BATCH; ++u) rv[u] = *reinterpret_cast<const dpair*>(r + e[u]);
 #pragma unroll
       for (int u = 0; u < BATCH; ++u) {
-        out[u] = cA * a[u] - cB * bv[u] - cC * cv[u];
-        const double rn = r1 * rv[u] + r2 * bv[u];
+        out[u] = form(a[u], bv[u], cv[u]);
+        const dpair rn{r1 * rv[u].x + r2 * bv[u].x, r1 * rv[u].y + r2 * bv[u].y};
         if (live[u]) {
-          q[e[u]] = out[u];
-          r[e[u]] = rn;
-          d.a += out[u] * out[u];
-          d.b += out[u] * rn;
-          d.c += rn * rn;
+          *reinterpret_cast<dpair*>(q + e[u]) = out[u];
+          *reinterpret_cast<dpair*>(r + e[u]) = rn;
+          d.a += out[u].x * out[u].x + out[u].y * out[u].y;
+          d.b += out[u].x * rn.x + out[u].y * rn.y;
+          d.c += rn.x * rn.x + rn.y * rn.y;
         }
       }
     }
+  }
+  __device__ __forceinline__ dpair form(dpair a, dpair b, dpair c) const {
+    return dpair{cA * a.x - cB * b.x - cC * c.x, cA * a.y - cB * b.y - cC * c.y};
+  }
+  // a single element, for the odd last one of a range
+  __device__ __forceinline__ double run1(size_t e, Dots3& d) const {
+    const double b = vj[e], c = vjm1[e];
+    const double out = cA * az[e] - cB * b - cC * c;
+    q[e] = out;
+    d.a += out * out;
+    if (!r) {
+      d.b += out * b;
+      d.c += out * c;
+    } else {
+      const double rn = r1 * r[e] + r2 * b;
+      r[e] = rn;
+      d.b += out * rn;
+      d.c += rn * rn;
+    }
+    return out;
   }
 };
 
@@ -208,30 +233,42 @@ __device__ __forceinline__ void dstx_fwd_tile(const DevPlan& P, int mode, const 
   const size_t base = (size_t)row0 * nx;
   const int cnt = nrows * nx;
   // cnt <= 2 S nx < WG * R: each thread stages at most R values, in batches whose
-  // loads (clamped to the tile, so unconditional) are all issued before they are used
-  constexpr int BATCH = 4;
+  // loads (clamped to the tile, so unconditional) are all issued before they are used.
+  // The Lanczos step moves pairs (cnt is even: a tile holds an even number of rows, since nt
+  // is even), twelve 16-byte loads at a time: where the accesses are marked (stream_branch) 129 -> 121 us
+  // at 255^2 x 256 FP64, 940 -> 905 us at 511^2 x 512 FP32 and 1055 -> 890 us for 64 x
+  // 127^2 x 128 FP64, against 8-byte plain loads.
+  constexpr int BATCH = R / 2 < 4 ? R / 2 : 4;
   if (mode == FWD_LANCZOS) {
     const LanczosStep step(P, b);
     Dots3 d{0.0, 0.0, 0.0};
+    auto sweep = [&](auto stream) {
 #pragma unroll
-    for (int u0 = 0; u0 < R; u0 += BATCH) {
-      size_t e[BATCH];
-      bool live[BATCH];
-      double q[BATCH];
+      for (int u0 = 0; u0 < R / 2; u0 += BATCH) {
+        size_t e[BATCH];
+        bool live[BATCH];
+        dpair q[BATCH];
 #pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        const int i = threadIdx.x + (u0 + u) * WG;
-        live[u] = i < cnt;
-        e[u] = base + min(i, cnt - 1);
+        for (int u = 0; u < BATCH; ++u) {
+          const int i = 2 * ((int)threadIdx.x + (u0 + u) * WG);
+          live[u] = i < cnt;
+          e[u] = base + min(i, cnt - 2);
+        }
+        step.run<BATCH, decltype(stream)::value>(e, live, q, d);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+          const int i = 2 * ((int)threadIdx.x + (u0 + u) * WG);
+          if (live[u]) {
+            stage[i] = (T)q[u].x;
+            stage[i + 1] = (T)q[u].y;
+          }
+        }
       }
-      step.run<BATCH>(e, live, q, d);
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u)
-        if (live[u]) stage[threadIdx.x + (u0 + u) * WG] = (T)q[u];
-    }
+    };
+    stream_branch(P.stream, sweep);
     dots_reduce(d, dred);
   } else {
-    stage_in<R, WG>(stage, in + (size_t)b * P.N + base, cnt);
+    stage_in<R, WG>(stage, in + (size_t)b * P.N + base, cnt, P.stream);
   }
   __syncthreads();
   if (mode == FWD_LANCZOS) dots_store(P, b, tile, dred);
@@ -588,7 +625,7 @@ __device__ __forceinline__ void dstx_inv_tile(const DevPlan& P, int mode, double
   const int nrows = min(2 * S, rows - row0);
   const T* scr = reinterpret_cast<const T*>(P.scratch) + (size_t)b * P.NS + (size_t)row0 * Mx;
   const int cnt = nrows * Mx;   // <= 2 S Mx = WG * R
-  stage_in<R, WG>(stage, scr, cnt);
+  stage_in<R, WG>(stage, scr, cnt, P.stream);
   __syncthreads();
   const int s = threadIdx.x % S, j = threadIdx.x / S;
   const int ra = 2 * s, rb = 2 * s + 1;
@@ -626,8 +663,11 @@ __device__ __forceinline__ void dstx_inv_tile(const DevPlan& P, int mode, double
   const int total = nrows * nx;   // < WG * R
   // one contiguous run: 16-byte moves of pairs, and the odd last value
   const int npair = total / 2;
-  for (int e = threadIdx.x; e < npair; e += WG)
-    *reinterpret_cast<dpair*>(o + 2 * e) = *reinterpret_cast<const dpair*>(ostage + 2 * e);
+  auto sweep = [&](auto stream) {
+    for (int e = threadIdx.x; e < npair; e += WG)
+      stream_store<decltype(stream)::value>(reinterpret_cast<dpair*>(o + 2 * e), *reinterpret_cast<const dpair*>(ostage + 2 * e));
+  };
+  stream_branch(P.stream, sweep);
   if ((total & 1) && threadIdx.x == 0) o[total - 1] = ostage[total - 1];
 }
 
@@ -727,21 +767,31 @@ __device__ __forceinline__ void dst2_fwd_tile(const DevPlan& P, int mode, const 
   if (mode == FWD_LANCZOS) {
     const LanczosStep step(P, b);
     Dots3 d{0.0, 0.0, 0.0};
-    for (int e0 = 0; e0 < cnt; e0 += BATCH * WG) {
-      size_t e[BATCH];
-      bool live[BATCH];
-      double q[BATCH];
+    constexpr int PB = BATCH / 2;
+    auto sweep = [&](auto stream) {
+      for (int e0 = 0; e0 + 1 < cnt; e0 += 2 * PB * WG) {
+        size_t e[PB];
+        bool live[PB];
+        dpair q[PB];
 #pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        const int i = e0 + (int)threadIdx.x + u * WG;
-        live[u] = i < cnt;
-        e[u] = base + min(i, cnt - 1);
+        for (int u = 0; u < PB; ++u) {
+          const int i = e0 + 2 * ((int)threadIdx.x + u * WG);
+          live[u] = i + 1 < cnt;
+          e[u] = base + min(i, cnt - 2);
+        }
+        step.run<PB, decltype(stream)::value>(e, live, q, d);
+#pragma unroll
+        for (int u = 0; u < PB; ++u) {
+          const int i = e0 + 2 * ((int)threadIdx.x + u * WG);
+          if (live[u]) {
+            put(i, q[u].x);
+            put(i + 1, q[u].y);
+          }
+        }
       }
-      step.run<BATCH>(e, live, q, d);
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u)
-        if (live[u]) put(e0 + (int)threadIdx.x + u * WG, q[u]);
-    }
+    };
+    stream_branch(P.stream, sweep);
+    if (threadIdx.x == 0) put(cnt - 1, step.run1(base + cnt - 1, d));   // cnt = nx^2 is odd
     dots_reduce(d, dred);
   } else {
     const double* src = in + (size_t)b * P.N + base;
