@@ -109,18 +109,27 @@ abac_status describe(int nx, int ny, int nt, double T, double alpha, int prec, i
   }
   // matvec decomposition: two columns per thread and bands of 2 rows; blocks march
   // over st_chunk levels (and their mirrors).  Longer marches re-read fewer warm-up
-  // levels, shorter ones give more blocks: the chunk is the longest of 64/32/16/8
+  // levels, shorter ones give more blocks: the chunk is the longest of 64/32/16/8/4/2
   // levels whose blocks still fill the GPU once at the matvec's occupancy (2 waves on
-  // each of the 1024 SIMDs).  The rule depends on the shape only (not on the batch), so
-  // a batched solve sums its partials in the same order as a single one.
+  // each of the 1024 SIMDs).  Grids that never do (below about 4 M unknowns) are bound by
+  // the march's chain of load latencies and take the shortest chunk (63^2 x 64 FP32, 10
+  // iterations: 545 us per solve with chunk 8, 470 with chunk 2 and the folded delta below).
+  // The rule depends on the shape only (not on the batch), so a batched solve sums its
+  // partials in the same order as a single one.
   P.st_cols = nx >= 2 ? 2 : 1;
   P.st_rows = ny && nx >= 2 ? 2 : 1;
   P.st_threads = std::min(kStencilThreads, ((nx + P.st_cols - 1) / P.st_cols + 63) / 64 * 64);
   P.st_chunk = 64;
-  while (P.st_chunk > 8 && (long long)stencil_blocks(P) * (P.st_threads / 64) < kStencilWaves) P.st_chunk /= 2;
+  while (P.st_chunk > 2 && (long long)stencil_blocks(P) * (P.st_threads / 64) < kStencilWaves) P.st_chunk /= 2;
   P.maxparts = std::max(std::max(stencil_blocks(P), update_blocks(P)), std::max((P.nt * P.ny1 + 1) / 2, P.ms / 2));
   P.maxparts = (P.maxparts + 63) & ~63;
   P.prec = prec;
+  // Where an iteration is bound by its launches (vectors within the L2s, 32 MB) every wave of
+  // the first pass sums the matvec's partials itself, and the scalar step of delta_j is no
+  // launch of its own (1D 1023 x 256 FP32, with the shorter march: 711 -> 620 us per solve).
+  // Larger grids keep it (4.7 us of an iteration of 400 us at 255^2 x 256, where the pass
+  // would read 8 KB more in each of 32 k waves).
+  P.fold = prec != ABAC_PREC_NONE && (long long)P.N * P.B * 8 <= (32ll << 20);
   // 64 MB: twice the L2s together.  Below it the next pass finds a stored vector in L2
   // (63 x 64 with 256 right-hand sides, 8 MB: 416 us per solve with plain accesses, 449
   // marked); above it the mark leaves the cache to the scratch (255^2 x 256, 133 MB: see
@@ -305,7 +314,7 @@ abac_status enqueue_iteration(abac_plan* p, bool host_checks) {
     return ABAC_OK;
   }
   RUN(ABAC_K_STENCIL, launch_stencil(P, STENCIL_MINRES, nullptr, nullptr, nullptr, p->stream));
-  RUN(ABAC_K_FIN, launch_fin(P, FIN_DELTA, FinArgs{}, p->stream));
+  if (!P.fold) RUN(ABAC_K_FIN, launch_fin(P, FIN_DELTA, FinArgs{}, p->stream));
   if (p->prec == ABAC_PREC_NONE) {
     RUN(ABAC_K_DSTX_INV, launch_identity(P, INV_GAMMA_ITER, nullptr, nullptr, p->stream));
   } else {

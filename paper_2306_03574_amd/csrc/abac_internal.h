@@ -147,7 +147,8 @@ struct DevPlan {
   int Mx, My;          // nx+1, ny+1 (My = 1 in 1D)
   int m;               // nx * ny1: unknowns per level
   int ms;              // Mx * ny1: scratch modes per level (one zero pad column)
-  int stream;          // vectors too large for the caches: see stream_store
+  int stream;          // vectors too large for the caches: see stream_branch
+  int fold;            // the first transform pass forms delta_j from the matvec's partials
   long long N;         // nt * m: unknowns per right-hand side
   long long NS;        // nt * ms: scratch values per right-hand side
   double c0, cx, cy;   // (L s)_i = c0 s_i - cx (s_{i-1} + s_{i+1}) - cy (s_{i-nx} + s_{i+nx})

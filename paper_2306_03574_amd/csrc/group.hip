@@ -53,6 +53,7 @@ struct GroupTable {
   GroupMember m[kGroupMax];
   int off[GS_COUNT][kGroupMax + 1];
   int n;
+  int fold;   // no member needs the scalar step of delta_j (DevPlan::fold)
 };
 
 // Member and block of block w of a step: r with off[r] <= w < off[r+1], then right-hand
@@ -79,41 +80,54 @@ __device__ __forceinline__ Where locate(const GroupTable* __restrict__ G, int st
   return at;
 }
 
-// ---- matvec: one logical block per workgroup, lanes beyond the member's column tile
-// idle (they add 0 to the block's sum, so the partial is the member kernel's) ---------
+// ---- matvec: as many of the member's logical blocks side by side as fit the workgroup
+// (members with short rows have blocks of one or two waves), each with its own partial,
+// the sum of its waves in order as in the member's own kernel ------------------------
+__host__ __device__ inline int stencil_side(const DevPlan& P) { return kGroupWG / P.st_threads; }
+
 template <int MODE>
 __device__ __forceinline__ void group_stencil(const GroupTable* __restrict__ G, int w) {
+  __shared__ double red[kGroupWG / 64];
   const Where at = locate(G, GS_STENCIL, w);
   const GroupMember& M = G->m[at.r];
   const DevPlan& P = M.P;
   const MinresState* st = P.st + at.b;
   if (MODE == STENCIL_RESIDUAL ? st->state != ST_RUNNING || !st->need_check : !rhs_active(st)) return;
   const size_t off = (size_t)at.b * P.N;
+  const int side = stencil_side(P), nblk = stencil_blocks(P);
+  const int sub = threadIdx.x / P.st_threads, tx = threadIdx.x - sub * P.st_threads;
+  const int blk = at.lbk * side + sub;
   double acc = 0.0;
-  const bool lane = (int)threadIdx.x < P.st_threads;
-  if (MODE == STENCIL_RESIDUAL && st->want_r) {
-    const double* x = M.u + off;
-    double* y = P.R + off;
-    const double* f = M.f + off;
-    if (lane)
-      acc = P.coef_x ? stencil_run<true, OUT_RESREV, false>(P, x, y, f, at.lbk, at.per, threadIdx.x, true)
-                     : stencil_run<false, OUT_RESREV, false>(P, x, y, f, at.lbk, at.per, threadIdx.x, true);
-  } else if (MODE == STENCIL_MINRES) {
-    const int j = st->iter + 1;
-    const double* x = P.Z[zslot(j)] + off;
-    double* y = P.V[(j + 1) % 3] + off;
-    if (lane)
-      acc = P.coef_x ? stencil_run<true, OUT_REV, true>(P, x, y, nullptr, at.lbk, at.per, threadIdx.x, true)
-                     : stencil_run<false, OUT_REV, true>(P, x, y, nullptr, at.lbk, at.per, threadIdx.x, true);
-  } else {
-    const double* x = M.u + off;
-    const double* f = M.f + off;
-    if (lane)
-      acc = P.coef_x ? stencil_run<true, OUT_RESNORM, false>(P, x, nullptr, f, at.lbk, at.per, threadIdx.x, true)
-                     : stencil_run<false, OUT_RESNORM, false>(P, x, nullptr, f, at.lbk, at.per, threadIdx.x, true);
+  if (sub < side && blk < nblk) {
+    // one logical block: the stride ends the walk over them after the first
+    if (MODE == STENCIL_RESIDUAL) {
+      const double* x = M.u + off;
+      const double* f = M.f + off;
+      double* y = P.R + off;
+      if (st->want_r)
+        acc = P.coef_x ? stencil_run<true, OUT_RESREV, false>(P, x, y, f, blk, nblk, tx, true)
+                       : stencil_run<false, OUT_RESREV, false>(P, x, y, f, blk, nblk, tx, true);
+      else
+        acc = P.coef_x ? stencil_run<true, OUT_RESNORM, false>(P, x, nullptr, f, blk, nblk, tx, true)
+                       : stencil_run<false, OUT_RESNORM, false>(P, x, nullptr, f, blk, nblk, tx, true);
+    } else {
+      const int j = st->iter + 1;
+      const double* x = P.Z[zslot(j)] + off;
+      double* y = P.V[(j + 1) % 3] + off;
+      acc = P.coef_x ? stencil_run<true, OUT_REV, true>(P, x, y, nullptr, blk, nblk, tx, true)
+                     : stencil_run<false, OUT_REV, true>(P, x, y, nullptr, blk, nblk, tx, true);
+    }
   }
-  const double bs = block_sum(acc);
-  if (threadIdx.x == 0) part_slot(P, MODE == STENCIL_MINRES ? PART_DELTA : PART_RES, at.b)[at.lbk] = bs;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (tx == 0 && sub < side && blk < nblk) {
+    double s = 0.0;
+    for (int i = 0; i < P.st_threads / 64; ++i) s += red[threadIdx.x / 64 + i];
+    part_slot(P, MODE == STENCIL_MINRES ? PART_DELTA : PART_RES, at.b)[blk] = s;
+  }
+  __syncthreads();
 }
 
 // ---- scalar steps: one workgroup per right-hand side --------------------------------
@@ -142,6 +156,7 @@ __device__ __forceinline__ double sum_parts_as(const double* __restrict__ part, 
 __device__ __forceinline__ void group_fin(const GroupTable* __restrict__ G, int w, int kind) {
   const Where at = locate(G, GS_FIN, w);
   const DevPlan& P = G->m[at.r].P;
+  if (kind == FIN_DELTA && P.fold) return;
   int nparts;
   switch (kind) {
     case FIN_DELTA: nparts = stencil_blocks(P); break;
@@ -384,7 +399,9 @@ k_group_persistent(const GroupTable* __restrict__ G, int iterations, GridSync* g
       if (!grid_barrier(gs, gen, deadline)) return;                       \
     }
     ABAC_STEP(GS_STENCIL, ps_stencil<STENCIL_MINRES>(G, w))
-    ABAC_STEP(GS_FIN, ps_fin(G, w, FIN_DELTA))
+    if (!G->fold) {
+      ABAC_STEP(GS_FIN, ps_fin(G, w, FIN_DELTA))
+    }
     ABAC_STEP(GS_XFWD, (group_xfwd<T, true>(G, w)))
     ABAC_STEP(GS_Y, (group_y<T, true>(G, w)))
     ABAC_STEP(GS_TIME, (group_time<T, true>(G, w)))
@@ -415,6 +432,7 @@ struct abac_group {
   std::vector<abac_plan*> members;
   int blocks[GS_COUNT];
   size_t lds[GS_COUNT];
+  bool fold;
   hipEvent_t joined;             // members' set-up done (recorded on each member stream in turn)
   hipEvent_t done;               // the group's last enqueued work
   GridSync* d_sync;              // barrier state of the persistent kernel
@@ -442,7 +460,7 @@ bool member_shape(const DevPlan& P, int prec, int blocks[GS_COUNT], size_t lds[G
     lds[k] = 0;
   }
   const int Lx = 2 * P.Mx, Ly = 2 * P.My;
-  blocks[GS_STENCIL] = stencil_blocks(P);
+  blocks[GS_STENCIL] = (stencil_blocks(P) + stencil_side(P) - 1) / stencil_side(P);
   blocks[GS_VEC] = update_blocks(P);
   blocks[GS_FIN] = 1;
   if (P.wg_s) {
@@ -488,7 +506,7 @@ abac_status group_launch(abac_group* g, int step, int threads, K kernel, A... ar
 template <typename T>
 abac_status group_iteration(abac_group* g) {
   GRUN(group_launch(g, GS_STENCIL, kGroupWG, k_group_stencil<STENCIL_MINRES>));
-  GRUN(group_launch(g, GS_FIN, kGroupFinThreads, k_group_fin, (int)FIN_DELTA));
+  if (!g->fold) GRUN(group_launch(g, GS_FIN, kGroupFinThreads, k_group_fin, (int)FIN_DELTA));
   GRUN(group_launch(g, GS_XFWD, kGroupWG, k_group_xfwd<T>));
   GRUN(group_launch(g, GS_Y, kGroupWG, k_group_y<T>));
   GRUN(group_launch(g, GS_TIME, kGroupWG, k_group_time<T>));
@@ -549,6 +567,7 @@ abac_status abac_group_create(void* stream, abac_group** out) {
   g->joined = g->done = nullptr;
   g->d_sync = nullptr;
   g->device = 0;
+  g->fold = false;
   std::memset(g->blocks, 0, sizeof(g->blocks));
   std::memset(g->lds, 0, sizeof(g->lds));
   hipError_t e = hipGetDevice(&g->device);
@@ -623,6 +642,9 @@ abac_status abac_group_set(abac_group* g, abac_plan* const* plans, int n) {
     g->lds[k] = lmax[k];
   }
   H.n = n;
+  H.fold = 1;
+  for (int r = 0; r < n; ++r) H.fold = H.fold && plans[r]->P.fold;
+  g->fold = H.fold != 0;
   // the group's stream waits for each member's stream (its set-up), then takes the new
   // table in stream order: launches enqueued before read the old one
   for (int r = 0; r < n; ++r) {

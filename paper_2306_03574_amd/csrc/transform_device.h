@@ -133,7 +133,19 @@ __device__ __forceinline__ void stage_in(TD* dst, const TS* __restrict__ src, in
 struct LanczosStep {
   const double *az, *vj, *vjm1;
   double *q, *r;   // r: NULL unless the residual is tracked
-  double cA, cB, cC, r1, r2;
+  double cA, cB, cC, r1, r2, delta;
+  // delta_j = <A z_j, z_j> from the matvec's partials, by each wave in the same order
+  static __device__ __forceinline__ double delta_from_parts(const DevPlan& P, int b, const MinresState* st) {
+    double s = parts_share(part_slot(P, PART_DELTA, b), stencil_blocks(P), threadIdx.x & 63, 64);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    return s * st->sig * st->sig;
+  }
+  // The scalar step that consumes delta_j runs after this pass: one thread of it leaves the
+  // value there (blk: index of the calling block in the right-hand side).
+  __device__ __forceinline__ void publish(const DevPlan& P, int b, int blk) const {
+    if (P.fold && blk == 0 && threadIdx.x == 0) P.st[b].delta = delta;
+  }
   __device__ __forceinline__ LanczosStep(const DevPlan& P, int b) {
     const size_t off = (size_t)b * P.N;
     const MinresState* st = P.st + b;
@@ -144,7 +156,8 @@ struct LanczosStep {
     vjm1 = P.V[j == 1 ? j % 3 : (j + 2) % 3] + off;   // v_0 has weight 0 at j = 1
     r = st->track ? P.R + off : nullptr;
     cA = st->sig;
-    cB = st->delta * st->sig;
+    delta = P.fold ? delta_from_parts(P, b, st) : st->delta;
+    cB = delta * st->sig;
     cC = st->gamma * st->sig_prev;
     r1 = st->r1;
     r2 = st->r2;
@@ -266,6 +279,7 @@ __device__ __forceinline__ void dstx_fwd_tile(const DevPlan& P, int mode, const 
       }
     };
     stream_branch(P.stream, sweep);
+    step.publish(P, b, tile);
     dots_reduce(d, dred);
   } else {
     stage_in<R, WG>(stage, in + (size_t)b * P.N + base, cnt, P.stream);
@@ -792,6 +806,7 @@ __device__ __forceinline__ void dst2_fwd_tile(const DevPlan& P, int mode, const 
     };
     stream_branch(P.stream, sweep);
     if (threadIdx.x == 0) put(cnt - 1, step.run1(base + cnt - 1, d));   // cnt = nx^2 is odd
+    step.publish(P, b, lvl);
     dots_reduce(d, dred);
   } else {
     const double* src = in + (size_t)b * P.N + base;
