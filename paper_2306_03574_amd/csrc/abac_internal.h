@@ -71,7 +71,7 @@ __device__ __forceinline__ bool pass_runs(const MinresState* st, int check) {
 // What the host sees of a right-hand side after the set-up and after the scalar steps of
 // an iteration, in host-mapped memory.  `word` is written last and names the snapshot, so
 // the host needs no event to know that a snapshot is complete: epoch (16 bits), sequence
-// number + 1 (24), hold (bit 2), state (bits 0-1).
+// number + 1 (24), Arnoldi column (GMRES, bits 3-7), hold (bit 2), state (bits 0-1).
 struct Snapshot {
   unsigned long long word;
   int status, iter;
@@ -79,13 +79,14 @@ struct Snapshot {
   double pad_[2];
 };
 static_assert(sizeof(Snapshot) == 64, "one line of host memory per snapshot");
-__host__ __device__ inline unsigned long long snap_word(int epoch, long long seq, int state, int hold) {
+__host__ __device__ inline unsigned long long snap_word(int epoch, long long seq, int state, int hold, int column = 0) {
   return (unsigned long long)(epoch & 0xffff) << 48 | (unsigned long long)((seq + 1) & 0xffffff) << 24 |
-         (unsigned long long)(hold ? 4 : 0) | (unsigned long long)state;
+         (unsigned long long)column << 3 | (unsigned long long)(hold ? 4 : 0) | (unsigned long long)state;
 }
 __host__ __device__ inline unsigned long long snap_name(unsigned long long word) { return word >> 24; }
 __host__ __device__ inline int snap_state(unsigned long long word) { return (int)(word & 3); }
 __host__ __device__ inline bool snap_hold(unsigned long long word) { return (word & 4) != 0; }
+__host__ __device__ inline int snap_column(unsigned long long word) { return (int)(word >> 3 & 31); }
 
 // More per right-hand side state of a MINRES solve, kept in the right-hand side's GMRES
 // state (the two solvers never run on one plan together).
@@ -133,13 +134,9 @@ struct GmresState {
   double bnorm2, tol2, scale, res2, resid2;
   int iter, k, maxit, restart, state, status, need, explicit_mode, restart_now;
   int reorth;   // the current column needs the second Gram-Schmidt pass
+  int epoch, snap;   // this solve's tag; the number of the next snapshot
 };
 static_assert(sizeof(MinresExt) <= sizeof(GmresState), "the MINRES state shares the GMRES state's memory");
-// what the host reads after every step
-struct GmresFlags {
-  int state, need, k, iter;
-};
-
 // Everything a kernel needs about a plan, passed by value.
 struct DevPlan {
   int nx, ny, nt, B;   // ny = 0 in 1D
@@ -172,7 +169,6 @@ struct DevPlan {
   double* Z[kZSlots];  // slot zslot(j) holds the stored z_j
   double* W[2];
   GmresState* gst;     // B entries (GMRES solves; MINRES solves keep their MinresExt there)
-  GmresFlags* gflags;  // B entries
   double* gparts;      // B x (kGmresMax + 1) x kVecMaxBlocks partial dot products
   double* R;           // MINRES: the residual vector while it is tracked; GMRES: the cycle's first iterate
   double* dot3;        // third inner product of the first transform pass, one partial per block
@@ -319,6 +315,28 @@ __device__ __forceinline__ void stream_branch(int stream, F&& sweep) {
   }
 }
 
+// Write snapshot `seq` of right-hand side b to the host-mapped ring (by one thread).  Every
+// store goes past the caches (system scope).  Of a solve that has stopped, the word that
+// names the snapshot is stored once the others have been acknowledged (a system-scope fence
+// would also write the whole L2 back); while it runs, the others are hints, and the step
+// does not wait for host memory.
+__device__ __forceinline__ void write_snapshot(const DevPlan& P, int b, int seq, unsigned long long word, bool stopped,
+                                               int status, int iter, double rnorm2, double bnorm2, double res2,
+                                               double tol2) {
+  if (!P.host_ring) return;
+  Snapshot* s = P.host_ring + (size_t)(seq % kSnapRing) * P.B + b;
+#define ABAC_PUT(field, value) __hip_atomic_store(&s->field, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)
+  ABAC_PUT(status, status);
+  ABAC_PUT(iter, iter);
+  ABAC_PUT(rnorm2, rnorm2);
+  ABAC_PUT(bnorm2, bnorm2);
+  ABAC_PUT(res2, res2);
+  ABAC_PUT(tol2, tol2);
+  if (stopped) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  ABAC_PUT(word, word);
+#undef ABAC_PUT
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs; remap the hardware block
 // index so each XCD receives a contiguous range of logical blocks (shared halo
 // rows then hit the same L2).
@@ -378,7 +396,6 @@ hipError_t launch_identity(const DevPlan& P, int mode, const double* in, double*
 // GMRES steps (kernels_gmres.hip); gslot(l) is the vector slot of Arnoldi vector v_l
 enum GmresFin : int { G_INIT = 0, G_DOTS1 = 1, G_DOTS2 = 2, G_NORM = 3, G_CHECK = 4 };
 hipError_t launch_ginit(const DevPlan& P, const double* f, double* u, hipStream_t s);
-hipError_t launch_gfin(const DevPlan& P, int kind, double tol, int maxit, int restart, hipStream_t s);
 hipError_t launch_gdots(const DevPlan& P, int j, const double* w, hipStream_t s);
 hipError_t launch_gaxpy(const DevPlan& P, int j, int pass, double* w, hipStream_t s);
 hipError_t launch_gbase(const DevPlan& P, const double* src, const double* u, int restart_step, hipStream_t s);
@@ -397,6 +414,7 @@ struct FinArgs {
   int post = 0;                // 1: FIN_GAMMA_ITER posts a snapshot, as the set-up and FIN_RES do; -1: none does
 };
 hipError_t launch_fin(const DevPlan& P, int kind, const FinArgs& a, hipStream_t s);
+hipError_t launch_gfin(const DevPlan& P, int kind, const FinArgs& a, int restart, hipStream_t s);
 
 // check: which right-hand sides the pass skips (PassCheck)
 hipError_t launch_dstx_fwd(const DevPlan& P, int prec, int mode, int check, const double* in, hipStream_t s);

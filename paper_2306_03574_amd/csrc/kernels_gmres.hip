@@ -239,30 +239,28 @@ k_gaddx(DevPlan P, double* __restrict__ u, const double* __restrict__ z) {
   for (size_t e = lo + threadIdx.x; e < hi; e += blockDim.x) u[off + e] = x0[e] + z[off + e];
 }
 
-__device__ void write_flags(const DevPlan& P, int b, const GmresState* st) {
-  GmresFlags f;
-  f.state = st->state;
-  f.need = st->need;
-  f.k = st->k;
-  f.iter = st->iter;
-  P.gflags[b] = f;
+// The snapshot the host reads after the set-up, after every column (hold: the iterate is to
+// be formed and checked) and after every check.
+__device__ void post_flags(const DevPlan& P, int b, int kind, GmresState* st) {
+  if (kind != G_INIT && kind != G_NORM && kind != G_CHECK) return;
+  const int seq = st->snap;
+  st->snap = seq + 1;
+  write_snapshot(P, b, seq, snap_word(st->epoch, seq, st->state, st->need, st->k), st->state != ST_RUNNING, st->status,
+                 st->iter, st->resid2, st->bnorm2, st->res2, st->tol2);
 }
 
 // The scalar steps, one block per right-hand side.
 __global__ void __launch_bounds__(kGFinThreads)
-k_gfin(DevPlan P, int kind, int nparts, double tol, int maxit, int restart) {
+k_gfin(DevPlan P, int kind, int nparts, FinArgs a, int restart) {
   const int b = blockIdx.x;
   GmresState* st = P.gst + b;
   if (kind != G_INIT && (st->state != ST_RUNNING || (kind == G_CHECK && !st->need))) {
-    if (threadIdx.x == 0) write_flags(P, b, st);
+    if (threadIdx.x == 0) post_flags(P, b, kind, st);
     return;
   }
   if (kind == G_DOTS1 || kind == G_DOTS2) {
     const int j = st->k;
-    if (kind == G_DOTS2 && !st->reorth) {   // no second pass: h2 = 0 (set by G_DOTS1)
-      if (threadIdx.x == 0) write_flags(P, b, st);
-      return;
-    }
+    if (kind == G_DOTS2 && !st->reorth) return;   // no second pass: h2 = 0 (set by G_DOTS1)
     double* h = kind == G_DOTS1 ? st->h1 : st->h2;
     double hh = 0.0;
     for (int l = 0; l <= j; ++l) {
@@ -282,7 +280,6 @@ k_gfin(DevPlan P, int kind, int nparts, double tol, int maxit, int restart) {
           for (int l = 0; l <= j; ++l) st->h2[l] = 0.0;
       }
       st->restart_now = 0;   // the restart copy (if any) has run
-      write_flags(P, b, st);
     }
     return;
   }
@@ -291,8 +288,10 @@ k_gfin(DevPlan P, int kind, int nparts, double tol, int maxit, int restart) {
   switch (kind) {
     case G_INIT:
       st->bnorm2 = tot;
-      st->tol2 = tol * tol;
-      st->maxit = maxit;
+      st->tol2 = a.tol * a.tol;
+      st->maxit = a.maxit;
+      st->epoch = a.epoch;
+      st->snap = 0;
       st->restart = restart;
       st->iter = 0;
       st->k = 0;
@@ -384,7 +383,7 @@ k_gfin(DevPlan P, int kind, int nparts, double tol, int maxit, int restart) {
     default:
       break;
   }
-  write_flags(P, b, st);
+  post_flags(P, b, kind, st);
 }
 
 }  // namespace
@@ -394,9 +393,9 @@ hipError_t launch_ginit(const DevPlan& P, const double* f, double* u, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_gfin(const DevPlan& P, int kind, double tol, int maxit, int restart, hipStream_t s) {
+hipError_t launch_gfin(const DevPlan& P, int kind, const FinArgs& a, int restart, hipStream_t s) {
   const int nparts = kind == G_CHECK ? stencil_grid(P, STENCIL_RESVEC) : update_blocks(P);
-  hipLaunchKernelGGL(k_gfin, dim3(P.B), dim3(kGFinThreads), 0, s, P, kind, nparts, tol, maxit, restart);
+  hipLaunchKernelGGL(k_gfin, dim3(P.B), dim3(kGFinThreads), 0, s, P, kind, nparts, a, restart);
   return hipGetLastError();
 }
 

@@ -213,26 +213,11 @@ __device__ __forceinline__ void step_coefs(const MinresState* st, MinresExt* x) 
   *xm += x->xc * w;
 }
 
-// Write the next snapshot of right-hand side b to the host-mapped ring (by one thread).
-// Every store goes past the caches (system scope).  Of a solve that has stopped, the word
-// that names the snapshot is stored once the others have been acknowledged (a system-scope
-// fence would also write the whole L2 back); while it runs, the others are hints, and the
-// step does not wait for host memory.
 __device__ __forceinline__ void post_snapshot(const DevPlan& P, int b, MinresState* st) {
   const int seq = st->snap;
   st->snap = seq + 1;
-  if (!P.host_ring) return;
-  Snapshot* s = P.host_ring + (size_t)(seq % kSnapRing) * P.B + b;
-#define ABAC_PUT(field, value) __hip_atomic_store(&s->field, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)
-  ABAC_PUT(status, st->status);
-  ABAC_PUT(iter, st->iter);
-  ABAC_PUT(rnorm2, st->rnorm2);
-  ABAC_PUT(bnorm2, st->bnorm2);
-  ABAC_PUT(res2, st->res2);
-  ABAC_PUT(tol2, st->tol2);
-  if (st->state != ST_RUNNING) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  ABAC_PUT(word, snap_word(st->epoch, seq, st->state, st->hold));
-#undef ABAC_PUT
+  write_snapshot(P, b, seq, snap_word(st->epoch, seq, st->state, st->hold), st->state != ST_RUNNING, st->status, st->iter,
+                 st->rnorm2, st->bnorm2, st->res2, st->tol2);
 }
 
 // First half of a scalar step of right-hand side b: the flag updates of the step kind

@@ -62,3 +62,31 @@ def test_more_iterations_than_the_ring_holds(nx, ny, nt):
     torch.cuda.synchronize()
     assert it1 == it2 and rr1 == rr2 and st1 == st2
     assert torch.equal(u1, u2)
+
+
+@pytest.mark.parametrize("nx,ny,nt", [(31, 15, 16), (15, 0, 16)])
+def test_gmres_and_minres_take_turns(nx, ny, nt):
+    """Both solvers post to the same ring: one plan that alternates them, with right-hand
+    sides that stop apart (one is zero), gives what fresh plans give, also past the ring's
+    length (40 GMRES steps in cycles of 3 post 54 snapshots)."""
+    from paper_2306_03574_amd import Plan
+    print(f"[case] alternating solvers nx={nx} ny={ny} nt={nt}", flush=True)
+
+    def fresh():
+        return Plan(nx, ny, nt, alpha=0.3, batch=3, device=DEV)
+
+    def outcome(u, iters, relres, status):
+        torch.cuda.synchronize()
+        return u.clone(), iters, relres, status
+
+    f = _rhs(fresh(), 9)
+    f[1].zero_()
+    calls = [lambda p: p.gmres(f, tol=1e-30, maxit=40, restart=3), lambda p: p.solve(f, tol=1e-8, maxit=200),
+             lambda p: p.gmres(f, tol=1e-8, maxit=200)]
+    want = [outcome(*c(fresh())) for c in calls]
+    assert want[0][1] == [40, 0, 40] and want[0][3] == [-4, 0, -4] and want[2][3] == [0, 0, 0]
+    p = fresh()
+    for i in (0, 1, 2, 1, 0, 2):
+        got = outcome(*calls[i](p))
+        assert got[1:] == want[i][1:]
+        assert torch.equal(got[0], want[i][0])
