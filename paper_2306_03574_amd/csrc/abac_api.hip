@@ -1019,6 +1019,7 @@ abac_status abac_gmres_solve(abac_plan* p, const double* f, double* u, double to
     RUN(ABAC_K_FIN, launch_gfin(P, G_CHECK, FinArgs{}, 0, p->stream));
     RUN(ABAC_K_GMRES, launch_gbase(P, t, u, 1, p->stream));
     if ((s = next_snapshot()) != ABAC_OK) return s;
+    if (!any(running)) break;   // also in the last column of a cycle
     const bool restarted = any([](unsigned long long w) { return snap_column(w) == 0; });
     j = restarted ? 0 : j + 1;
     if (j >= restart) return fail(ABAC_EDEVICE, "GMRES cycle bookkeeping out of step");

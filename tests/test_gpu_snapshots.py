@@ -90,3 +90,19 @@ def test_gmres_and_minres_take_turns(nx, ny, nt):
         got = outcome(*calls[i](p))
         assert got[1:] == want[i][1:]
         assert torch.equal(got[0], want[i][0])
+
+
+@pytest.mark.parametrize("restart", [1, 3])
+def test_gmres_stops_in_the_last_column_of_a_cycle(restart):
+    """maxit at the end of a cycle: the iterate of that column and ABAC_ENOCONV (-4), equal
+    to what longer cycles give there."""
+    from paper_2306_03574_amd import Plan
+    p = Plan(31, 15, 16, alpha=0.3, device=DEV)
+    f = _rhs(p, 9)
+    u, iters, relres, status = p.gmres(f, tol=1e-30, maxit=restart, restart=restart)
+    u = u.clone()
+    assert iters == [restart] and status == [-4]
+    v, iters2, relres2, status2 = p.gmres(f, tol=1e-30, maxit=restart, restart=15)
+    torch.cuda.synchronize()
+    assert (iters2, relres2, status2) == (iters, relres, status)
+    assert torch.equal(u, v)
