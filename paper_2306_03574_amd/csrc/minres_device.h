@@ -9,9 +9,15 @@
 namespace abac {
 namespace {
 
+constexpr int kFormTrips = kVecPerThread / 2;
+
 // u = [u +] sum_l xm_l z_l over the NB vectors of the current cycle, plus the two carried
 // w vectors of a later cycle; with FLUSH also W[0] = w_j and W[1] = w_{j-1} from their
-// coefficients.  Elements [part N/nparts, (part+1) N/nparts) of right-hand side b.
+// coefficients.  The nparts blocks of right-hand side b take turns
+// of kFormTrips trips: 32 KB of each vector in a row per block, and the chip sweeps all of
+// them front to back.  Memory bounds it.  Against one range per block (1 MB at 511^2 x 512):
+// 2400 -> 2285 us there (10 iterations, 5.1 TB/s), 238 -> 202 us at 255^2 x 256; turns of
+// 4 KB 1866 us at 64 x 127^2 x 128, where a range is one turn and takes 1790 to 1810 us.
 template <int NB, bool FLUSH>
 __device__ __forceinline__ void form_from_basis(const DevPlan& P, int b, double* __restrict__ u, int part,
                                                 int nparts) {
@@ -32,20 +38,13 @@ __device__ __forceinline__ void form_from_basis(const DevPlan& P, int b, double*
   double* X = u + off;
   double* W1 = P.W[0] + off;
   double* W2 = P.W[1] + off;
-  const size_t per = ((size_t)P.N + nparts - 1) / nparts;
-  const size_t lo = (size_t)part * per;
-  const size_t hi = lo + per < (size_t)P.N ? lo + per : (size_t)P.N;
-  // a pair of elements per trip: NB 16-byte loads in flight, past the caches (each z is read
-  // once)
+  // a pair of elements per trip (N is even, since nt is): NB 16-byte loads in flight, past
+  // the caches (each z is read once)
   const auto pair = [](const double* p) { return stream_load<true>(reinterpret_cast<const dpair*>(p)); };
-  const auto store = [](double* p, dpair v, bool two) {
-    if (two) *reinterpret_cast<dpair*>(p) = v;
-    else *p = v.y;
-  };
-  for (size_t e0 = lo + 2 * threadIdx.x; e0 < hi; e0 += 2 * (size_t)blockDim.x) {
-    // the odd last element of a range is the second of a pair that starts before it
-    const bool two = e0 + 1 < hi;
-    const size_t e = two ? e0 : e0 - 1;
+  const auto store = [](double* p, dpair v) { *reinterpret_cast<dpair*>(p) = v; };
+  const size_t step = 2 * (size_t)blockDim.x, chunk = kFormTrips * step;
+  size_t e = part * chunk + 2 * threadIdx.x;
+  for (int trip = 1; e < (size_t)P.N; e += trip % kFormTrips ? step : step + (nparts - 1) * chunk, ++trip) {
     dpair z[NB];
 #pragma unroll
     for (int l = 0; l < NB; ++l) z[l] = pair(zs[l] + e);
@@ -67,10 +66,10 @@ __device__ __forceinline__ void form_from_basis(const DevPlan& P, int b, double*
         a2 += c2[l] * z[l];
       }
     }
-    store(X + e0, ax, two);
+    store(X + e, ax);
     if (FLUSH) {
-      store(W1 + e0, a1, two);
-      store(W2 + e0, a2, two);
+      store(W1 + e, a1);
+      store(W2 + e, a2);
     }
   }
 }
