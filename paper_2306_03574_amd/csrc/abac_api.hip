@@ -67,6 +67,9 @@ struct Layout {
       counters, total;
 };
 
+// Whether the partials of the first pass's third inner product fit the GMRES partials' region.
+bool dots_apart(const DevPlan& P) { return (long long)P.nt * P.ny1 / 2 <= (kGmresMax + 1) * kVecMaxBlocks; }
+
 // Validate the problem and fill the size fields of a DevPlan.
 abac_status describe(int nx, int ny, int nt, double T, double alpha, int prec, int batch, DevPlan& P) {
   if (prec != ABAC_PREC_FP64 && prec != ABAC_PREC_FP32 && prec != ABAC_PREC_NONE)
@@ -129,7 +132,9 @@ abac_status describe(int nx, int ny, int nt, double T, double alpha, int prec, i
   // launch of its own (1D 1023 x 256 FP32, with the shorter march: 711 -> 620 us per solve).
   // Larger grids keep it (4.7 us of an iteration of 400 us at 255^2 x 256, where the pass
   // would read 8 KB more in each of 32 k waves).
-  P.fold = prec != ABAC_PREC_NONE && (long long)P.N * P.B * 8 <= (32ll << 20);
+  // Never where that pass leaves an inner product's partials in the matvec's slots
+  // (dots_apart): its later blocks would sum what its earlier ones wrote.
+  P.fold = prec != ABAC_PREC_NONE && (long long)P.N * P.B * 8 <= (32ll << 20) && dots_apart(P);
   // 64 MB: twice the L2s together.  Below it the next pass finds a stored vector in L2
   // (63 x 64 with 256 right-hand sides, 8 MB: 416 us per solve with plain accesses, 449
   // marked); above it the mark leaves the cache to the scratch (255^2 x 256, 133 MB: see
@@ -774,8 +779,9 @@ abac_status abac_plan_create(int nx, int ny, int nt, double T, double alpha, int
   P.st = reinterpret_cast<MinresState*>(base + Lo.st);
   P.partials = reinterpret_cast<double*>(base + Lo.partials);
   // the third inner product's partials: the GMRES partials' region where a right-hand
-  // side's blocks fit it, else the matvec's, which are summed before that pass starts
-  if ((long long)P.nt * P.ny1 / 2 <= (kGmresMax + 1) * kVecMaxBlocks) {
+  // side's blocks fit it, else the matvec's, which are then summed before that pass starts
+  // (DevPlan::fold)
+  if (dots_apart(P)) {
     P.dot3 = P.gparts;
     P.dot3_stride = (long long)(kGmresMax + 1) * kVecMaxBlocks;
   } else {
