@@ -381,6 +381,16 @@ __host__ __device__ inline int stencil_blocks(const DevPlan& P) {
   const int nchunks = (P.nt / 2 + P.st_chunk - 1) / P.st_chunk;
   return tiles * nchunks;
 }
+// <A z_j, z_j> from the matvec's partials, by each wave that calls it, in one order: the
+// scalar step and the first transform pass (DevPlan::fold) get the same bits, so that a
+// batch whose vectors are too large to fold equals its right-hand sides on their own.
+__device__ __forceinline__ double delta_sum(const DevPlan& P, int b) {
+  double s = parts_share(part_slot(P, PART_DELTA, b), stencil_blocks(P), threadIdx.x & 63, 64);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  return s;
+}
+
 int stencil_grid(const DevPlan& P, int mode);
 int update_blocks(const DevPlan& P);
 int dstx_blocks(const DevPlan& P, int wg);

@@ -166,6 +166,7 @@ __device__ __forceinline__ void group_fin(const GroupTable* __restrict__ G, int 
   }
   fin_step(P, at.b, kind, FinArgs{}, [&](Dots3* dots) {
     if (kind == FIN_GAMMA_ITER) *dots = sum_dots(P, at.b, (G->off[GS_XFWD][at.r + 1] - G->off[GS_XFWD][at.r]) / P.B);
+    if (kind == FIN_DELTA) return threadIdx.x < 64 ? delta_sum(P, at.b) : 0.0;
     return sum_parts_as(part_slot(P, fin_part_kind(kind), at.b), nparts, kGroupFinThreads);
   });
 }

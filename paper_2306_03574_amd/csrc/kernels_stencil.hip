@@ -189,6 +189,7 @@ k_fin(DevPlan P, int kind, int nparts, int ndots, FinArgs a) {
   const int b = blockIdx.x;
   fin_step(P, b, kind, a, [&](Dots3* dots) {
     if (kind == FIN_GAMMA_ITER) *dots = sum_dots(P, b, ndots);
+    if (kind == FIN_DELTA) return threadIdx.x < 64 ? delta_sum(P, b) : 0.0;
     return sum_parts(part_slot(P, fin_part_kind(kind), b), nparts);
   });
 }

@@ -134,13 +134,6 @@ struct LanczosStep {
   const double *az, *vj, *vjm1;
   double *q, *r;   // r: NULL unless the residual is tracked
   double cA, cB, cC, r1, r2, delta;
-  // delta_j = <A z_j, z_j> from the matvec's partials, by each wave in the same order
-  static __device__ __forceinline__ double delta_from_parts(const DevPlan& P, int b, const MinresState* st) {
-    double s = parts_share(part_slot(P, PART_DELTA, b), stencil_blocks(P), threadIdx.x & 63, 64);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    return s * st->sig * st->sig;
-  }
   // The scalar step that consumes delta_j runs after this pass: one thread of it leaves the
   // value there (blk: index of the calling block in the right-hand side).
   __device__ __forceinline__ void publish(const DevPlan& P, int b, int blk) const {
@@ -156,7 +149,7 @@ struct LanczosStep {
     vjm1 = P.V[j == 1 ? j % 3 : (j + 2) % 3] + off;   // v_0 has weight 0 at j = 1
     r = st->track ? P.R + off : nullptr;
     cA = st->sig;
-    delta = P.fold ? delta_from_parts(P, b, st) : st->delta;
+    delta = P.fold ? delta_sum(P, b) * st->sig * st->sig : st->delta;
     cB = delta * st->sig;
     cC = st->gamma * st->sig_prev;
     r1 = st->r1;
