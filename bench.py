@@ -198,8 +198,8 @@ def copy_probe(nbytes=None, pattern="copy"):
 
 
 def run_gpu(w, prec, steps, warmup, tol, maxit, profile=True, solver="minres", restart=15):
-    """Time `steps` whole solves (production path: graph-replayed iterations, no
-    per-kernel events), then, if `profile`, repeat the same steps with every kernel
+    """Time `steps` whole solves (production path, no per-kernel
+    events), then, if `profile`, repeat the same steps with every kernel
     bracketed by HIP events on the plan stream to get per-kernel durations."""
     import torch
     from paper_2306_03574_amd import Plan
@@ -382,7 +382,7 @@ def run_serving(args):
     import synth
     budget = int(args.budget_gb * (1 << 30))
     prec = args.prec or "fp32"
-    # warm every shape class once (plans, workspaces and graphs are cached by the server)
+    # warm every shape class once (plans and workspaces are cached by the server)
     classes = sorted({(nx, ny, nt, a) for (nx, ny) in synth.workloads.SERVING_SHAPES for nt in synth.workloads.SERVING_NT
                       for a in synth.workloads.SERVING_ALPHA})
     log(f"serving: rate {args.rate}/s, {args.requests} requests, budget {args.budget_gb} GB, max_active {args.max_active}")

@@ -277,7 +277,7 @@ enum {
   ABAC_K_DSTY = 2,      /* y-direction DST pass (2D, both directions)   */
   ABAC_K_TIME = 3,      /* per-mode time pipeline K Y K Y               */
   ABAC_K_DSTX_INV = 4,  /* last spatial DST pass (x)                    */
-  ABAC_K_UPDATE = 5,    /* MINRES residual (and late w / x) update      */
+  ABAC_K_UPDATE = 5,    /* no launches: iterations update no vectors    */
   ABAC_K_RESIDUAL = 6,  /* explicit residual check                      */
   ABAC_K_INIT = 7,      /* solve set-up                                 */
   ABAC_K_RHS = 8,       /* right-hand side assembly                     */

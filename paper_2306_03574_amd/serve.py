@@ -98,7 +98,7 @@ def run_trace(trace, budget_bytes, max_active=16, prec="fp32", tol=1e-8, maxit=5
     to the last completion)."""
     srv = Server(budget_bytes, max_active, group_max_unknowns)
     if warm_classes:
-        # one untimed solve per shape class: the server keeps their plans and graphs cached
+        # one untimed solve per shape class: the server keeps their plans cached
         warm = [srv.submit(nx, ny, nt, a, seed=1, prec=prec, tol=tol, maxit=maxit) for (nx, ny, nt, a) in warm_classes]
         srv.drain(warm, timeout=600)
     t0 = srv.clock()
