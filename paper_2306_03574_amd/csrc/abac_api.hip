@@ -376,6 +376,19 @@ const Snapshot* newest_snapshot(const abac_plan* p) {
   return p->h_ring + (size_t)((p->ring_posted - 1) % kSnapRing) * p->P.B;
 }
 
+// A new solve's tag.  Where the 16 bits start over the ring is cleared behind all queued
+// work: a slot that no solve has written since could hold this tag and number from 65536
+// solves ago.
+abac_status next_epoch(abac_plan* p) {
+  p->ring_posted = 0;
+  p->epoch = (p->epoch + 1) & 0xffff;
+  if (p->epoch == 0) {
+    HIP_TRY(hipStreamSynchronize(p->stream));
+    std::memset(p->h_ring, 0, sizeof(Snapshot) * (size_t)kSnapRing * p->P.B);
+  }
+  return ABAC_OK;
+}
+
 bool all_stopped(const Snapshot* s, int B) {
   for (int b = 0; b < B; ++b)
     if (snap_state(s[b].word) == ST_RUNNING) return false;
@@ -974,8 +987,7 @@ abac_status abac_gmres_solve(abac_plan* p, const double* f, double* u, double to
   // The set-up, every column and every check end with a snapshot in host memory: a copy
   // and a stream synchronisation in their place cost 45 us each, of 200 us a column takes at
   // 255 x 127 x 128 (1217 -> 1026 us per solve).
-  p->epoch = (p->epoch + 1) & 0xffff;
-  p->ring_posted = 0;
+  if (abac_status e = next_epoch(p); e != ABAC_OK) return e;
   const Snapshot* snap = nullptr;
   auto next_snapshot = [&]() -> abac_status {
     abac_status e = wait_snapshot(p, p->ring_posted++);
@@ -1045,12 +1057,11 @@ abac_status abac_gmres_solve(abac_plan* p, const double* f, double* u, double to
 
 namespace {
 
-void start_solve(abac_plan* p, const double* f, double* u) {
+abac_status start_solve(abac_plan* p, const double* f, double* u) {
   p->f = f;
   p->u = u;
   p->active = true;
-  p->epoch = (p->epoch + 1) & 0xffff;
-  p->ring_posted = 0;
+  return next_epoch(p);
 }
 
 FinArgs solve_args(const abac_plan* p, double tol, int maxit) {
@@ -1117,7 +1128,7 @@ abac_status abac_minres_begin(abac_plan* p, const double* f, double* u, double t
   if (!p || !f || !u) return fail(ABAC_EINVAL, "NULL argument");
   if (!(tol > 0) || maxit < 1) return fail(ABAC_EINVAL, "tol must be > 0 and maxit >= 1");
   if (f == u) return fail(ABAC_EINVAL, "u must not alias f");
-  start_solve(p, f, u);
+  if (abac_status e = start_solve(p, f, u); e != ABAC_OK) return e;
   if (p->P.small) {
     RUN(ABAC_K_INIT, launch_setup_small(p->P, p->prec, f, u, solve_args(p, tol, maxit), p->stream));
   } else {
@@ -1167,7 +1178,7 @@ abac_status abac_minres_solve(abac_plan* p, const double* f, double* u, double t
                               double* relres, int* status) {
   if (p && p->P.small && f && u && f != u && tol > 0 && maxit >= 1) {
     // small problems: the set-up and every iteration in one launch
-    start_solve(p, f, u);
+    if (abac_status e = start_solve(p, f, u); e != ABAC_OK) return e;
     RUN(ABAC_K_ITER, launch_solve_small(p->P, p->prec, f, u, solve_args(p, tol, maxit), p->stream));
     p->ring_posted++;
     return abac_minres_finish(p, iters, relres, status);

@@ -106,3 +106,23 @@ def test_gmres_stops_in_the_last_column_of_a_cycle(restart):
     torch.cuda.synchronize()
     assert (iters2, relres2, status2) == (iters, relres, status)
     assert torch.equal(u, v)
+
+
+def test_tags_start_over():
+    """The 16-bit tag of a plan's solves comes round again: a long solve that gets an earlier
+    long solve's tag must wait for its own snapshots, of which the ring still holds the
+    earlier one's last."""
+    from paper_2306_03574_amd import Plan
+    p = Plan(7, 7, 8, alpha=1e-2, device=DEV)
+    f1, f2 = _rhs(p, 3), _rhs(p, 40)
+    want = p.solve(f2, tol=1e-30, maxit=40)[1:]
+    p = Plan(7, 7, 8, alpha=1e-2, device=DEV)
+    u = p.empty()
+    p.solve(f1, u, tol=1e-30, maxit=40)       # tag 1
+    zero = torch.zeros_like(f1)
+    for n in range(65535):                    # a zero right-hand side stops in the set-up
+        p.solve(zero, u)
+        if n % 16384 == 0:
+            print(f"[progress] {n} solves", flush=True)
+    got = p.solve(f2, u, tol=1e-30, maxit=40)[1:]
+    assert got == want
