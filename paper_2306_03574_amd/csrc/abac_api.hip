@@ -122,8 +122,7 @@ abac_status describe(int nx, int ny, int nt, double T, double alpha, int prec, i
   P.st_cols = nx >= 2 ? 2 : 1;
   P.st_rows = ny && nx >= 2 ? 2 : 1;
   P.st_threads = std::min(kStencilThreads, ((nx + P.st_cols - 1) / P.st_cols + 63) / 64 * 64);
-  P.st_chunk = 64;
-  while (P.st_chunk > 2 && (long long)stencil_blocks(P) * (P.st_threads / 64) < kStencilWaves) P.st_chunk /= 2;
+  stencil_chunk(P, 1);
   P.maxparts = std::max(std::max(stencil_blocks(P), update_blocks(P)), std::max((P.nt * P.ny1 + 1) / 2, P.ms / 2));
   P.maxparts = (P.maxparts + 63) & ~63;
   P.prec = prec;

@@ -381,6 +381,14 @@ __host__ __device__ inline int stencil_blocks(const DevPlan& P) {
   const int nchunks = (P.nt / 2 + P.st_chunk - 1) / P.st_chunk;
   return tiles * nchunks;
 }
+// The longest chunk of 64/32/16/8/4/2 levels whose blocks fill the GPU once at the matvec's
+// occupancy: those of one right-hand side down to 8 levels, of `rhs` of them below.
+inline void stencil_chunk(DevPlan& P, int rhs) {
+  P.st_chunk = 64;
+  while (P.st_chunk > 2 &&
+         (long long)stencil_blocks(P) * (P.st_chunk > 8 ? 1 : rhs) * (P.st_threads / 64) < kStencilWaves)
+    P.st_chunk /= 2;
+}
 // <A z_j, z_j> from the matvec's partials, by each wave that calls it, in one order: the
 // scalar step and the first transform pass (DevPlan::fold) get the same bits, so that a
 // batch whose vectors are too large to fold equals its right-hand sides on their own.

@@ -208,7 +208,13 @@ int update_blocks(const DevPlan& P) {
   return (int)want;
 }
 
-hipError_t launch_stencil(const DevPlan& P, int mode, const double* x, double* y, const double* f, hipStream_t s) {
+hipError_t launch_stencil(const DevPlan& plan, int mode, const double* x, double* y, const double* f, hipStream_t s) {
+  DevPlan P = plan;
+  // Without a sum over its blocks the march may depend on the batch too (each value is the
+  // same expression in any chunk): P^{-1} and A of 8 x 255^2 x 8 107.2 -> 104.8 us against
+  // the chunks of 2 levels that one right-hand side takes.  Chunks above 8 levels where the
+  // batch fills the GPU with them gained nothing (64 x 63^2 x 64), so those follow the shape.
+  if (mode == STENCIL_PLAIN || mode == STENCIL_T) stencil_chunk(P, P.B);
   dim3 grid(stencil_grid(P, mode), P.B);
   const dim3 block(P.st_threads);
 #define ABAC_STENCIL_CASE(M)                                                                           \
