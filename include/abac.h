@@ -89,10 +89,11 @@ abac_status abac_plan_tiles(abac_plan *plan, int *wg);
 /* Override the tiles the tuner chose for the plan's first x-DST pass (wg_x), y-DST pass
  * (wg_y, 2D only), time pass (wg_t) and last x-DST pass (wg_xi), in threads per
  * workgroup; 0 keeps the current choice.  Every sequence of the fast transforms of
- * Section 2.3 is computed by the same arithmetic whatever the tile, and the one
- * reduction these passes carry in a MINRES solve (the time pass's partials of
- * <q, P^{-1} q>) is summed in an order fixed by the sequence length, so every legal tile
- * gives bitwise the same results; this call lets a caller (a test) run each one.
+ * Section 2.3 is computed by the same arithmetic whatever the tile, and the reductions
+ * these passes carry in a MINRES solve (the first pass's three inner products for the
+ * stopping test, the time pass's partials of <q, P^{-1} q>) are summed in orders fixed by
+ * the shape, so every legal tile gives bitwise the same results; this call lets a caller
+ * (a test) run each one.
  * ABAC_EINVAL (nothing changed) if a tile is not legal for its kernel (it must be a
  * multiple of 64 and of the threads per sequence, and its LDS must fit the device), if
  * the plan uses the fused x-y passes and wg_x, wg_y or wg_xi is nonzero, for

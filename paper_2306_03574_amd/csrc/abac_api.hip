@@ -68,7 +68,9 @@ struct Layout {
 };
 
 // Whether the partials of the first pass's third inner product fit the GMRES partials' region.
-bool dots_apart(const DevPlan& P) { return (long long)P.nt * P.ny1 / 2 <= (kGmresMax + 1) * kVecMaxBlocks; }
+bool dots_apart(const DevPlan& P) {
+  return (long long)P.nt * P.ny1 / 2 + dot_group_units(64) <= (kGmresMax + 1) * kVecMaxBlocks;
+}
 
 // Validate the problem and fill the size fields of a DevPlan.
 abac_status describe(int nx, int ny, int nt, double T, double alpha, int prec, int batch, DevPlan& P) {
@@ -123,7 +125,7 @@ abac_status describe(int nx, int ny, int nt, double T, double alpha, int prec, i
   P.st_rows = ny && nx >= 2 ? 2 : 1;
   P.st_threads = std::min(kStencilThreads, ((nx + P.st_cols - 1) / P.st_cols + 63) / 64 * 64);
   stencil_chunk(P, 1);
-  P.maxparts = std::max(std::max(stencil_blocks(P), update_blocks(P)), std::max((P.nt * P.ny1 + 1) / 2, P.ms / 2));
+  P.maxparts = std::max(std::max(stencil_blocks(P), update_blocks(P)), std::max(P.nt * P.ny1 / 2 + dot_group_units(64), P.ms / 2));
   P.maxparts = (P.maxparts + 63) & ~63;
   P.prec = prec;
   // Where an iteration is bound by its launches (vectors within the L2s, 32 MB) every wave of
@@ -159,8 +161,8 @@ Layout make_layout(const DevPlan& P, int prec) {
   Lo.scratch = take(prec == ABAC_PREC_NONE ? 0 : real * (size_t)P.NS * P.B);
   for (int i = 0; i < Layout::kVecs; ++i) Lo.vec[i] = take(sizeof(double) * (size_t)P.N * P.B);
   Lo.gst = take(sizeof(GmresState) * P.B);
-  Lo.gparts = take(sizeof(double) * (size_t)(kGmresMax + 1) * kVecMaxBlocks * P.B);
   Lo.st = take(sizeof(MinresState) * P.B);
+  Lo.gparts = take(sizeof(double) * (size_t)(kGmresMax + 1) * kVecMaxBlocks * P.B);
   Lo.partials = take(sizeof(double) * (size_t)P.maxparts * P.B * PART_KINDS);
   Lo.counters = take(sizeof(unsigned) * P.B);
   Lo.total = o;

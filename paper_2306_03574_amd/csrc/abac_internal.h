@@ -207,7 +207,15 @@ __device__ __forceinline__ MinresExt* minres_ext(const DevPlan& P, int b) {
 
 // The inner products a block of the first transform pass forms for the stopping test
 // (see MinresExt): <q, q>, then <q, V_j> and <q, V_{j-1}>, or with the residual tracked
-// <q, r_{j-1}> and ||r_{j-1}||^2.  One partial each per block.
+// <q, r_{j-1}> and ||r_{j-1}||^2.  They are summed in one order, whatever the tile, so that
+// tuned, batched and grouped solves take the same decisions: a wave sums a unit of 64 / TPS row
+// pairs (TPS threads to a sequence; TPS / 64 waves a unit of one row pair where TPS > 64),
+// units are added two by two up to a group of twice those of a 1024-thread block, partly by
+// the block, which leaves one partial of the units it has, partly by the scalar step, which
+// then sums the groups.  In the fused x-y passes the unit is a level, the group two of them.
+// Partials per block summed as they come, so that the tile decides, take the scalar step as
+// long at 255^2 x 256 FP64 (10.5 us), 5 us less at 511^2 x 512 FP32 (25 and 20 us).
+__host__ __device__ constexpr int dot_group_units(int tps) { return 2048 / (tps > 64 ? tps : 64); }
 struct Dots3 {
   double a, b, c;
 };
@@ -215,9 +223,17 @@ __device__ __forceinline__ double* dot_slot(const DevPlan& P, int which, int b) 
   return which == 0 ? part_slot(P, PART_RNORM, b) : which == 1 ? part_slot(P, PART_RES, b) : P.dot3 + b * P.dot3_stride;
 }
 
-// First half of the block sum of three values: every wave leaves its sums in LDS (the
-// caller places the barrier).  Second half, thread 0: the block's partials.
-__device__ __forceinline__ void dots_reduce(Dots3 d, double (*red)[3]) {
+template <int N>
+__device__ __forceinline__ double tree_sum(double* v) {
+#pragma unroll
+  for (int d = 1; d < N; d *= 2)
+#pragma unroll
+    for (int i = 0; i < N; i += 2 * d) v[i] += v[i + d];
+  return v[0];
+}
+
+// Every wave leaves its sums of three values in `red` (the caller places the barrier).
+__device__ __forceinline__ void dots_reduce(Dots3 d, double* red) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     d.a += __shfl_down(d.a, off, 64);
@@ -225,17 +241,30 @@ __device__ __forceinline__ void dots_reduce(Dots3 d, double (*red)[3]) {
     d.c += __shfl_down(d.c, off, 64);
   }
   if ((threadIdx.x & 63) == 0) {
-    double* r = red[threadIdx.x >> 6];
-    r[0] = d.a;
-    r[1] = d.b;
-    r[2] = d.c;
+    red[0] = d.a;
+    red[1] = d.b;
+    red[2] = d.c;
   }
 }
-__device__ __forceinline__ void dots_store(const DevPlan& P, int b, int blk, const double (*red)[3]) {
+// Where partial i of n in groups of `group` lies: the pairs of a group `groups` apart, so that
+// consecutive threads of the scalar step read consecutive groups.
+__device__ __forceinline__ int dot_place(int i, int n, int group) {
+  const int groups = (n + group - 1) / group, g = i / group, j = i - g * group;
+  return ((j >> 1) * groups + g) * 2 + (j & 1);
+}
+
+// The partial of block blk of n, from the sums of UNITS units of WAVES waves each.
+template <int UNITS, int WAVES>
+__device__ __forceinline__ void dots_store(const DevPlan& P, int b, int blk, int n, int group, const double (*red)[3]) {
   if (threadIdx.x < 3) {
-    double s = 0.0;
-    for (int w = 0; w < (int)(blockDim.x + 63) >> 6; ++w) s += red[w][threadIdx.x];
-    dot_slot(P, threadIdx.x, b)[blk] = s;
+    double s[UNITS];
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      s[u] = red[u * WAVES][threadIdx.x];
+#pragma unroll
+      for (int w = 1; w < WAVES; ++w) s[u] += red[u * WAVES + w][threadIdx.x];
+    }
+    dot_slot(P, threadIdx.x, b)[dot_place(blk, n, group)] = tree_sum<UNITS>(s);
   }
 }
 
@@ -278,6 +307,51 @@ __device__ __forceinline__ double parts_share(const double* __restrict__ part, i
   }
   if ((n & 1) && t == 0) s += part[n - 1];
   return s;
+}
+
+// The same of three times n partials in groups of 2 H = 2 Q steps (dot_place; what is missing of
+// the last group counts as 0), four pairs of each at a time: of 4 / Q groups, or with Q = 4 a
+// whole, a half or a quarter of one (steps 1, 2 or 4).
+template <int Q>
+__device__ __forceinline__ Dots3 group_share(const double* const (&part)[3], int n, int steps, int t, int nt) {
+  const int H = Q < 4 ? Q : 4 * steps, groups = (n + 2 * H - 1) / (2 * H);
+  double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll 1
+  for (int g0 = t; g0 < groups; g0 += 4 / Q * nt) {
+    double even[3], half[3];
+#pragma unroll 1
+    for (int st = 0; st < (Q < 4 ? 1 : steps); ++st) {
+      double2 v[3][4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const unsigned at = (st * Q + q % Q) * groups + min(g0 + q / Q * nt, groups - 1);
+#pragma unroll
+        for (int r = 0; r < 3; ++r) v[r][q] = reinterpret_cast<const double2*>(part[r])[at];
+      }
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        double w[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int i = 2 * ((g0 + q / Q * nt) * H + st * Q + q % Q);
+          w[q] = (i < n ? v[r][q].x : 0.0) + (i + 1 < n ? v[r][q].y : 0.0);
+        }
+        if constexpr (Q < 4) {
+#pragma unroll
+          for (int u = 0; u < 4 / Q; ++u)
+            if (g0 + u * nt < groups) s[r] += tree_sum<Q>(w + u * Q);
+        } else {
+          double x = tree_sum<4>(w);
+          if (st & 1) x += even[r];
+          if (st == 3) x += half[r];
+          if (st == steps - 1) s[r] += x;
+          else if (st & 1) half[r] = x;
+          else even[r] = x;
+        }
+      }
+    }
+  }
+  return {s[0], s[1], s[2]};
 }
 
 __device__ __forceinline__ double sum_parts(const double* __restrict__ part, int n) {
@@ -401,7 +475,12 @@ __device__ __forceinline__ double delta_sum(const DevPlan& P, int b) {
 
 int stencil_grid(const DevPlan& P, int mode);
 int update_blocks(const DevPlan& P);
-int dstx_blocks(const DevPlan& P, int wg);
+// the first pass's partials of an inner product per right-hand side with tiles of wg threads,
+// and how many of them make a group
+struct DotParts {
+  int n, group;
+};
+DotParts dot_parts(const DevPlan& P, int wg);
 
 hipError_t launch_stencil(const DevPlan& P, int mode, const double* x, double* y, const double* f, hipStream_t s);
 hipError_t launch_rhs(const DevPlan& P, const double* src, const double* psi0, const double* psi1, double* f,

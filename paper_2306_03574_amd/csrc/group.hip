@@ -45,6 +45,7 @@ struct GroupMember {
   DevPlan P;
   const double* f;
   double* u;
+  DotParts dots;
 };
 
 // Device table of a group: the members and, per step, the first block of each member
@@ -165,7 +166,7 @@ __device__ __forceinline__ void group_fin(const GroupTable* __restrict__ G, int 
     default: nparts = stencil_blocks(P); break;
   }
   fin_step(P, at.b, kind, FinArgs{}, [&](Dots3* dots) {
-    if (kind == FIN_GAMMA_ITER) *dots = sum_dots(P, at.b, (G->off[GS_XFWD][at.r + 1] - G->off[GS_XFWD][at.r]) / P.B);
+    if (kind == FIN_GAMMA_ITER) *dots = sum_dots(P, at.b, G->m[at.r].dots);
     if (kind == FIN_DELTA) return threadIdx.x < 64 ? delta_sum(P, at.b) : 0.0;
     return sum_parts_as(part_slot(P, fin_part_kind(kind), at.b), nparts, kGroupFinThreads);
   });
@@ -631,6 +632,7 @@ abac_status abac_group_set(abac_group* g, abac_plan* const* plans, int n) {
     H.m[r].P = p->P;
     H.m[r].f = p->f;
     H.m[r].u = p->u;
+    H.m[r].dots = dot_parts(p->P, kGroupWG);
     for (int k = 0; k < GS_COUNT; ++k) {
       H.off[k][r] = total[k];
       total[k] += blocks[k] * p->P.B;

@@ -305,7 +305,7 @@ struct SmallRun {
           }
         }
       }
-      dots_reduce(d, dred);
+      dots_reduce(d, dred[tid >> 6]);
       __syncthreads();
       x_pass<false>();
       tot = time_pass();

@@ -182,10 +182,8 @@ k_identity(DevPlan P, int mode, const double* __restrict__ in, double* __restric
   if (threadIdx.x == 0) part_slot(P, PART_GAMMA, b)[blockIdx.x] = bs;
 }
 
-constexpr int kFinThreads = 1024;
-
 __global__ void __launch_bounds__(kFinThreads)
-k_fin(DevPlan P, int kind, int nparts, int ndots, FinArgs a) {
+k_fin(DevPlan P, int kind, int nparts, DotParts ndots, FinArgs a) {
   const int b = blockIdx.x;
   fin_step(P, b, kind, a, [&](Dots3* dots) {
     if (kind == FIN_GAMMA_ITER) *dots = sum_dots(P, b, ndots);
@@ -279,8 +277,7 @@ hipError_t launch_fin(const DevPlan& P, int kind, const FinArgs& a, hipStream_t 
     case FIN_GAMMA_ITER: nparts = P.gamma_nparts; break;
     default: nparts = stencil_grid(P, STENCIL_RESIDUAL); break;
   }
-  // blocks of the first transform pass, which leave the inner products' partials
-  const int ndots = kind != FIN_GAMMA_ITER || P.prec == 2 ? 0 : P.wg_s ? P.nt : dstx_blocks(P, P.wg_x);
+  const DotParts ndots = kind == FIN_GAMMA_ITER && P.prec != 2 ? dot_parts(P, P.wg_x) : DotParts{0, 2};
   hipLaunchKernelGGL(k_fin, dim3(P.B), dim3(kFinThreads), 0, s, P, kind, nparts, ndots, a);
   return hipGetLastError();
 }

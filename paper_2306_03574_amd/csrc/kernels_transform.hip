@@ -341,10 +341,10 @@ template <typename T> int transform_tps_t(int L) {
 
 int transform_tps(int L, int prec) { return prec == 1 ? transform_tps_t<float>(L) : transform_tps_t<double>(L); }
 
-int dstx_blocks(const DevPlan& P, int wg) {
-  const int S = wg / transform_tps(2 * P.Mx, P.prec);
-  const int rows = P.nt * P.ny1;
-  return (rows + 2 * S - 1) / (2 * S);
+DotParts dot_parts(const DevPlan& P, int wg) {
+  if (P.wg_s) return {P.nt, 2};
+  const int tps = transform_tps(2 * P.Mx, P.prec), S = wg / tps;
+  return {(P.nt * P.ny1 / 2 + S - 1) / S, dot_group_units(tps) / (wg / std::max(tps, 64))};
 }
 
 size_t transform_lds_bytes(int kind, int L, int wg, int prec) {

@@ -10,6 +10,7 @@ namespace abac {
 namespace {
 
 constexpr int kFormTrips = kVecPerThread / 2;
+constexpr int kFinThreads = 1024;   // threads of a scalar step
 
 // u = [u +] sum_l xm_l z_l over the NB vectors of the current cycle, plus the two carried
 // w vectors of a later cycle; with FLUSH also W[0] = w_j and W[1] = w_{j-1} from their
@@ -265,17 +266,23 @@ __device__ __forceinline__ int fin_part_kind(int kind) {
   }
 }
 
-// Sums of the n partials of the first transform pass's inner products; valid in thread 0.
-__device__ __forceinline__ Dots3 sum_dots(const DevPlan& P, int b, int n) {
-  __shared__ double red[16][3];
-  const double *pa = dot_slot(P, 0, b), *pb = dot_slot(P, 1, b), *pc = dot_slot(P, 2, b);
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const Dots3 d{parts_share(pa, n, tid, nt), parts_share(pb, n, tid, nt), parts_share(pc, n, tid, nt)};
-  dots_reduce(d, red);
+// Sums of the partials of the first transform pass's inner products; valid in thread 0.  In the
+// order of kFinThreads threads, whatever the block has (a divisor of them, whole waves), so
+// that every kernel's scalar step gets the same bits.
+__device__ __forceinline__ Dots3 sum_dots(const DevPlan& P, int b, DotParts parts) {
+  __shared__ double red[kFinThreads / 64][3];
+  const double* const part[3] = {dot_slot(P, 0, b), dot_slot(P, 1, b), dot_slot(P, 2, b)};
+  auto sum = [&](auto pairs) {
+    for (int t = threadIdx.x; t < kFinThreads; t += blockDim.x)
+      dots_reduce(group_share<decltype(pairs)::value>(part, parts.n, parts.group / 8, t, kFinThreads), red[t >> 6]);
+  };
+  if (parts.group >= 8) sum(std::integral_constant<int, 4>{});
+  else if (parts.group == 4) sum(std::integral_constant<int, 2>{});
+  else sum(std::integral_constant<int, 1>{});
   __syncthreads();
   Dots3 t{0.0, 0.0, 0.0};
   if (threadIdx.x == 0) {
-    for (int w = 0; w < (int)(blockDim.x + 63) >> 6; ++w) {
+    for (int w = 0; w < kFinThreads / 64; ++w) {
       t.a += red[w][0];
       t.b += red[w][1];
       t.c += red[w][2];

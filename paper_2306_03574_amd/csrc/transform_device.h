@@ -244,41 +244,54 @@ __device__ __forceinline__ void dstx_fwd_tile(const DevPlan& P, int mode, const 
   // is even), twelve 16-byte loads at a time: where the accesses are marked (stream_branch) 129 -> 121 us
   // at 255^2 x 256 FP64, 940 -> 905 us at 511^2 x 512 FP32 and 1055 -> 890 us for 64 x
   // 127^2 x 128 FP64, against 8-byte plain loads.
+  // UW threads take UP row pairs, the unit of the inner products (Dots3), in R / 2 trips of UW
+  // pairs that start at a cache line of the right-hand side: what the unit has ahead of its
+  // first line's start comes last.  64 x 127^2 x 128 FP64 takes 790 us (trips from each row
+  // pair's start, across the lines: 866), 255^2 x 256 FP64 109 us and 511^2 x 512 FP32 785
+  // us (115 and 805 with the block's trips one after the other from the tile's start).
   constexpr int BATCH = R / 2 < 4 ? R / 2 : 4;
+  constexpr int UW = TPS > 64 ? TPS : 64, UP = UW / TPS;
   if (mode == FWD_LANCZOS) {
     const LanczosStep step(P, b);
     Dots3 d{0.0, 0.0, 0.0};
+    constexpr int pairs = UP * (Mx - 1), slots = UP * Mx;
+    const int unit = threadIdx.x / UW, ut = threadIdx.x % UW;
+    const int ahead = (tile * (WG / UW) + unit) * pairs & 7;   // pairs between a line's start and the unit
     auto sweep = [&](auto stream) {
 #pragma unroll
       for (int u0 = 0; u0 < R / 2; u0 += BATCH) {
+        int i[BATCH];
         size_t e[BATCH];
         bool live[BATCH];
         dpair q[BATCH];
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
-          const int i = 2 * ((int)threadIdx.x + (u0 + u) * WG);
-          live[u] = i < cnt;
-          e[u] = base + min(i, cnt - 2);
+          const int g = (ut + (u0 + u) * UW - ahead) & (slots - 1);
+          i[u] = 2 * (unit * pairs + g);
+          live[u] = g < pairs && i[u] < cnt;
+          e[u] = base + min(i[u], cnt - 2);
         }
         step.run<BATCH, decltype(stream)::value>(e, live, q, d);
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
-          const int i = 2 * ((int)threadIdx.x + (u0 + u) * WG);
           if (live[u]) {
-            stage[i] = (T)q[u].x;
-            stage[i + 1] = (T)q[u].y;
+            stage[i[u]] = (T)q[u].x;
+            stage[i[u] + 1] = (T)q[u].y;
           }
         }
       }
     };
     stream_branch(P.stream, sweep);
     step.publish(P, b, tile);
-    dots_reduce(d, dred);
+    dots_reduce(d, dred[threadIdx.x >> 6]);
   } else {
     stage_in<R, WG>(stage, in + (size_t)b * P.N + base, cnt, P.stream);
   }
   __syncthreads();
-  if (mode == FWD_LANCZOS) dots_store(P, b, tile, dred);
+  if (mode == FWD_LANCZOS) {
+    constexpr int units = WG / UW;
+    dots_store<units, UW / 64>(P, b, tile, (P.nt * P.ny1 / 2 + S - 1) / S, dot_group_units(TPS) / units, dred);
+  }
   const int s = threadIdx.x % S, j = threadIdx.x / S;
   const int ra = 2 * s, rb = 2 * s + 1;
   const bool va = ra < nrows, vb = rb < nrows;
@@ -692,6 +705,9 @@ constexpr size_t slab_bytes() {
   return ((size_t)(L / 2 - 1) * (L / 2 + 1) * sizeof(T) + 15) / 16 * 16;
 }
 
+// parts of a level's inner products (Dots3): the waves of the largest workgroup slab_wg gives
+constexpr int kSlabParts = 8;
+
 template <typename T, int L, int WG>
 constexpr size_t slab_lds_of() {
   return slab_bytes<T, L>() + (size_t)seqs_of<T, L, WG>() * L * sizeof(cplx<T>);
@@ -773,34 +789,43 @@ __device__ __forceinline__ void dst2_fwd_tile(const DevPlan& P, int mode, const 
   };
   if (mode == FWD_LANCZOS) {
     const LanczosStep step(P, b);
-    Dots3 d{0.0, 0.0, 0.0};
     constexpr int PB = BATCH / 2;
+    // the level in kSlabParts parts, whatever the workgroup: part w has the pairs of lanes
+    // 64 w .. 64 w + 63 of 64 kSlabParts, summed by one wave (t opaque: the parts' addresses
+    // hoisted out of the loop over them take 196 registers for 139)
     auto sweep = [&](auto stream) {
-      for (int e0 = 0; e0 + 1 < cnt; e0 += 2 * PB * WG) {
-        size_t e[PB];
-        bool live[PB];
-        dpair q[PB];
+#pragma unroll 1
+      for (int w = threadIdx.x >> 6; w < kSlabParts; w += WG / 64) {
+        Dots3 d{0.0, 0.0, 0.0};
+        int t = 64 * w + (threadIdx.x & 63);
+        asm volatile("" : "+v"(t));
+#pragma unroll 1
+        for (int e0 = 0; e0 + 1 < cnt; e0 += 2 * PB * 64 * kSlabParts) {
+          size_t e[PB];
+          bool live[PB];
+          dpair q[PB];
 #pragma unroll
-        for (int u = 0; u < PB; ++u) {
-          const int i = e0 + 2 * ((int)threadIdx.x + u * WG);
-          live[u] = i + 1 < cnt;
-          e[u] = base + min(i, cnt - 2);
-        }
-        step.run<PB, decltype(stream)::value>(e, live, q, d);
+          for (int u = 0; u < PB; ++u) {
+            const int i = e0 + 2 * (t + u * 64 * kSlabParts);
+            live[u] = i + 1 < cnt;
+            e[u] = base + min(i, cnt - 2);
+          }
+          step.run<PB, decltype(stream)::value>(e, live, q, d);
 #pragma unroll
-        for (int u = 0; u < PB; ++u) {
-          const int i = e0 + 2 * ((int)threadIdx.x + u * WG);
-          if (live[u]) {
-            put(i, q[u].x);
-            put(i + 1, q[u].y);
+          for (int u = 0; u < PB; ++u) {
+            const int i = e0 + 2 * (t + u * 64 * kSlabParts);
+            if (live[u]) {
+              put(i, q[u].x);
+              put(i + 1, q[u].y);
+            }
           }
         }
+        if (t == 0) put(cnt - 1, step.run1(base + cnt - 1, d));   // cnt = nx^2 is odd
+        dots_reduce(d, dred[w]);
       }
     };
     stream_branch(P.stream, sweep);
-    if (threadIdx.x == 0) put(cnt - 1, step.run1(base + cnt - 1, d));   // cnt = nx^2 is odd
     step.publish(P, b, lvl);
-    dots_reduce(d, dred);
   } else {
     const double* src = in + (size_t)b * P.N + base;
     for (int e0 = 0; e0 < cnt; e0 += BATCH * WG) {
@@ -815,7 +840,7 @@ __device__ __forceinline__ void dst2_fwd_tile(const DevPlan& P, int mode, const 
     }
   }
   __syncthreads();
-  if (mode == FWD_LANCZOS) dots_store(P, b, lvl, dred);
+  if (mode == FWD_LANCZOS) dots_store<1, kSlabParts>(P, b, lvl, P.nt, 2, dred);
   slab_dst<T, L, WG, true>(slab, nx, exch, reinterpret_cast<const C*>(P.twx));
   slab_dst<T, L, WG, false>(slab, M, exch, reinterpret_cast<const C*>(P.twy));
   T* out = reinterpret_cast<T*>(P.scratch) + (size_t)b * P.NS + (size_t)lvl * P.ms;
