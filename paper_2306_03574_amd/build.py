@@ -36,6 +36,40 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
+# A conditional branch reaches 2^15 instruction words either way.  Past that the compiler goes
+# by a long branch through a free register pair, and in a device function that calls nothing it
+# has taken the pair that holds the return address, so that the function never returned.
+BRANCH_REACH = 1 << 17
+
+
+def overlong_functions(symbols: str) -> list[str]:
+    """The device functions (not kernels) of a code object that a branch may not span, from its
+    symbol table as llvm-readelf -sW prints it."""
+    rows = [r.split() for r in symbols.splitlines()]
+    rows = [r for r in rows if len(r) == 8 and r[0].endswith(":") and r[3] in ("FUNC", "OBJECT")]
+    kernels = {r[7][:-len(".kd")] for r in rows if r[3] == "OBJECT" and r[7].endswith(".kd")}
+    return sorted({r[7] for r in rows if r[3] == "FUNC" and int(r[2]) >= BRANCH_REACH and r[7] not in kernels})
+
+
+def device_symbols(obj: str) -> str:
+    """The symbol table of the gfx950 code in an object file that hipcc wrote ("" if it has none)."""
+    tools = os.path.join(os.path.dirname(os.path.realpath(hipcc())), "..", "llvm", "bin")
+    fat, code = obj + ".fat", obj + ".code"
+
+    def tool(name, *args):
+        res = subprocess.run([os.path.join(tools, name), *args], capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError(f"{name} failed on {obj}: {res.stderr}")
+        return res.stdout
+
+    if ".hip_fatbin " not in tool("llvm-readelf", "-SW", obj):
+        return ""
+    tool("llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", obj, os.devnull)
+    tool("clang-offload-bundler", "--unbundle", "--type=o", f"--input={fat}", f"--output={code}",
+         "--targets=hipv4-amdgcn-amd-amdhsa--gfx950")
+    return tool("llvm-readelf", "-sW", code)
+
+
 def build(verbose: bool = False, csrc: str = CSRC, lib: str = LIB) -> str:
     """Compile every source into libabac.so (always recompiles).  The translation
     units compile in parallel to objects in a temporary folder, then link."""
@@ -56,6 +90,9 @@ def build(verbose: bool = False, csrc: str = CSRC, lib: str = LIB) -> str:
             if res.returncode != 0:
                 sys.stderr.write(res.stdout + res.stderr)
                 raise RuntimeError(f"hipcc failed compiling {c[-3]}")
+        for o in objs:
+            if long := overlong_functions(device_symbols(o)):
+                raise RuntimeError(f"device functions past the reach of a branch ({BRANCH_REACH} bytes): {long}")
         tmp = lib + ".tmp"
         link = [cc, "-shared", "-fPIC", "--offload-arch=gfx950"] + objs + ["-o", tmp]
         if verbose:

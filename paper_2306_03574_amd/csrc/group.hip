@@ -193,7 +193,8 @@ __device__ __forceinline__ void group_form(const GroupTable* __restrict__ G, int
 // so that each tile gets the registers of its own.  One function per length, not one
 // for a pass with all its lengths: past 128 KB of code the compiler reaches a function's end
 // by a long branch through s[30:31], which hold the return address of a function that calls
-// nothing, and the function then never returns.
+// nothing, and the function then never returns.  The build refuses such a function; the
+// largest here takes 42 KB.
 template <typename T, int LL>
 __device__ __forceinline__ void tile_slab_fwd(const DevPlan& P, int b, int lbk) {
   if constexpr (slab_ok<T, LL, kGroupWG>()) dst2_fwd_tile<T, LL, kGroupWG>(P, FWD_LANCZOS, nullptr, b, lbk);
