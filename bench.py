@@ -94,12 +94,18 @@ def algorithmic_bytes(w, prec, iters_total, solves, fused=False, resident=False)
     With `fused` (small 1D plans: one launch per solve, one workgroup per right-hand side
     runs the set-up with its first preconditioner apply and every iteration) all of the
     above is the "iter" class.
+    With both, the workgroup keeps z, the scratch and the matvec's output in LDS: 32 N per
+    iteration (read v_j, v_{j-1}; write q, z_{j+1}, the last not in the iteration a solve
+    stops in), 8 (k+1) N to form u and 8 N to check it (read f) once per solve, 32 N for the
+    set-up (read f; write v1, u, z_1).
     """
     nx, ny, nt = w["nx"], w["ny"], w["nt"]
     N = nt * nx * max(ny, 1)
     NS = nt * (nx + 1) * max(ny, 1)
     s = 8 if prec == "fp64" else 4
     applies = iters_total + solves
+    if fused and resident:
+        return {"iter": 32 * N * iters_total - 8 * N * solves + 8 * N * (iters_total + solves) + (8 + 32) * N * solves}
     if fused:
         per_iter = 16 * N + (32 * N + s * NS) + 2 * s * NS + (s * NS + 8 * N) + 24 * N
         setup = 24 * N + (8 * N + s * NS) + 2 * s * NS + (s * NS + 8 * N)
