@@ -63,8 +63,7 @@ int default_wg(int kind, int L, int prec, int maxlds) {
 struct Layout {
   // vectors: V x3, Z x kZSlots, W x2, R
   static constexpr int kVecs = 3 + kZSlots + 2 + 1;
-  size_t twx, twy, twt, beta, abk, sc, sci, coef, scratch, vec[kVecs], gst, gparts, st, partials,
-      counters, total;
+  size_t twx, twy, twt, beta, abk, sc, sci, coef, scratch, vec[kVecs], gst, gparts, st, partials, total;
 };
 
 // Whether the partials of the first pass's third inner product fit the GMRES partials' region.
@@ -164,7 +163,6 @@ Layout make_layout(const DevPlan& P, int prec) {
   Lo.st = take(sizeof(MinresState) * P.B);
   Lo.gparts = take(sizeof(double) * (size_t)(kGmresMax + 1) * kVecMaxBlocks * P.B);
   Lo.partials = take(sizeof(double) * (size_t)P.maxparts * P.B * PART_KINDS);
-  Lo.counters = take(sizeof(unsigned) * P.B);
   Lo.total = o;
   return Lo;
 }
@@ -806,7 +804,6 @@ abac_status abac_plan_create(int nx, int ny, int nt, double T, double alpha, int
     P.dot3 = P.partials + (size_t)PART_DELTA * P.B * P.maxparts;
     P.dot3_stride = P.maxparts;
   }
-  P.counters = reinterpret_cast<unsigned*>(base + Lo.counters);
   P.coef_x = nullptr;   // constant coefficient until abac_plan_set_coefficient
   P.coef_y = nullptr;
 
@@ -843,7 +840,6 @@ abac_status abac_plan_create(int nx, int ny, int nt, double T, double alpha, int
   if (e == hipSuccess) e = upload(P.abk, abk);
   if (e == hipSuccess) e = upload(P.sc, sc);
   if (e == hipSuccess) e = upload(P.sci, sci);
-  if (e == hipSuccess) e = hipMemset(P.counters, 0, sizeof(unsigned) * batch);
   if (e == hipSuccess) e = hipMemset(P.st, 0, sizeof(MinresState) * batch);
   if (e == hipSuccess && prec != ABAC_PREC_NONE)
     e = hipMemset(P.scratch, 0, (prec ? 4 : 8) * (size_t)P.NS * batch);

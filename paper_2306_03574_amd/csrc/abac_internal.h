@@ -175,7 +175,6 @@ struct DevPlan {
   long long dot3_stride;   // doubles per right-hand side
   MinresState* st;     // B entries
   double* partials;    // PART_KINDS * B * maxparts
-  unsigned* counters;  // B entries
   Snapshot* host_ring;     // device view of the host-mapped snapshot ring (kSnapRing * B)
   int maxparts;
   // workgroup sizes of the transform kernels (chosen by the plan's autotuner)

@@ -106,17 +106,17 @@ __device__ __forceinline__ void group_stencil(const GroupTable* __restrict__ G, 
       const double* f = M.f + off;
       double* y = P.R + off;
       if (st->want_r)
-        acc = P.coef_x ? stencil_run<true, OUT_RESREV, false>(P, x, y, f, blk, nblk, tx, true)
-                       : stencil_run<false, OUT_RESREV, false>(P, x, y, f, blk, nblk, tx, true);
+        acc = P.coef_x ? stencil_run<true, OUT_RESREV, false>(P, x, y, f, blk, nblk, tx)
+                       : stencil_run<false, OUT_RESREV, false>(P, x, y, f, blk, nblk, tx);
       else
-        acc = P.coef_x ? stencil_run<true, OUT_RESNORM, false>(P, x, nullptr, f, blk, nblk, tx, true)
-                       : stencil_run<false, OUT_RESNORM, false>(P, x, nullptr, f, blk, nblk, tx, true);
+        acc = P.coef_x ? stencil_run<true, OUT_RESNORM, false>(P, x, nullptr, f, blk, nblk, tx)
+                       : stencil_run<false, OUT_RESNORM, false>(P, x, nullptr, f, blk, nblk, tx);
     } else {
       const int j = st->iter + 1;
       const double* x = P.Z[zslot(j)] + off;
       double* y = P.V[(j + 1) % 3] + off;
-      acc = P.coef_x ? stencil_run<true, OUT_REV, true>(P, x, y, nullptr, blk, nblk, tx, true)
-                     : stencil_run<false, OUT_REV, true>(P, x, y, nullptr, blk, nblk, tx, true);
+      acc = P.coef_x ? stencil_run<true, OUT_REV, true>(P, x, y, nullptr, blk, nblk, tx)
+                     : stencil_run<false, OUT_REV, true>(P, x, y, nullptr, blk, nblk, tx);
     }
   }
 #pragma unroll
@@ -158,13 +158,7 @@ __device__ __forceinline__ void group_fin(const GroupTable* __restrict__ G, int 
   const Where at = locate(G, GS_FIN, w);
   const DevPlan& P = G->m[at.r].P;
   if (kind == FIN_DELTA && P.fold) return;
-  int nparts;
-  switch (kind) {
-    case FIN_DELTA: nparts = stencil_blocks(P); break;
-    case FIN_GAMMA_INIT:
-    case FIN_GAMMA_ITER: nparts = P.gamma_nparts; break;
-    default: nparts = stencil_blocks(P); break;
-  }
+  const int nparts = kind == FIN_GAMMA_ITER ? P.gamma_nparts : stencil_blocks(P);
   fin_step(P, at.b, kind, FinArgs{}, [&](Dots3* dots) {
     if (kind == FIN_GAMMA_ITER) *dots = sum_dots(P, at.b, G->m[at.r].dots);
     if (kind == FIN_DELTA) return threadIdx.x < 64 ? delta_sum(P, at.b) : 0.0;
@@ -202,7 +196,7 @@ __device__ __forceinline__ void tile_slab_fwd(const DevPlan& P, int b, int lbk) 
 template <typename T, int LL>
 __device__ __forceinline__ void tile_xfwd(const DevPlan& P, int b, int lbk) {
   if constexpr (tile_ok<T, LL, kGroupWG, TK_XFWD>())
-    dstx_fwd_tile<T, LL, kGroupWG>(P, FWD_LANCZOS, nullptr, b, lbk, reinterpret_cast<const cplx<T>*>(P.twx));
+    dstx_fwd_tile<T, LL, kGroupWG>(P, FWD_LANCZOS, nullptr, b, lbk);
 }
 template <typename T, int LL>
 __device__ __forceinline__ void tile_y(const DevPlan& P, int b, int lbk) {
@@ -219,7 +213,7 @@ __device__ __forceinline__ void tile_slab_inv(const DevPlan& P, int b, int lbk) 
 template <typename T, int LL>
 __device__ __forceinline__ void tile_xinv(const DevPlan& P, int b, int lbk) {
   if constexpr (tile_ok<T, LL, kGroupWG, TK_XINV>())
-    dstx_inv_tile<T, LL, kGroupWG>(P, INV_Z_ITER, nullptr, b, lbk, reinterpret_cast<const cplx<T>*>(P.twx));
+    dstx_inv_tile<T, LL, kGroupWG>(P, INV_Z_ITER, nullptr, b, lbk);
 }
 #define ABAC_FAR(NAME)                                                              \
   template <typename T, int LL>                                                     \

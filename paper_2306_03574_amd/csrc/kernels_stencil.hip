@@ -38,22 +38,22 @@ k_stencil(DevPlan P, const double* __restrict__ xin, double* __restrict__ yout, 
   if (y) y += (size_t)b * P.N;
   const double* f = fref ? fref + (size_t)b * P.N : nullptr;
   if (MODE == STENCIL_PLAIN) {
-    stencil_run<VAR, OUT_REV, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x, true);
+    stencil_run<VAR, OUT_REV, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x);
     return;
   }
   if (MODE == STENCIL_T) {
-    stencil_run<VAR, OUT_NAT, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x, true);
+    stencil_run<VAR, OUT_NAT, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x);
     return;
   }
   double acc;
   if (MODE == STENCIL_RESIDUAL && st->want_r)
-    acc = stencil_run<VAR, OUT_RESREV, false>(P, x, P.R + (size_t)b * P.N, f, blockIdx.x, gridDim.x, threadIdx.x, true);
+    acc = stencil_run<VAR, OUT_RESREV, false>(P, x, P.R + (size_t)b * P.N, f, blockIdx.x, gridDim.x, threadIdx.x);
   else if (MODE == STENCIL_MINRES)
-    acc = stencil_run<VAR, OUT_REV, true>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x, true);
+    acc = stencil_run<VAR, OUT_REV, true>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x);
   else if (MODE == STENCIL_RESVEC)
-    acc = stencil_run<VAR, OUT_RESVEC, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x, true);
+    acc = stencil_run<VAR, OUT_RESVEC, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x);
   else
-    acc = stencil_run<VAR, OUT_RESNORM, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x, true);
+    acc = stencil_run<VAR, OUT_RESNORM, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x);
   const double bs = block_sum(acc);
   if (threadIdx.x == 0) part_slot(P, MODE == STENCIL_MINRES ? PART_DELTA : PART_RES, b)[blockIdx.x] = bs;
 }
@@ -272,7 +272,6 @@ hipError_t launch_fin(const DevPlan& P, int kind, const FinArgs& a, hipStream_t 
   int nparts;
   switch (kind) {
     case FIN_BNORM: nparts = update_blocks(P); break;
-    case FIN_DELTA: nparts = stencil_grid(P, STENCIL_MINRES); break;
     case FIN_GAMMA_INIT:
     case FIN_GAMMA_ITER: nparts = P.gamma_nparts; break;
     default: nparts = stencil_grid(P, STENCIL_RESIDUAL); break;

@@ -30,7 +30,7 @@ template <typename T, int L, int WG>
 __global__ void __launch_bounds__(WG)
 k_dstx_fwd(DevPlan P, int mode, int check, const double* __restrict__ in) {
   if (!pass_runs(P.st + blockIdx.y, check)) return;
-  dstx_fwd_tile<T, L, WG>(P, mode, in, blockIdx.y, blockIdx.x, reinterpret_cast<const cplx<T>*>(P.twx));
+  dstx_fwd_tile<T, L, WG>(P, mode, in, blockIdx.y, blockIdx.x);
 }
 
 template <typename T, int L, int WG>
@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(WG)
 k_dstx_inv(DevPlan P, int mode, int check, double* __restrict__ outp) {
   const int b = blockIdx.y;
   if (!pass_runs(P.st + b, check)) return;
-  dstx_inv_tile<T, L, WG>(P, mode, outp, b, blockIdx.x, reinterpret_cast<const cplx<T>*>(P.twx));
+  dstx_inv_tile<T, L, WG>(P, mode, outp, b, blockIdx.x);
 }
 
 // fused 2D passes (square grids whose level fits in LDS; tile bodies in

@@ -376,24 +376,22 @@ __device__ __forceinline__ double stencil_tile2(const DevPlan& P, const double* 
 }
 
 // Logical blocks first, first + stride, ... of one right-hand side, lane tx of each
-// (the kernels: one logical block per workgroup, grid-stride, in XCD-aware order so that
-// consecutive logical blocks, neighbouring column tiles and bands of the same levels,
-// share an L2; the fused small-problem iteration: several logical blocks side by side
-// in one workgroup, in natural order).  A block covers st_threads * st_cols columns:
+// (in XCD-aware order, so that consecutive logical blocks, neighbouring column tiles and
+// bands of the same levels, share an L2).  A block covers st_threads * st_cols columns:
 // with two columns per thread the constant-coefficient tile takes columns
 // (2 tx, 2 tx + 1) of its tile, the variable-coefficient tile marches columns tx and
 // st_threads + tx one after the other.
 template <int RB, bool VAR, int OUT, bool DOT>
 __device__ __forceinline__ double stencil_run_rb(const DevPlan& P, const double* __restrict__ x,
                                                  double* __restrict__ y, const double* __restrict__ f, int first,
-                                                 int stride, int tx, bool remap) {
+                                                 int stride, int tx) {
   const int cols = P.st_threads * P.st_cols;
   const int xtiles = (P.nx + cols - 1) / cols;
   const int tiles = ((P.ny1 + RB - 1) / RB) * xtiles;
   const int nblk = stencil_blocks(P);
   double acc = 0.0;
   for (int w = first; w < nblk; w += stride) {
-    const int lb = remap ? xcd_remap(w, nblk) : w;
+    const int lb = xcd_remap(w, nblk);
     const int tile = lb % tiles;
     const int band = tile / xtiles, c0 = (tile % xtiles) * cols, chunk = lb / tiles;
     if constexpr (!VAR) {
@@ -410,10 +408,9 @@ __device__ __forceinline__ double stencil_run_rb(const DevPlan& P, const double*
 
 template <bool VAR, int OUT, bool DOT>
 __device__ __forceinline__ double stencil_run(const DevPlan& P, const double* __restrict__ x, double* __restrict__ y,
-                                              const double* __restrict__ f, int first, int stride, int tx,
-                                              bool remap) {
-  return P.st_rows == 2 ? stencil_run_rb<2, VAR, OUT, DOT>(P, x, y, f, first, stride, tx, remap)
-                        : stencil_run_rb<1, VAR, OUT, DOT>(P, x, y, f, first, stride, tx, remap);
+                                              const double* __restrict__ f, int first, int stride, int tx) {
+  return P.st_rows == 2 ? stencil_run_rb<2, VAR, OUT, DOT>(P, x, y, f, first, stride, tx)
+                        : stencil_run_rb<1, VAR, OUT, DOT>(P, x, y, f, first, stride, tx);
 }
 
 }  // namespace

@@ -1,8 +1,8 @@
 // Device code of the transform passes of z = P_alpha^{-1} r (Section 2.3): per-tile
 // bodies of the first x-DST pass (with the fused Lanczos step), the y-DST pass, the time
-// pass K Y K Y (or the single K of C_alpha^{-1}) and the last x-DST pass.  Each body is one workgroup's work on one tile; the kernels
-// run one tile per workgroup, the fused small-problem iteration runs every tile of a
-// right-hand side in one workgroup.
+// pass K Y K Y (or the single K of C_alpha^{-1}) and the last x-DST pass.  Each body is one
+// workgroup's work on one tile; the one-workgroup solves of small problems use the time
+// pass's core.
 #pragma once
 #include "abac_internal.h"
 
@@ -222,10 +222,9 @@ struct LanczosStep {
 // optionally fused with the Lanczos step
 // ---------------------------------------------------------------------------
 // One tile (2 S rows) of right-hand side b; the caller skips stopped right-hand sides.
-// tw: the length-L twiddle table (the plan's, or a copy the caller staged in LDS).
 template <typename T, int L, int WG>
 __device__ __forceinline__ void dstx_fwd_tile(const DevPlan& P, int mode, const double* __restrict__ in, int b,
-                                              int tile, const cplx<T>* __restrict__ tw) {
+                                              int tile) {
   using C = cplx<T>;
   constexpr int R = FftShape<T, L>::R, TPS = L / R, S = seqs_of<T, L, WG>(), Mx = L / 2;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -306,7 +305,7 @@ __device__ __forceinline__ void dstx_fwd_tile(const DevPlan& P, int mode, const 
     v[i] = C{zero || !va ? (T)0 : (neg ? -a : a), zero || !vb ? (T)0 : (neg ? -c : c)};
   }
   __syncthreads();
-  fft_seq<T, L, false>(v, j, lds + s, S, tw);
+  fft_seq<T, L, false>(v, j, lds + s, S, reinterpret_cast<const C*>(P.twx));
   const T scl = (T)(1.0 / sqrt((double)L));
   // stage the transformed rows ([2S][Mx+1] padded) and write them out contiguously
   __syncthreads();
@@ -623,10 +622,9 @@ __device__ __forceinline__ void time_tile(const DevPlan& P, int inv1, int b, int
 // last pass: inverse DST-I along x (transform precision in, FP64 out).
 // ---------------------------------------------------------------------------
 // One tile (2 S rows) of right-hand side b.  The caller skips stopped right-hand sides.
-// tw as for dstx_fwd_tile.
 template <typename T, int L, int WG>
 __device__ __forceinline__ void dstx_inv_tile(const DevPlan& P, int mode, double* __restrict__ outp, int b,
-                                                int tile, const cplx<T>* __restrict__ tw) {
+                                                int tile) {
   using C = cplx<T>;
   constexpr int R = FftShape<T, L>::R, TPS = L / R, S = seqs_of<T, L, WG>(), Mx = L / 2;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -663,7 +661,7 @@ __device__ __forceinline__ void dstx_inv_tile(const DevPlan& P, int mode, double
     v[i] = C{zero || !va ? (T)0 : (neg ? -a : a), zero || !vb ? (T)0 : (neg ? -c : c)};
   }
   __syncthreads();
-  fft_seq<T, L, false>(v, j, lds + s, S, tw);
+  fft_seq<T, L, false>(v, j, lds + s, S, reinterpret_cast<const C*>(P.twx));
   const double scl = 1.0 / sqrt((double)L);
   // stage the FP64 rows packed ([2S][nx]: the block's 2S output rows are one contiguous
   // run of memory, and the odd row length in 8-byte words spreads the sequences of a
@@ -680,15 +678,13 @@ __device__ __forceinline__ void dstx_inv_tile(const DevPlan& P, int mode, double
   }
   __syncthreads();
   double* o = out + (size_t)row0 * nx;
-  const int total = nrows * nx;   // < WG * R
-  // one contiguous run: 16-byte moves of pairs, and the odd last value
-  const int npair = total / 2;
+  // one contiguous run, in 16-byte moves of pairs (nrows is even: see dstx_fwd_tile)
+  const int npair = nrows * nx / 2;
   auto sweep = [&](auto stream) {
     for (int e = threadIdx.x; e < npair; e += WG)
       stream_store<decltype(stream)::value>(reinterpret_cast<dpair*>(o + 2 * e), *reinterpret_cast<const dpair*>(ostage + 2 * e));
   };
   stream_branch(P.stream, sweep);
-  if ((total & 1) && threadIdx.x == 0) o[total - 1] = ostage[total - 1];
 }
 
 // ---------------------------------------------------------------------------
