@@ -701,8 +701,13 @@ constexpr size_t slab_bytes() {
   return ((size_t)(L / 2 - 1) * (L / 2 + 1) * sizeof(T) + 15) / 16 * 16;
 }
 
-// parts of a level's inner products (Dots3): the waves of the largest workgroup slab_wg gives
-constexpr int kSlabParts = 8;
+// parts of a level's inner products (Dots3): the waves of the largest workgroup slab_wg gives,
+// or fewer where the level has less than 64 pairs for each
+template <int L>
+constexpr int slab_parts() {
+  constexpr int n = ((L / 2 - 1) * (L / 2 - 1) / 2 + 63) / 64;
+  return n < 8 ? n : 8;
+}
 
 template <typename T, int L, int WG>
 constexpr size_t slab_lds_of() {
@@ -785,31 +790,31 @@ __device__ __forceinline__ void dst2_fwd_tile(const DevPlan& P, int mode, const 
   };
   if (mode == FWD_LANCZOS) {
     const LanczosStep step(P, b);
-    constexpr int PB = BATCH / 2;
-    // the level in kSlabParts parts, whatever the workgroup: part w has the pairs of lanes
-    // 64 w .. 64 w + 63 of 64 kSlabParts, summed by one wave (t opaque: the parts' addresses
+    constexpr int PB = BATCH / 2, PARTS = slab_parts<L>();
+    // the level in PARTS parts, whatever the workgroup: part w has the pairs of lanes
+    // 64 w .. 64 w + 63 of 64 PARTS, summed by one wave (t opaque: the parts' addresses
     // hoisted out of the loop over them take 196 registers for 139)
     auto sweep = [&](auto stream) {
 #pragma unroll 1
-      for (int w = threadIdx.x >> 6; w < kSlabParts; w += WG / 64) {
+      for (int w = threadIdx.x >> 6; w < PARTS; w += WG / 64) {
         Dots3 d{0.0, 0.0, 0.0};
         int t = 64 * w + (threadIdx.x & 63);
         asm volatile("" : "+v"(t));
 #pragma unroll 1
-        for (int e0 = 0; e0 + 1 < cnt; e0 += 2 * PB * 64 * kSlabParts) {
+        for (int e0 = 0; e0 + 1 < cnt; e0 += 2 * PB * 64 * PARTS) {
           size_t e[PB];
           bool live[PB];
           dpair q[PB];
 #pragma unroll
           for (int u = 0; u < PB; ++u) {
-            const int i = e0 + 2 * (t + u * 64 * kSlabParts);
+            const int i = e0 + 2 * (t + u * 64 * PARTS);
             live[u] = i + 1 < cnt;
             e[u] = base + min(i, cnt - 2);
           }
           step.run<PB, decltype(stream)::value>(e, live, q, d);
 #pragma unroll
           for (int u = 0; u < PB; ++u) {
-            const int i = e0 + 2 * (t + u * 64 * kSlabParts);
+            const int i = e0 + 2 * (t + u * 64 * PARTS);
             if (live[u]) {
               put(i, q[u].x);
               put(i + 1, q[u].y);
@@ -836,7 +841,7 @@ __device__ __forceinline__ void dst2_fwd_tile(const DevPlan& P, int mode, const 
     }
   }
   __syncthreads();
-  if (mode == FWD_LANCZOS) dots_store<1, kSlabParts>(P, b, lvl, P.nt, 2, dred);
+  if (mode == FWD_LANCZOS) dots_store<1, slab_parts<L>()>(P, b, lvl, P.nt, 2, dred);
   slab_dst<T, L, WG, true>(slab, nx, exch, reinterpret_cast<const C*>(P.twx));
   slab_dst<T, L, WG, false>(slab, M, exch, reinterpret_cast<const C*>(P.twy));
   T* out = reinterpret_cast<T*>(P.scratch) + (size_t)b * P.NS + (size_t)lvl * P.ms;
