@@ -118,13 +118,16 @@ abac_status describe(int nx, int ny, int nt, double T, double alpha, int prec, i
   // each of the 1024 SIMDs).  Grids that never do (below about 4 M unknowns) are bound by
   // the march's chain of load latencies and take the shortest chunk (63^2 x 64 FP32, 10
   // iterations: 545 us per solve with chunk 8, 470 with chunk 2 and the folded delta below).
-  // The rule depends on the shape only (not on the batch), so a batched solve sums its
-  // partials in the same order as a single one.
+  // The partial sums follow this rule of the shape, so that a batched solve sums in the order
+  // of a single one.  Where the batch fills the GPU a block marches over several such chunks,
+  // up to 8 levels, and sums each: 64 x 1023 x 256 FP32 takes 63 us (one chunk of 2 levels a
+  // block: 107), 64 x 127^2 x 128 FP64 428 (546), whole solves 3.95 (4.62) and 28.8 ms (29.6).
   P.st_cols = nx >= 2 ? 2 : 1;
   P.st_rows = ny && nx >= 2 ? 2 : 1;
   P.st_threads = std::min(kStencilThreads, ((nx + P.st_cols - 1) / P.st_cols + 63) / 64 * 64);
-  stencil_chunk(P, 1);
-  P.maxparts = std::max(std::max(stencil_blocks(P), update_blocks(P)), std::max(P.nt * P.ny1 / 2 + dot_group_units(64), P.ms / 2));
+  P.st_chunk = stencil_chunk(P, 1);
+  P.st_march = stencil_chunk(P, batch) / P.st_chunk;
+  P.maxparts = std::max(std::max(stencil_parts(P), update_blocks(P)), std::max(P.nt * P.ny1 / 2 + dot_group_units(64), P.ms / 2));
   P.maxparts = (P.maxparts + 63) & ~63;
   P.prec = prec;
   // Where an iteration is bound by its launches (vectors within the L2s, 32 MB) every wave of

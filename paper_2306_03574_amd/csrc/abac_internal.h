@@ -181,7 +181,8 @@ struct DevPlan {
   int wg_x, wg_xi, wg_y, wg_t;
   int wg_s;            // fused 2D passes (0: separate x and y passes)
   int small;           // 1: one workgroup per right-hand side runs a whole iteration
-  int st_chunk;        // forward time levels per matvec block
+  int st_chunk;        // forward time levels per partial sum of the matvec
+  int st_march;        // chunks a matvec block marches over
   int st_threads;      // threads per matvec block
   int st_cols;         // columns per matvec thread (2, or 1 for a one-column grid)
   int st_rows;         // grid rows per matvec block (1 in 1D)
@@ -440,39 +441,42 @@ enum FinKind : int {
   FIN_FINAL = 6    // end of a solve: form u if it is stale
 };
 
-// matvec decomposition: a block covers a band of st_rows grid rows times
-// st_threads * st_cols columns, and st_chunk forward time levels (plus their mirrors)
+// matvec decomposition: a tile is a band of st_rows grid rows times st_threads * st_cols
+// columns; a block covers a tile and st_march chunks of st_chunk forward time levels (plus
+// their mirrors), and leaves one partial sum per chunk
 // two doubles moved by one 16-byte access; 8-byte alignment suffices on gfx950 (rows of
 // odd length start at odd 8-byte offsets)
 typedef double dpair __attribute__((ext_vector_type(2), aligned(8)));
 
 constexpr int kStencilThreads = 256;
+constexpr int kStencilMarch = 4;      // most chunks of a block: 8 levels in chunks of 2
 constexpr int kStencilWaves = 2048;   // 2 waves per SIMD on 256 CUs x 4 SIMDs
-__host__ __device__ inline int stencil_blocks(const DevPlan& P) {
+__host__ __device__ inline int stencil_tiles(const DevPlan& P) {
   const int cols = P.st_threads * P.st_cols;
-  const int tiles = ((P.ny1 + P.st_rows - 1) / P.st_rows) * ((P.nx + cols - 1) / cols);
-  const int nchunks = (P.nt / 2 + P.st_chunk - 1) / P.st_chunk;
-  return tiles * nchunks;
+  return ((P.ny1 + P.st_rows - 1) / P.st_rows) * ((P.nx + cols - 1) / cols);
 }
+__host__ __device__ inline int stencil_blocks(const DevPlan& P, int levels) {
+  return stencil_tiles(P) * ((P.nt / 2 + levels - 1) / levels);
+}
+// partial sums per right-hand side
+__host__ __device__ inline int stencil_parts(const DevPlan& P) { return stencil_blocks(P, P.st_chunk); }
 // The longest chunk of 64/32/16/8/4/2 levels whose blocks fill the GPU once at the matvec's
 // occupancy: those of one right-hand side down to 8 levels, of `rhs` of them below.
-inline void stencil_chunk(DevPlan& P, int rhs) {
-  P.st_chunk = 64;
-  while (P.st_chunk > 2 &&
-         (long long)stencil_blocks(P) * (P.st_chunk > 8 ? 1 : rhs) * (P.st_threads / 64) < kStencilWaves)
-    P.st_chunk /= 2;
+inline int stencil_chunk(const DevPlan& P, int rhs) {
+  int c = 64;
+  while (c > 2 && (long long)stencil_blocks(P, c) * (c > 8 ? 1 : rhs) * (P.st_threads / 64) < kStencilWaves) c /= 2;
+  return c;
 }
 // <A z_j, z_j> from the matvec's partials, by each wave that calls it, in one order: the
 // scalar step and the first transform pass (DevPlan::fold) get the same bits, so that a
 // batch whose vectors are too large to fold equals its right-hand sides on their own.
 __device__ __forceinline__ double delta_sum(const DevPlan& P, int b) {
-  double s = parts_share(part_slot(P, PART_DELTA, b), stencil_blocks(P), threadIdx.x & 63, 64);
+  double s = parts_share(part_slot(P, PART_DELTA, b), stencil_parts(P), threadIdx.x & 63, 64);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
   return s;
 }
 
-int stencil_grid(const DevPlan& P, int mode);
 int update_blocks(const DevPlan& P);
 // the first pass's partials of an inner product per right-hand side with tiles of wg threads,
 // and how many of them make a group

@@ -95,28 +95,27 @@ __device__ __forceinline__ void group_stencil(const GroupTable* __restrict__ G, 
   const MinresState* st = P.st + at.b;
   if (MODE == STENCIL_RESIDUAL ? st->state != ST_RUNNING || !st->need_check : !rhs_active(st)) return;
   const size_t off = (size_t)at.b * P.N;
-  const int side = stencil_side(P), nblk = stencil_blocks(P);
+  const int side = stencil_side(P), nblk = stencil_parts(P);   // blocks of one chunk each
   const int sub = threadIdx.x / P.st_threads, tx = threadIdx.x - sub * P.st_threads;
-  const int blk = at.lbk * side + sub;
+  const int blk = at.lbk * side + sub, lb = blk < nblk ? xcd_remap(blk, nblk) : 0;
   double acc = 0.0;
   if (sub < side && blk < nblk) {
-    // one logical block: the stride ends the walk over them after the first
     if (MODE == STENCIL_RESIDUAL) {
       const double* x = M.u + off;
       const double* f = M.f + off;
       double* y = P.R + off;
       if (st->want_r)
-        acc = P.coef_x ? stencil_run<true, OUT_RESREV, false>(P, x, y, f, blk, nblk, tx)
-                       : stencil_run<false, OUT_RESREV, false>(P, x, y, f, blk, nblk, tx);
+        acc = P.coef_x ? stencil_run<true, OUT_RESREV, false>(P, x, y, f, lb, 1, tx)
+                       : stencil_run<false, OUT_RESREV, false>(P, x, y, f, lb, 1, tx);
       else
-        acc = P.coef_x ? stencil_run<true, OUT_RESNORM, false>(P, x, nullptr, f, blk, nblk, tx)
-                       : stencil_run<false, OUT_RESNORM, false>(P, x, nullptr, f, blk, nblk, tx);
+        acc = P.coef_x ? stencil_run<true, OUT_RESNORM, false>(P, x, nullptr, f, lb, 1, tx)
+                       : stencil_run<false, OUT_RESNORM, false>(P, x, nullptr, f, lb, 1, tx);
     } else {
       const int j = st->iter + 1;
       const double* x = P.Z[zslot(j)] + off;
       double* y = P.V[(j + 1) % 3] + off;
-      acc = P.coef_x ? stencil_run<true, OUT_REV, true>(P, x, y, nullptr, blk, nblk, tx)
-                     : stencil_run<false, OUT_REV, true>(P, x, y, nullptr, blk, nblk, tx);
+      acc = P.coef_x ? stencil_run<true, OUT_REV, true>(P, x, y, nullptr, lb, 1, tx)
+                     : stencil_run<false, OUT_REV, true>(P, x, y, nullptr, lb, 1, tx);
     }
   }
 #pragma unroll
@@ -126,7 +125,7 @@ __device__ __forceinline__ void group_stencil(const GroupTable* __restrict__ G, 
   if (tx == 0 && sub < side && blk < nblk) {
     double s = 0.0;
     for (int i = 0; i < P.st_threads / 64; ++i) s += red[threadIdx.x / 64 + i];
-    part_slot(P, MODE == STENCIL_MINRES ? PART_DELTA : PART_RES, at.b)[blk] = s;
+    part_slot(P, MODE == STENCIL_MINRES ? PART_DELTA : PART_RES, at.b)[lb] = s;
   }
   __syncthreads();
 }
@@ -158,7 +157,7 @@ __device__ __forceinline__ void group_fin(const GroupTable* __restrict__ G, int 
   const Where at = locate(G, GS_FIN, w);
   const DevPlan& P = G->m[at.r].P;
   if (kind == FIN_DELTA && P.fold) return;
-  const int nparts = kind == FIN_GAMMA_ITER ? P.gamma_nparts : stencil_blocks(P);
+  const int nparts = kind == FIN_GAMMA_ITER ? P.gamma_nparts : stencil_parts(P);
   fin_step(P, at.b, kind, FinArgs{}, [&](Dots3* dots) {
     if (kind == FIN_GAMMA_ITER) *dots = sum_dots(P, at.b, G->m[at.r].dots);
     if (kind == FIN_DELTA) return threadIdx.x < 64 ? delta_sum(P, at.b) : 0.0;
@@ -457,7 +456,7 @@ bool member_shape(const DevPlan& P, int prec, int blocks[GS_COUNT], size_t lds[G
     lds[k] = 0;
   }
   const int Lx = 2 * P.Mx, Ly = 2 * P.My;
-  blocks[GS_STENCIL] = (stencil_blocks(P) + stencil_side(P) - 1) / stencil_side(P);
+  blocks[GS_STENCIL] = (stencil_parts(P) + stencil_side(P) - 1) / stencil_side(P);
   blocks[GS_VEC] = update_blocks(P);
   blocks[GS_FIN] = 1;
   if (P.wg_s) {

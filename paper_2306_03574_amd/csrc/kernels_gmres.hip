@@ -420,7 +420,7 @@ hipError_t launch_ginit(const DevPlan& P, const double* f, double* u, hipStream_
 }
 
 hipError_t launch_gfin(const DevPlan& P, int kind, const FinArgs& a, int restart, hipStream_t s) {
-  const int nparts = kind == G_CHECK ? stencil_grid(P, STENCIL_RESVEC) : update_blocks(P);
+  const int nparts = kind == G_CHECK ? stencil_parts(P) : update_blocks(P);
   hipLaunchKernelGGL(k_gfin, dim3(P.B), dim3(kGFinThreads), 0, s, P, kind, nparts, a, restart);
   return hipGetLastError();
 }

@@ -17,9 +17,13 @@ namespace {
 
 
 // One kernel per mode and coefficient kind, so each gets the registers its own path
-// needs.
-template <int MODE, bool VAR>
+// needs.  SPLIT: the block marches over several chunks and leaves a partial of each.  The
+// others get no third wave per SIMD, which 166 registers would allow: their chunks are made
+// for two (511^2 x 512: 504 us with three, as 1024 blocks then run as 768 and 256, 431 with two).
+constexpr bool stencil_sums(int mode) { return mode != STENCIL_PLAIN && mode != STENCIL_T; }
+template <int MODE, bool VAR, bool SPLIT>
 __global__ void __launch_bounds__(kStencilThreads)
+__attribute__((amdgpu_waves_per_eu(1, stencil_sums(MODE) && !VAR && !SPLIT ? 2 : 8)))
 k_stencil(DevPlan P, const double* __restrict__ xin, double* __restrict__ yout, const double* __restrict__ fref) {
   const int b = blockIdx.y;
   MinresState* st = P.st + b;
@@ -37,25 +41,39 @@ k_stencil(DevPlan P, const double* __restrict__ xin, double* __restrict__ yout, 
   x += (size_t)b * P.N;
   if (y) y += (size_t)b * P.N;
   const double* f = fref ? fref + (size_t)b * P.N : nullptr;
+  const int lb = xcd_remap(blockIdx.x, gridDim.x);
   if (MODE == STENCIL_PLAIN) {
-    stencil_run<VAR, OUT_REV, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x);
+    stencil_run<VAR, OUT_REV, false>(P, x, y, f, lb, P.st_march, threadIdx.x);
     return;
   }
   if (MODE == STENCIL_T) {
-    stencil_run<VAR, OUT_NAT, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x);
+    stencil_run<VAR, OUT_NAT, false>(P, x, y, f, lb, P.st_march, threadIdx.x);
     return;
   }
+  __shared__ double red[kStencilMarch][kStencilThreads / 64];
+  auto emit = [&](int q, double v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    if ((threadIdx.x & 63) == 0) red[q][threadIdx.x >> 6] = v;
+  };
   double acc;
   if (MODE == STENCIL_RESIDUAL && st->want_r)
-    acc = stencil_run<VAR, OUT_RESREV, false>(P, x, P.R + (size_t)b * P.N, f, blockIdx.x, gridDim.x, threadIdx.x);
+    acc = stencil_run<VAR, OUT_RESREV, false, SPLIT>(P, x, P.R + (size_t)b * P.N, f, lb, P.st_march, threadIdx.x, emit);
   else if (MODE == STENCIL_MINRES)
-    acc = stencil_run<VAR, OUT_REV, true>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x);
+    acc = stencil_run<VAR, OUT_REV, true, SPLIT>(P, x, y, f, lb, P.st_march, threadIdx.x, emit);
   else if (MODE == STENCIL_RESVEC)
-    acc = stencil_run<VAR, OUT_RESVEC, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x);
+    acc = stencil_run<VAR, OUT_RESVEC, false, SPLIT>(P, x, y, f, lb, P.st_march, threadIdx.x, emit);
   else
-    acc = stencil_run<VAR, OUT_RESNORM, false>(P, x, y, f, blockIdx.x, gridDim.x, threadIdx.x);
-  const double bs = block_sum(acc);
-  if (threadIdx.x == 0) part_slot(P, MODE == STENCIL_MINRES ? PART_DELTA : PART_RES, b)[blockIdx.x] = bs;
+    acc = stencil_run<VAR, OUT_RESNORM, false, SPLIT>(P, x, y, f, lb, P.st_march, threadIdx.x, emit);
+  if (!SPLIT) emit(0, acc);
+  __syncthreads();
+  // the partial of a chunk: its waves in order, at the chunk's place whatever the march
+  const int tiles = stencil_tiles(P), q = threadIdx.x, chunk = lb / tiles * P.st_march + q;
+  if (q < P.st_march && chunk * tiles < stencil_parts(P)) {
+    double s = 0.0;
+    for (int w = 0; w < (int)blockDim.x / 64; ++w) s += red[q][w];
+    part_slot(P, MODE == STENCIL_MINRES ? PART_DELTA : PART_RES, b)[chunk * tiles + lb % tiles] = s;
+  }
 }
 
 // f_1 = tau^2 src_0 / 2 + tau psi1 + psi0; f_2 = tau^2 src_1 - L psi0; f_k = tau^2 src_{k-1}
@@ -194,11 +212,6 @@ k_fin(DevPlan P, int kind, int nparts, DotParts ndots, FinArgs a) {
 
 }  // namespace
 
-int stencil_grid(const DevPlan& P, int mode) {
-  (void)mode;
-  return stencil_blocks(P);
-}
-
 int update_blocks(const DevPlan& P) {
   long long want = (P.N + (long long)kVecThreads * kVecPerThread - 1) / ((long long)kVecThreads * kVecPerThread);
   if (want > kVecMaxBlocks) want = kVecMaxBlocks;
@@ -208,19 +221,18 @@ int update_blocks(const DevPlan& P) {
 
 hipError_t launch_stencil(const DevPlan& plan, int mode, const double* x, double* y, const double* f, hipStream_t s) {
   DevPlan P = plan;
-  // Without a sum over its blocks the march may depend on the batch too (each value is the
-  // same expression in any chunk): P^{-1} and A of 8 x 255^2 x 8 107.2 -> 104.8 us against
-  // the chunks of 2 levels that one right-hand side takes.  Chunks above 8 levels where the
-  // batch fills the GPU with them gained nothing (64 x 63^2 x 64), so those follow the shape.
-  if (mode == STENCIL_PLAIN || mode == STENCIL_T) stencil_chunk(P, P.B);
-  dim3 grid(stencil_grid(P, mode), P.B);
+  // the one-column tile marches its columns one after the other: its sums take a chunk at a time
+  if (stencil_sums(mode) && (P.coef_x || P.st_cols != 2)) P.st_march = 1;
+  const dim3 grid(stencil_blocks(P, P.st_march * P.st_chunk), P.B);
   const dim3 block(P.st_threads);
 #define ABAC_STENCIL_CASE(M)                                                                           \
   case M:                                                                                              \
     if (P.coef_x)                                                                                      \
-      hipLaunchKernelGGL((k_stencil<M, true>), grid, block, 0, s, P, x, y, f);                         \
+      hipLaunchKernelGGL((k_stencil<M, true, false>), grid, block, 0, s, P, x, y, f);                  \
+    else if (stencil_sums(M) && P.st_march > 1)                                                        \
+      hipLaunchKernelGGL((k_stencil<M, false, stencil_sums(M)>), grid, block, 0, s, P, x, y, f);       \
     else                                                                                               \
-      hipLaunchKernelGGL((k_stencil<M, false>), grid, block, 0, s, P, x, y, f);                        \
+      hipLaunchKernelGGL((k_stencil<M, false, false>), grid, block, 0, s, P, x, y, f);                 \
     break;
   switch (mode) {
     ABAC_STENCIL_CASE(STENCIL_PLAIN)
@@ -274,7 +286,7 @@ hipError_t launch_fin(const DevPlan& P, int kind, const FinArgs& a, hipStream_t 
     case FIN_BNORM: nparts = update_blocks(P); break;
     case FIN_GAMMA_INIT:
     case FIN_GAMMA_ITER: nparts = P.gamma_nparts; break;
-    default: nparts = stencil_grid(P, STENCIL_RESIDUAL); break;
+    default: nparts = stencil_parts(P); break;
   }
   const DotParts ndots = kind == FIN_GAMMA_ITER && P.prec != 2 ? dot_parts(P, P.wg_x) : DotParts{0, 2};
   hipLaunchKernelGGL(k_fin, dim3(P.B), dim3(kFinThreads), 0, s, P, kind, nparts, ndots, a);

@@ -117,7 +117,7 @@ __device__ __forceinline__ void band_level(const DevPlan& P, const Band<RB, VAR>
 template <int RB, bool VAR, int OUT, bool DOT>
 __device__ __forceinline__ double stencil_tile(const DevPlan& P, const double* __restrict__ x,
                                                double* __restrict__ y, const double* __restrict__ f, int band,
-                                               int ix_raw, int chunk) {
+                                               int ix_raw, int chunk, int levels) {
   const int n = P.nt, m = P.m, nx = P.nx, ny1 = P.ny1;
   const bool active = ix_raw < nx;
   const int ix = min(ix_raw, nx - 1);   // inactive lanes repeat the last column and store nothing
@@ -137,8 +137,8 @@ __device__ __forceinline__ double stencil_tile(const DevPlan& P, const double* _
     Bd.cw = ix > 0 ? P.cx : 0.0;
     Bd.ce = ix < nx - 1 ? P.cx : 0.0;
   }
-  const int k0 = chunk * P.st_chunk;
-  const int k1 = min(k0 + P.st_chunk, n / 2);
+  const int k0 = chunk * levels;
+  const int k1 = min(k0 + levels, n / 2);
   double acc = 0.0;
   double Lf2[RB], zf1[RB], Lf1[RB], zb0[RB], Lb0[RB], zb1[RB], Lb1[RB], tL[RB], tz[RB];
   {
@@ -257,10 +257,13 @@ __device__ __forceinline__ void pair_L(const DevPlan& P, int iy0, double cw0, do
   }
 }
 
-template <int RB, int OUT, bool DOT>
+//
+// With SPLIT the sum of each P.st_chunk levels goes to emit(index, sum) as the march gets
+// there: a batch that fills the GPU with long marches sums what short ones would.
+template <int RB, int OUT, bool DOT, bool SPLIT, typename Emit>
 __device__ __forceinline__ double stencil_tile2(const DevPlan& P, const double* __restrict__ x,
                                                 double* __restrict__ y, const double* __restrict__ f, int band, int c,
-                                                int chunk) {
+                                                int chunk, int levels, Emit&& emit) {
   const int n = P.nt, m = P.m, nx = P.nx, ny1 = P.ny1;
   const bool act0 = c < nx, act1 = c + 1 < nx;
   const int iy0 = band * RB;
@@ -277,8 +280,8 @@ __device__ __forceinline__ double stencil_tile2(const DevPlan& P, const double* 
   const double cw0 = c > 0 ? P.cx : 0.0;
   const double ce0 = c < nx - 1 ? P.cx : 0.0;
   const double ce1 = c + 1 < nx - 1 ? P.cx : 0.0;
-  const int k0 = chunk * P.st_chunk;
-  const int k1 = min(k0 + P.st_chunk, n / 2);
+  const int k0 = chunk * levels;
+  const int k1 = min(k0 + levels, n / 2);
   double acc = 0.0;
   double Lf2[RB][2], zf1[RB][2], Lf1[RB][2], zb0[RB][2], Lb0[RB][2], zb1[RB][2], Lb1[RB][2], tL[RB][2], tz[RB][2];
   {
@@ -371,46 +374,49 @@ __device__ __forceinline__ double stencil_tile2(const DevPlan& P, const double* 
         zb0[r][q] = zb1[r][q]; Lb0[r][q] = Lb1[r][q]; zb1[r][q] = zb2[r][q]; Lb1[r][q] = Lb2[r][q];
       }
     }
+    if (SPLIT && ((k + 1) % P.st_chunk == 0 || k + 1 == k1)) {
+      emit((k - k0) / P.st_chunk, acc);
+      acc = 0.0;
+    }
   }
   return acc;
 }
 
-// Logical blocks first, first + stride, ... of one right-hand side, lane tx of each
-// (in XCD-aware order, so that consecutive logical blocks, neighbouring column tiles and
-// bands of the same levels, share an L2).  A block covers st_threads * st_cols columns:
-// with two columns per thread the constant-coefficient tile takes columns
-// (2 tx, 2 tx + 1) of its tile, the variable-coefficient tile marches columns tx and
-// st_threads + tx one after the other.
-template <int RB, bool VAR, int OUT, bool DOT>
+// Logical block lb of one right-hand side (chunk-major: consecutive ones are neighbouring
+// column tiles and bands of the same levels), marching over `march` chunks, lane tx of it;
+// returns the lane's part of its sum, or with SPLIT passes those of its chunks to emit.  A
+// block covers st_threads * st_cols columns: with two columns per thread the
+// constant-coefficient tile takes columns (2 tx, 2 tx + 1) of its tile, the
+// variable-coefficient tile marches columns tx and st_threads + tx one after the other.
+template <int RB, bool VAR, int OUT, bool DOT, bool SPLIT, typename Emit>
 __device__ __forceinline__ double stencil_run_rb(const DevPlan& P, const double* __restrict__ x,
-                                                 double* __restrict__ y, const double* __restrict__ f, int first,
-                                                 int stride, int tx) {
-  const int cols = P.st_threads * P.st_cols;
+                                                 double* __restrict__ y, const double* __restrict__ f, int lb,
+                                                 int march, int tx, Emit&& emit) {
+  const int cols = P.st_threads * P.st_cols, levels = march * P.st_chunk;
   const int xtiles = (P.nx + cols - 1) / cols;
   const int tiles = ((P.ny1 + RB - 1) / RB) * xtiles;
-  const int nblk = stencil_blocks(P);
-  double acc = 0.0;
-  for (int w = first; w < nblk; w += stride) {
-    const int lb = xcd_remap(w, nblk);
-    const int tile = lb % tiles;
-    const int band = tile / xtiles, c0 = (tile % xtiles) * cols, chunk = lb / tiles;
-    if constexpr (!VAR) {
-      if (P.st_cols == 2) {
-        acc += stencil_tile2<RB, OUT, DOT>(P, x, y, f, band, c0 + 2 * tx, chunk);
-        continue;
-      }
-    }
-    for (int q = 0; q < P.st_cols; ++q)
-      acc += stencil_tile<RB, VAR, OUT, DOT>(P, x, y, f, band, c0 + q * P.st_threads + tx, chunk);
+  const int tile = lb % tiles;
+  const int band = tile / xtiles, c0 = (tile % xtiles) * cols, chunk = lb / tiles;
+  if constexpr (!VAR) {
+    if (P.st_cols == 2)
+      return stencil_tile2<RB, OUT, DOT, SPLIT>(P, x, y, f, band, c0 + 2 * tx, chunk, levels, emit);
   }
+  double acc = 0.0;
+  for (int q = 0; q < P.st_cols; ++q)
+    acc += stencil_tile<RB, VAR, OUT, DOT>(P, x, y, f, band, c0 + q * P.st_threads + tx, chunk, levels);
   return acc;
 }
 
+template <bool VAR, int OUT, bool DOT, bool SPLIT, typename Emit>
+__device__ __forceinline__ double stencil_run(const DevPlan& P, const double* __restrict__ x, double* __restrict__ y,
+                                              const double* __restrict__ f, int lb, int march, int tx, Emit&& emit) {
+  return P.st_rows == 2 ? stencil_run_rb<2, VAR, OUT, DOT, SPLIT>(P, x, y, f, lb, march, tx, emit)
+                        : stencil_run_rb<1, VAR, OUT, DOT, SPLIT>(P, x, y, f, lb, march, tx, emit);
+}
 template <bool VAR, int OUT, bool DOT>
 __device__ __forceinline__ double stencil_run(const DevPlan& P, const double* __restrict__ x, double* __restrict__ y,
-                                              const double* __restrict__ f, int first, int stride, int tx) {
-  return P.st_rows == 2 ? stencil_run_rb<2, VAR, OUT, DOT>(P, x, y, f, first, stride, tx)
-                        : stencil_run_rb<1, VAR, OUT, DOT>(P, x, y, f, first, stride, tx);
+                                              const double* __restrict__ f, int lb, int march, int tx) {
+  return stencil_run<VAR, OUT, DOT, false>(P, x, y, f, lb, march, tx, [](int, double) {});
 }
 
 }  // namespace
