@@ -172,10 +172,16 @@ abac_status abac_apply_Pinv_noalloc(int nx, int ny, int nt, double T, double alp
 
 /* Solve Y T u = Y f for every right-hand side in the batch by preconditioned MINRES
  * with zero initial guess (Section 3).  Stops a right-hand side at the first
- * iteration whose residual ||Y f - Y T u||_2 <= tol ||Y f||_2 (tracked by the MINRES
- * residual recurrence and confirmed explicitly; iterations continue with explicit
- * checks if the confirmation fails).  Host-synchronous.  f must stay valid and
- * unchanged during the call; u receives the iterates.
+ * iteration whose residual ||Y f - Y T u||_2 <= tol ||Y f||_2 (bounded from inner
+ * products of the Lanczos vectors and confirmed explicitly; iterations continue with
+ * explicit checks if the confirmation fails).  f must stay valid and unchanged during
+ * the call; u receives the iterates.
+ * Host-synchronous: on return u and the results are complete, and nothing that is still
+ * queued reads f or u.  The stream need not be idle: the solve's last scalar step may
+ * still write the workspace, and kernels that find the solve stopped may still run.
+ * Calls on this plan are ordered behind them; other use of the workspace's memory has to
+ * wait for the stream (abac_plan_destroy does).  The calling thread waits for the device
+ * in every iteration, up to a millisecond without sleeping.
  *   iters, relres, status: host arrays of length batch (status may be NULL) that
  *   receive per right-hand side the iteration count, the explicit relative residual
  *   and the status (ABAC_OK, ABAC_ENOTCONV with the last iterate in u, or
@@ -202,11 +208,12 @@ abac_status abac_minres_finish(abac_plan *plan, int *iters, double *relres, int 
  * precision), each with a solve begun by abac_minres_begin.  abac_group_advance runs
  * one MINRES iteration (Section 3's solver) of every member with ONE launch per step
  * of the iteration for all of them -- the matvec, the scalar steps, the three
- * transform passes of Section 2.3 done twice, the residual recurrence and the
- * stopping test -- instead of one launch per step per member, which is what bounds
- * small grids.  Each member's results are bitwise those of its own solve
- * (abac_minres_solve on the same plan): the same tiles compute the same values and
- * every reduction is grouped as in the member's own kernels.
+ * transform passes of Section 2.3 done twice, the stopping test and the check of
+ * members that may have converged -- instead of one launch per step per member, which is
+ * what bounds small grids.  Each member's results are bitwise those of its own solve
+ * (abac_minres_solve on the same plan): the same arithmetic computes the same values and
+ * every reduction is summed in the order of the member's own kernels, which the shape
+ * alone fixes.
  * ------------------------------------------------------------------------- */
 typedef struct abac_group abac_group;
 
@@ -262,7 +269,8 @@ abac_status abac_group_check(abac_group *group, int *aborted);
  * ends by forming u and restarting from its explicit residual.  f, u: [batch][nt][...]
  * device vectors (u must not alias f); iters, relres, status: host arrays of batch
  * entries (may be NULL).  1 <= restart <= 15 (the Arnoldi basis uses the plan's Krylov
- * vectors).  Host-synchronous (one small device-to-host read per step).  Returns
+ * vectors).  Host-synchronous as abac_minres_solve (the host reads one record per step
+ * from mapped memory).  Returns
  * ABAC_OK, ABAC_ENOTCONV (some right-hand side reached maxit), ABAC_EBREAKDOWN
  * (non-finite values) or ABAC_EINVAL. */
 abac_status abac_gmres_solve(abac_plan *plan, const double *f, double *u, double tol, int maxit, int restart,

@@ -132,16 +132,15 @@ abac_status describe(int nx, int ny, int nt, double T, double alpha, int prec, i
   P.prec = prec;
   // Where an iteration is bound by its launches (vectors within the L2s, 32 MB) every wave of
   // the first pass sums the matvec's partials itself, and the scalar step of delta_j is no
-  // launch of its own (1D 1023 x 256 FP32, with the shorter march: 711 -> 620 us per solve).
-  // Larger grids keep it (4.7 us of an iteration of 400 us at 255^2 x 256, where the pass
+  // launch of its own.  Whole solves of 30 shapes against the launched step: 0.95 to 0.96 of
+  // the time at 2 to 8 MB, 0.96 to 0.98 at 16, 0.97 to 0.99 at 24, 0.98 to 1.00 at 32 (1.0003 at 511^2 x
+  // 16).  Larger grids keep it (4.7 us of an iteration of 400 us at 255^2 x 256, where the pass
   // would read 8 KB more in each of 32 k waves).
   // Never where that pass leaves an inner product's partials in the matvec's slots
   // (dots_apart): its later blocks would sum what its earlier ones wrote.
   P.fold = prec != ABAC_PREC_NONE && (long long)P.N * P.B * 8 <= (32ll << 20) && dots_apart(P);
-  // 64 MB: twice the L2s together.  Below it the next pass finds a stored vector in L2
-  // (63 x 64 with 256 right-hand sides, 8 MB: 416 us per solve with plain accesses, 449
-  // marked); above it the mark leaves the cache to the scratch (255^2 x 256, 133 MB: see
-  // stream_load).
+  // 64 MB: twice the L2s together.  Below it the next pass finds a stored vector in L2, above
+  // it the mark leaves the cache to the scratch (both sides measured: see stream_load).
   P.stream = (long long)P.N * P.B * 8 >= (64ll << 20);
   return ABAC_OK;
 }

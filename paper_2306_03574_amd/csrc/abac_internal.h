@@ -365,8 +365,11 @@ __device__ __forceinline__ double sum_parts(const double* __restrict__ part, int
 // of 1 GiB 5.7 and 6.3.  Loads of the scratch itself (y and time passes) are faster plain:
 // 255^2 x 256 FP64 4.04 ms per solve against 4.12 to 4.17 with them marked.
 //
-// They are marked only where the plan's vectors exceed the L2s (P.stream): the next pass
-// finds a smaller vector there.  stream_branch makes the choice outside a sweep's loops; its
+// They are marked only where the vectors of the batch take 64 MB, twice the L2s (P.stream): the
+// next pass finds a smaller vector there.  Whole solves with the marks against without:
+// 1.01 to 1.06 of the time at 16 MB, 1.01 to 1.04 at 32, 1.01 to 1.02 at 47, 0.98 to 1.01 at 62 to
+// 64, 0.96 to 1.00 at 79 to 95, 0.90 to 0.93 at 127.  The iterate's reads of the basis are marked
+// at every size (form_from_basis).  stream_branch makes the choice outside a sweep's loops; its
 // marked branch holds an empty asm statement, since the compiler merges two branches that
 // differ in the marks alone into one of plain accesses.
 template <bool STREAM, typename V>
@@ -461,7 +464,8 @@ __host__ __device__ inline int stencil_blocks(const DevPlan& P, int levels) {
 // partial sums per right-hand side
 __host__ __device__ inline int stencil_parts(const DevPlan& P) { return stencil_blocks(P, P.st_chunk); }
 // The longest chunk of 64/32/16/8/4/2 levels whose blocks fill the GPU once at the matvec's
-// occupancy: those of one right-hand side down to 8 levels, of `rhs` of them below.
+// occupancy: those of one right-hand side down to 8 levels, of `rhs` of them below.  (More
+// than 8 levels where a batch fills the GPU with them gained nothing: 64 x 63^2 x 64.)
 inline int stencil_chunk(const DevPlan& P, int rhs) {
   int c = 64;
   while (c > 2 && (long long)stencil_blocks(P, c) * (c > 8 ? 1 : rhs) * (P.st_threads / 64) < kStencilWaves) c /= 2;

@@ -8,9 +8,10 @@
 // tile (the same per-tile device code as the member's own kernels) for its grid.  All
 // list kernels use one workgroup size, kGroupWG threads (the scalar steps kFinThreads),
 // so the tile of a transform pass is the one of that size; those passes are computed by
-// the same arithmetic whatever the tile, the reductions are grouped as in the members'
-// own kernels (one partial per logical matvec or vector block, one per mode pair of
-// the time pass), and each member keeps its own state, partials and snapshots.  A
+// the same arithmetic whatever the tile, the reductions are summed in the order of the
+// members' own kernels, which the shape fixes (one partial per chunk of a matvec tile and
+// per vector block, the units of the first pass's inner products, one partial per mode pair
+// of the time pass), and each member keeps its own state, partials and snapshots.  A
 // member's results are therefore bitwise those of its solo solve.
 //
 // The persistent kernel runs the same step bodies for several iterations in one
