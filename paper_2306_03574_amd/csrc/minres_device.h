@@ -116,7 +116,8 @@ __device__ __forceinline__ void form_done(MinresState* st, MinresExt* x) {
 
 // Bounds on ||r_j|| after the Givens step of iteration j (st->iter), from the inner
 // products of the first transform pass (see MinresExt); returns the estimate of
-// ||r_j||^2.  Sums of squares carry a relative rounding slack of 1e-13 of their terms.
+// ||r_j||^2.  The unrolled sums carry a relative rounding slack of 1e-13 of their terms; the
+// tracked vector's norm is compared as it is, as an explicit one would be.
 __device__ __forceinline__ double residual_bounds(MinresState* st, MinresExt* x, const Dots3& d, bool identity,
                                                   double* lo, double* hi) {
   const double r1 = st->r1, r2 = st->r2;
